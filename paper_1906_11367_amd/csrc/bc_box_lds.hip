@@ -1,0 +1,303 @@
+// Box filter kernels on tables built in LDS: forward (plain and strided) and
+// backward (input and box-parameter gradients).  gfx950, wave64.
+#include "bc_box.hpp"
+
+namespace bc {
+
+// Forward on a map's table in LDS, for the boxes b0 .. b0+nb-1 of channel c.
+// Items of one box are (row segment, 3-column chunk), chunk fastest so that
+// adjacent lanes write adjacent columns; each box's items are padded to a
+// multiple of 64 (per_box_p) so that a wave works on one box and reads its
+// taps through scalar loads.
+template <typename T, typename OutT, int SEG, bool kOffset, bool kInt, int Q = kQ, bool kPack = false>
+__device__ __forceinline__ void fwd_boxes(const LdsTable<T>& tab, const int* __restrict__ taps,
+                                          OutT* __restrict__ y, int map, int c, int b0, int nb, int H, int W,
+                                          int B, int per_box_p, float mu) {
+  const int nch = (W + Q - 1) / Q, nseg = (H + SEG - 1) / SEG, per_box = nch * nseg;
+  for (int it = threadIdx.x; it < nb * per_box_p; it += blockDim.x) {
+    const int bl = __builtin_amdgcn_readfirstlane(it / per_box_p);
+    const int r = it - bl * per_box_p;
+    if (r >= per_box) continue;
+    const int seg = r / nch, ch = r - seg * nch;
+    const int b = b0 + bl;
+    const Taps<T> tp = typed_taps<T>(load_taps(taps + (size_t)(c * B + b) * 16, W, H));
+    OutT* out = y + ((size_t)map * B + b) * H * W;
+    const int x0 = ch * Q, y0 = seg * SEG, y1 = min(y0 + SEG, H);
+    StoreRows<OutT, T, false, Q, kPack> em{out, W, x0, y0 * W + x0};
+    if (y0 + SEG <= H && x0 + Q <= W) walk_fwd<SEG, T, kOffset, true, kInt, Q>(tab, tp, H, W, x0, y0, y1, mu, em);
+    else walk_fwd<SEG, T, kOffset, false, kInt, Q>(tab, tp, H, W, x0, y0, y1, mu, em);
+  }
+}
+
+// Forward, table in LDS: one block per (map, group of bpg boxes).  The block
+// builds the map's table once and evaluates every box of its group.
+// kW > 0: the map width compiled in (W is then ignored), as in the LDS
+// backward.  Q: columns per item; kPack: packed bf16 row stores (StoreRows).
+template <typename T, typename OutT, int SEG, bool kOffset, bool kInt, int kW = 0, int Q = kQ, bool kPack = false>
+__global__ __launch_bounds__(256) void k_box_fwd_lds(const T* __restrict__ x, const int* __restrict__ taps,
+                                                     OutT* __restrict__ y, int C, int H, int W_arg, int B, int bpg,
+                                                     int per_box_p) {
+  const int W = kW > 0 ? kW : W_arg;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  T* S = reinterpret_cast<T*>(smem_raw);
+  __shared__ float red[16];
+  const int pitch = lds_pitch_dev(W);
+  const int ngrp = (B + bpg - 1) / bpg;
+  const int map = blockIdx.x / ngrp, grp = blockIdx.x - map * ngrp;
+  const T* src = x + (size_t)map * H * W;
+  float mu = 0.f;
+  if (kOffset) mu = block_mean(reinterpret_cast<const float*>(src), H * W, red);
+  build_table_lds<T, true>(src, S, H, W, pitch, mu, kOffset);
+  const int b0 = grp * bpg;
+  fwd_boxes<T, OutT, SEG, kOffset, kInt, Q, kPack>(LdsTable<T>{S, pitch, W, H}, taps, y, map, map % C, b0,
+                                                   min(bpg, B - b0), H, W, B, per_box_p, mu);
+}
+
+// Strided forward (stride s > 1) on a map's table in LDS, boxes b0 .. b0+nb-1
+// of channel c: items are (output column, segment of kSegS output rows),
+// column fastest; a box's items are padded to per_box_p (a multiple of 64)
+// so each wave serves one box.
+template <typename T, typename OutT, bool kOffset, bool kInt>
+__device__ __forceinline__ void fwd_boxes_strided(const LdsTable<T>& tab, const int* __restrict__ taps,
+                                                  OutT* __restrict__ y, int map, int c, int b0, int nb, int H, int W,
+                                                  int B, int s, int Ho, int Wo, int per_box_p, float mu) {
+  const int per_box = Wo * ((Ho + kSegS - 1) / kSegS);
+  for (int it = threadIdx.x; it < nb * per_box_p; it += blockDim.x) {
+    const int bl = __builtin_amdgcn_readfirstlane(it / per_box_p);
+    const int r = it - bl * per_box_p;
+    if (r >= per_box) continue;
+    const int seg = r / Wo, j = r - seg * Wo;
+    const int b = b0 + bl;
+    const Taps<T> tp = typed_taps<T>(load_taps(taps + (size_t)(c * B + b) * 16, W, H));
+    const int i0 = seg * kSegS;
+    StoreCol<OutT, T> em{y + ((size_t)map * B + b) * Ho * Wo, Wo, i0 * Wo + j};
+    box_walk_strided<kSegS, T, kOffset, kInt>(tab, tp, H, W, s * j, i0, min(i0 + kSegS, Ho), s, mu, em);
+  }
+}
+
+template <typename T, typename OutT, bool kOffset, bool kInt, int kW = 0>
+__global__ __launch_bounds__(256) void k_box_fwd_lds_strided(const T* __restrict__ x, const int* __restrict__ taps,
+                                                             OutT* __restrict__ y, int C, int H, int W_arg, int B, int s,
+                                                             int Ho, int Wo, int bpg, int per_box_p) {
+  const int W = kW > 0 ? kW : W_arg;  // kW > 0: the map width compiled in
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  T* S = reinterpret_cast<T*>(smem_raw);
+  __shared__ float red[16];
+  const int pitch = lds_pitch_dev(W);
+  const int ngrp = (B + bpg - 1) / bpg;
+  const int map = blockIdx.x / ngrp, grp = blockIdx.x - map * ngrp;
+  const T* src = x + (size_t)map * H * W;
+  float mu = 0.f;
+  if (kOffset) mu = block_mean(reinterpret_cast<const float*>(src), H * W, red);
+  build_table_lds(src, S, H, W, pitch, mu, kOffset);
+  const int b0 = grp * bpg;
+  fwd_boxes_strided<T, OutT, kOffset, kInt>(LdsTable<T>{S, pitch, W, H}, taps, y, map, map % C, b0,
+                                            min(bpg, B - b0), H, W, B, s, Ho, Wo, per_box_p, mu);
+}
+
+// Backward, table in LDS: one block per map (n, c); items (row segment,
+// chunk), one per thread, whose map values stay in registers.  For each box
+// b the table of grad_y[n][c*B+b] is built in LDS and the adjoint walk adds
+// the input gradient (in registers, summed over b) and the edge gradients;
+// each wave writes its edge-gradient sums to
+// partials[(n * nw + wave) * C*B + c*B + b][4].  kInt (boxes with integer
+// corners): the adjoint four-corner sums only, no edge gradients.  kUp
+// (stride s > 1): grad_y is [maps][Ho][Wo] and is tabulated zero-upsampled,
+// which makes every gradient that of the strided layer.  kRelu: gx is bf16,
+// store_item_relu_bf16 (not with kInt, which does not read x).
+// Four waves per SIMD: bounded to 128 VGPRs (from 144, three waves) the
+// 8-row items fit without spilling once the final stores recompute their
+// addresses (below); pose-layer backward 172.5 -> 151.5 us, results
+// bit-identical.  The 4-row items take 92.
+// kW > 0: the map width as a compile-time constant (W is then ignored), so
+// the table pitch is one too and every row offset of the scans, the walk and
+// the item loads and stores is an immediate of its LDS or global access
+// instead of a per-element address add; the results are the same bits.
+template <int SEG, bool kInt, bool kUp, int kMaxT, bool kRelu, int kW = 0>
+__global__ __launch_bounds__(kMaxT) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_box_bwd_lds(
+    const float* __restrict__ x, const int* __restrict__ taps, const float* __restrict__ gy, void* __restrict__ gx,
+    float* __restrict__ partials, int C, int H, int W_arg, int B, int s, int Ho, int Wo) {
+  static_assert(!(kInt && kRelu), "the ReLU mask needs x");
+  const int W = kW > 0 ? kW : W_arg;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int pitch = lds_pitch_dev(W);
+  float* SG = reinterpret_cast<float*>(smem_raw);
+  const int map = blockIdx.x, n = map / C, c = map - n * C;
+  const int nw = blockDim.x >> 6, wave = threadIdx.x >> 6;
+  const int nch = (W + kQ - 1) / kQ, nseg = (H + SEG - 1) / SEG;
+  const int it = threadIdx.x;
+  const bool active = it < nch * nseg;
+  const int seg = it / nch, ch = it - seg * nch;
+  const int x0 = ch * kQ, y0 = seg * SEG, y1 = min(y0 + SEG, H);
+  const bool full = y0 + SEG <= H && x0 + kQ <= W;
+  const size_t plane = (size_t)H * W;
+  const size_t gplane = kUp ? (size_t)Ho * Wo : plane;
+  const float* g0 = gy + (size_t)map * B * gplane;
+  float v[SEG][kQ], acc[SEG][kQ];
+  if constexpr (!kInt) load_item<SEG>(x + (size_t)map * plane, H, W, x0, y0, active, v);
+  uint32_t rmask = 0;
+  if constexpr (kRelu) rmask = relu_mask<SEG>(v);
+#pragma unroll
+  for (int s = 0; s < SEG; ++s)
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) acc[s][q] = 0.f;
+  const LdsTable<float> tg{SG, pitch, W, H};
+  const int* adj = taps + (size_t)C * B * 16;
+  for (int b = 0; b < B; ++b) {
+    __syncthreads();
+    if constexpr (kUp) build_table_lds_up(g0 + b * gplane, SG, H, W, pitch, s, Ho, Wo);
+    else build_table_lds(g0 + b * plane, SG, H, W, pitch, 0.f, false);
+    const Taps<float> tp = load_taps(adj + (size_t)(c * B + b) * 16, W, H);
+    if constexpr (kInt) {  // integer corners: input gradient only
+      AccRows<SEG> em{acc};
+      if (active) {
+        if (full) box_walk_int<SEG, float, false, true>(tg, tp, H, W, x0, y0, y1, 0.f, em);
+        else box_walk_int<SEG, float, false, false>(tg, tp, H, W, x0, y0, y1, 0.f, em);
+      }
+      continue;
+    }
+    float E[4] = {0.f, 0.f, 0.f, 0.f};
+    if (active) {
+      if (full) adjoint_walk<SEG, true>(tg, tp, x0, y0, y1, v, acc, E);
+      else adjoint_walk<SEG, false>(tg, tp, x0, y0, y1, v, acc, E);
+    }
+    float g4[4] = {-E[1], E[0], -E[3], E[2]};   // dL/da, dL/db, dL/dc, dL/dd
+    store_wave_partial(g4, partials + (((size_t)n * nw + wave) * C * B + (size_t)c * B + b) * 4);
+  }
+  if (active && gx != nullptr) {
+    if constexpr (kRelu) store_item_relu_bf16<SEG>(static_cast<uint16_t*>(gx) + (size_t)map * plane, H, W, x0, y0, acc, rmask);
+    else store_item<SEG>(static_cast<float*>(gx) + (size_t)map * plane, H, W, x0, y0, acc);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Launchers
+// ---------------------------------------------------------------------------
+template <typename T, typename OutT, bool kOffset>
+static void fwd_lds_t(const void* x, const int* taps, void* y, int N, int C, int H, int W, int B, bool rounded,
+                      int stride, hipStream_t s) {
+  constexpr int SEG = 16;
+  const size_t shm = (size_t)(H + 1) * lds_pitch(W) * sizeof(T);
+  if (stride == 1) {
+    // bf16 output of 48-column maps, 4-byte aligned: items of 6 columns x 8
+    // rows (still 64 per box on 64-row maps), each row stored as 3 packed
+    // words
+    if constexpr (std::is_same<T, float>::value && std::is_same<OutT, uint16_t>::value) {
+      if (W == kPoseW && ((uintptr_t)y & 3) == 0) {  // the ABI also requires 16-byte aligned tensors
+        constexpr int kSeg6 = 8, kQ6 = 6;
+        const FwdGeom g6 = fwd_geom_items(N, C, B, ((W + kQ6 - 1) / kQ6) * n_segs(H, kSeg6));
+        with_flag(rounded, [&](auto ki) {
+          hipLaunchKernelGGL((k_box_fwd_lds<T, OutT, kSeg6, kOffset, decltype(ki)::value, kPoseW, kQ6, true>),
+                             dim3(N * C * g6.ngrp), dim3(g6.threads), shm, s, (const T*)x, taps, (OutT*)y, C, H, W,
+                             B, g6.bpg, g6.per_box_p);
+        });
+        return;
+      }
+    }
+    const FwdGeom g = fwd_geom(N, C, H, W, B, SEG);
+    with_flag(rounded, [&](auto ki) {
+      if (std::is_same<T, float>::value && W == kPoseW)
+        hipLaunchKernelGGL((k_box_fwd_lds<T, OutT, SEG, kOffset, decltype(ki)::value, kPoseW>), dim3(N * C * g.ngrp),
+                           dim3(g.threads), shm, s, (const T*)x, taps, (OutT*)y, C, H, W, B, g.bpg, g.per_box_p);
+      else
+        hipLaunchKernelGGL((k_box_fwd_lds<T, OutT, SEG, kOffset, decltype(ki)::value>), dim3(N * C * g.ngrp),
+                           dim3(g.threads), shm, s, (const T*)x, taps, (OutT*)y, C, H, W, B, g.bpg, g.per_box_p);
+    });
+    return;
+  }
+  const int Ho = (H + stride - 1) / stride, Wo = (W + stride - 1) / stride;
+  const FwdGeom g = fwd_geom_items(N, C, B, Wo * ((Ho + kSegS - 1) / kSegS));
+  with_flag(rounded, [&](auto ki) {
+    if (std::is_same<T, float>::value && W == kPoseW)
+      hipLaunchKernelGGL((k_box_fwd_lds_strided<T, OutT, kOffset, decltype(ki)::value, kPoseW>), dim3(N * C * g.ngrp),
+                         dim3(g.threads), shm, s, (const T*)x, taps, (OutT*)y, C, H, W, B, stride, Ho, Wo, g.bpg,
+                         g.per_box_p);
+    else
+      hipLaunchKernelGGL((k_box_fwd_lds_strided<T, OutT, kOffset, decltype(ki)::value>), dim3(N * C * g.ngrp),
+                         dim3(g.threads), shm, s, (const T*)x, taps, (OutT*)y, C, H, W, B, stride, Ho, Wo, g.bpg,
+                         g.per_box_p);
+  });
+}
+
+hipError_t launch_box_fwd_lds(const void* x, bool is_int, const int* taps, void* y, int out_kind, int N, int C,
+                              int H, int W, int B, bool offset, bool rounded, int stride, hipStream_t s) {
+  if (is_int) {
+    fwd_lds_t<int, int, false>(x, taps, y, N, C, H, W, B, rounded, stride, s);
+  } else if (out_kind == 2) {
+    if (offset) fwd_lds_t<float, uint16_t, true>(x, taps, y, N, C, H, W, B, rounded, stride, s);
+    else fwd_lds_t<float, uint16_t, false>(x, taps, y, N, C, H, W, B, rounded, stride, s);
+  } else {
+    if (offset) fwd_lds_t<float, float, true>(x, taps, y, N, C, H, W, B, rounded, stride, s);
+    else fwd_lds_t<float, float, false>(x, taps, y, N, C, H, W, B, rounded, stride, s);
+  }
+  return last_error();
+}
+
+template <int SEG, int kMaxT>
+static void bwd_lds_t(const float* x, const int* taps, const float* gy, void* gx, float* partials, int N, int C,
+                      int H, int W, int B, bool rounded, bool relu_bf16, int stride, hipStream_t s) {
+  const int items = n_chunks(W) * n_segs(H, SEG);
+  const int threads = ((items + 63) / 64) * 64;
+  const size_t shm = (size_t)(H + 1) * lds_pitch(W) * sizeof(float);
+  const int Ho = (H + stride - 1) / stride, Wo = (W + stride - 1) / stride;
+  auto go = [&](auto ki, auto ku, auto kr) {
+    if (SEG == 8 && W == kPoseW)
+      hipLaunchKernelGGL((k_box_bwd_lds<SEG, decltype(ki)::value, decltype(ku)::value, kMaxT, decltype(kr)::value, kPoseW>),
+                         dim3(N * C), dim3(threads), shm, s, x, taps, gy, gx, partials, C, H, W, B, stride, Ho, Wo);
+    else
+      hipLaunchKernelGGL((k_box_bwd_lds<SEG, decltype(ki)::value, decltype(ku)::value, kMaxT, decltype(kr)::value>),
+                         dim3(N * C), dim3(threads), shm, s, x, taps, gy, gx, partials, C, H, W, B, stride, Ho, Wo);
+  };
+  with_flag(stride > 1, [&](auto ku) {
+    if (rounded) go(std::true_type{}, ku, std::false_type{});
+    else with_flag(relu_bf16, [&](auto kr) { go(std::false_type{}, ku, kr); });
+  });
+}
+
+// Segment length of the LDS backward: 8 rows when the map's items fit one
+// 256-thread block, else 4 while they fit max_items threads; 0 = too many.
+// The 4-row walk fits 128 VGPRs, so its blocks may take up to 1024 threads
+// (maps up to 128x96 or 256x48): one block per CU, 16 waves.
+int box_bwd_lds_seg(int H, int W, int max_items) {
+  if (n_chunks(W) * n_segs(H, 8) <= 256) return 8;
+  if (n_chunks(W) * n_segs(H, 4) <= max_items) return 4;
+  return 0;
+}
+
+int box_bwd_lds_waves(int H, int W, int max_items) {
+  const int seg = box_bwd_lds_seg(H, W, max_items);
+  return seg == 0 ? 0 : (n_chunks(W) * n_segs(H, seg) + 63) / 64;
+}
+
+// A call whose maps give fewer than kBwdFillWaves waves with 8-row items
+// takes 4-row items instead (twice the waves, each with fewer registers):
+// 8 x 64 maps of 64x48 with 8 boxes, 51.5 -> 46.4 us; with 32 x 256 maps the
+// 8-row items stay faster (163 against 209 us).
+constexpr long kBwdFillWaves = 2048;  // 8 waves on each of 256 CUs
+int box_bwd_lds_seg_maps(int H, int W, long maps) {
+  const int seg = box_bwd_lds_seg(H, W, kBwdLdsItems);
+  if (seg == 8 && maps * ((n_chunks(W) * n_segs(H, 8) + 63) / 64) < kBwdFillWaves &&
+      n_chunks(W) * n_segs(H, 4) <= 256)
+    return 4;
+  return seg;
+}
+
+int box_bwd_lds_waves_maps(int H, int W, long maps) {
+  const int seg = box_bwd_lds_seg_maps(H, W, maps);
+  return seg == 0 ? 0 : (n_chunks(W) * n_segs(H, seg) + 63) / 64;
+}
+
+hipError_t launch_box_bwd_lds(const float* x, const int* taps, const float* gy, void* gx, float* partials, int N,
+                              int C, int H, int W, int B, bool rounded, bool relu_bf16, int stride, hipStream_t s) {
+  if (rounded && relu_bf16) return hipErrorInvalidValue;
+  const int seg = box_bwd_lds_seg_maps(H, W, (long)N * C);
+  if (seg == 8) bwd_lds_t<8, 256>(x, taps, gy, gx, partials, N, C, H, W, B, rounded, relu_bf16, stride, s);
+  else if (seg == 4 && n_chunks(W) * n_segs(H, 4) <= 256)
+    bwd_lds_t<4, 256>(x, taps, gy, gx, partials, N, C, H, W, B, rounded, relu_bf16, stride, s);
+  else if (seg == 4)
+    bwd_lds_t<4, kBwdLdsItems>(x, taps, gy, gx, partials, N, C, H, W, B, rounded, relu_bf16, stride, s);
+  else return hipErrorInvalidValue;
+  return last_error();
+}
+
+}  // namespace bc
