@@ -506,9 +506,11 @@ __device__ __forceinline__ void adjoint_walk(const Src& S, const Taps<float>& tp
 // off0 + s * W (elements; off0 = y0 * W + x0).
 // kNT: non-temporal stores (the HBM-table forwards with outputs larger than
 // the last-level cache, see kStreamOutBytes).  kPack (bf16 outputs, Q even,
-// every row offset and x0 even and the output 4-byte aligned): a whole row
-// of the item goes out as Q / 2 packed words in one store.
-template <typename OutT, typename T, bool kNT = false, int Q = kQ, bool kPack = false>
+// whole items): a row of the item goes out as Q / 2 packed words in one store,
+// 2: W and x0 even and the output 4-byte aligned, so each word is aligned; 1:
+// any W (the store is then 2-byte aligned, which global memory accesses may
+// be on this target).
+template <typename OutT, typename T, bool kNT = false, int Q = kQ, int kPack = 0>
 struct StoreRows {
   OutT* out;
   int W, x0, off0;
@@ -517,14 +519,16 @@ struct StoreRows {
     if constexpr (kPack && kFull) {
       static_assert(std::is_same<OutT, uint16_t>::value && std::is_same<T, float>::value && Q % 2 == 0 && !kNT,
                     "packed rows are bf16 pairs");
-      // one v_cvt_pk_bf16_f32 per pair (the rounding of convert_out); the
-      // row's word offset s * W / 2 folds into the store's immediate
+      // one v_cvt_pk_bf16_f32 per pair (the rounding of convert_out)
       typedef float f32x2 __attribute__((ext_vector_type(2)));
       typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-      uint32_t* w = reinterpret_cast<uint32_t*>(out + off0) + s * (W >> 1);
+      struct Words { uint32_t w[Q / 2]; } t;
 #pragma unroll
       for (int k = 0; k < Q / 2; ++k)
-        w[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){o[2 * k], o[2 * k + 1]}, bf16x2));
+        t.w[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){o[2 * k], o[2 * k + 1]}, bf16x2));
+      OutT* row = out + (unsigned)(off0 + s * W);
+      if constexpr (kPack == 2) row = static_cast<OutT*>(__builtin_assume_aligned(row, 4));
+      __builtin_memcpy(row, &t, sizeof(t));
       return;
     }
     OutT* row = out + (unsigned)(off0 + s * W);
@@ -555,6 +559,27 @@ __device__ __forceinline__ void load_item(const float* __restrict__ xs, int H, i
     }
 }
 
+// The same of an item that lies whole inside the map.
+template <int SEG>
+__device__ __forceinline__ void load_item_full(const float* __restrict__ xs, int W, int x0, int y0,
+                                               float (&v)[SEG][kQ]) {
+  const float* p = xs + (unsigned)(y0 * W + x0);
+#pragma unroll
+  for (int s = 0; s < SEG; ++s)
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) v[s][q] = p[(unsigned)(s * W) + q];
+}
+
+// Zeroes the values of an item's first `cols` columns and `rows` rows (those
+// that belong to its neighbours).
+template <int SEG>
+__device__ __forceinline__ void keep_own(float (&v)[SEG][kQ], int cols, int rows) {
+#pragma unroll
+  for (int s = 0; s < SEG; ++s)
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) v[s][q] = (q >= cols && s >= rows) ? v[s][q] : 0.f;
+}
+
 // The item's origin passes through an opaque copy (an empty asm with the
 // coordinates as operands): the stores then recompute their row addresses
 // instead of the compiler holding load_item's 64-bit row offsets live across
@@ -562,17 +587,18 @@ __device__ __forceinline__ void load_item(const float* __restrict__ xs, int H, i
 // them at four waves per SIMD).
 __device__ __forceinline__ void opaque_origin(int& x0, int& y0) { asm volatile("" : "+v"(x0), "+v"(y0)); }
 
-template <int SEG>
+// kFull: the item lies whole inside the map.
+template <int SEG, bool kFull = false>
 __device__ __forceinline__ void store_item(float* __restrict__ out, int H, int W, int x0, int y0,
                                            const float (&acc)[SEG][kQ]) {
   opaque_origin(x0, y0);
 #pragma unroll
   for (int s = 0; s < SEG; ++s) {
     const int yy = y0 + s;
-    if (yy < H) {
+    if (kFull || yy < H) {
 #pragma unroll
       for (int q = 0; q < kQ; ++q)
-        if (x0 + q < W) out[(size_t)yy * W + x0 + q] = acc[s][q];
+        if (kFull || x0 + q < W) out[(size_t)yy * W + x0 + q] = acc[s][q];
     }
   }
 }
@@ -590,6 +616,7 @@ __device__ __forceinline__ uint32_t relu_mask(const float (&v)[SEG][kQ]) {
   for (int s = 0; s < SEG; ++s)
 #pragma unroll
     for (int q = 0; q < kQ; ++q) m |= (v[s][q] > 0.f ? 1u : 0u) << (s * kQ + q);
+  asm volatile("" : "+v"(m));  // else the compiler tests the values again at the end, and keeps them live
   return m;
 }
 
@@ -603,17 +630,17 @@ __device__ __forceinline__ uint16_t bf16_rne_bits(float f) {
   return (uint16_t)((b + 0x7fffu + ((b >> 16) & 1u)) >> 16);
 }
 
-template <int SEG>
+template <int SEG, bool kFull = false>
 __device__ __forceinline__ void store_item_relu_bf16(uint16_t* __restrict__ out, int H, int W, int x0, int y0,
                                                      const float (&acc)[SEG][kQ], uint32_t mask) {
   opaque_origin(x0, y0);
 #pragma unroll
   for (int s = 0; s < SEG; ++s) {
     const int yy = y0 + s;
-    if (yy < H) {
+    if (kFull || yy < H) {
 #pragma unroll
       for (int q = 0; q < kQ; ++q)
-        if (x0 + q < W)
+        if (kFull || x0 + q < W)
           out[(size_t)yy * W + x0 + q] = bf16_rne_bits(((mask >> (s * kQ + q)) & 1u) ? acc[s][q] : 0.f);
     }
   }
@@ -688,10 +715,6 @@ inline FwdGeom fwd_geom(int N, int C, int H, int W, int B, int seg) {
   return fwd_geom_items(N, C, B, n_chunks(W) * n_segs(H, seg));
 }
 
-// The pose network's maps are 48 columns wide (a 192-pixel-wide input at
-// stride 4): the LDS forward and backward take instances with that width
-// compiled in.
-constexpr int kPoseW = 48;
 
 // The HBM-table forwards re-read their tables through the caches; an output
 // larger than the last-level cache (256 MiB) cannot stay there for the next

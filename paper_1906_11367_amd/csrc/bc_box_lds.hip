@@ -4,12 +4,33 @@
 
 namespace bc {
 
+// Items of a map: Q columns x SEG rows each, chunks fastest.  The last chunk
+// and the last segment are moved back to end at the map's edge, so that every
+// item is whole: its walk has no guards, and a wave never runs a guarded walk
+// beside an unguarded one (with 64 columns in 3-column chunks every wave held
+// a one-column chunk and ran both).  The overlapped outputs are computed twice,
+// by the same operations on the same table entries, and stored with the same
+// bits.  Maps smaller than one item (W < Q or H < SEG) take the guarded
+// instances (kTail).
+template <int SEG, int Q>
+struct ItemPos {
+  int xo, yo;  // first column and row that are the item's own
+  int x0, y0;  // first column and row it covers
+  __device__ __forceinline__ ItemPos(int it, int nch, int H, int W, bool tail) {
+    const int seg = it / nch, ch = it - seg * nch;
+    xo = ch * Q;
+    yo = seg * SEG;
+    x0 = tail ? xo : min(xo, W - Q);
+    y0 = tail ? yo : min(yo, H - SEG);
+  }
+};
+
 // Forward on a map's table in LDS, for the boxes b0 .. b0+nb-1 of channel c.
-// Items of one box are (row segment, 3-column chunk), chunk fastest so that
+// Items of one box are (row segment, column chunk), chunk fastest so that
 // adjacent lanes write adjacent columns; each box's items are padded to a
 // multiple of 64 (per_box_p) so that a wave works on one box and reads its
 // taps through scalar loads.
-template <typename T, typename OutT, int SEG, bool kOffset, bool kInt, int Q = kQ, bool kPack = false>
+template <typename T, typename OutT, int SEG, bool kOffset, bool kInt, int Q, int kPack, bool kTail>
 __device__ __forceinline__ void fwd_boxes(const LdsTable<T>& tab, const int* __restrict__ taps,
                                           OutT* __restrict__ y, int map, int c, int b0, int nb, int H, int W,
                                           int B, int per_box_p, float mu) {
@@ -18,30 +39,27 @@ __device__ __forceinline__ void fwd_boxes(const LdsTable<T>& tab, const int* __r
     const int bl = __builtin_amdgcn_readfirstlane(it / per_box_p);
     const int r = it - bl * per_box_p;
     if (r >= per_box) continue;
-    const int seg = r / nch, ch = r - seg * nch;
+    const ItemPos<SEG, Q> ip(r, nch, H, W, kTail);
     const int b = b0 + bl;
     const Taps<T> tp = typed_taps<T>(load_taps(taps + (size_t)(c * B + b) * 16, W, H));
     OutT* out = y + ((size_t)map * B + b) * H * W;
-    const int x0 = ch * Q, y0 = seg * SEG, y1 = min(y0 + SEG, H);
-    StoreRows<OutT, T, false, Q, kPack> em{out, W, x0, y0 * W + x0};
-    if (y0 + SEG <= H && x0 + Q <= W) walk_fwd<SEG, T, kOffset, true, kInt, Q>(tab, tp, H, W, x0, y0, y1, mu, em);
-    else walk_fwd<SEG, T, kOffset, false, kInt, Q>(tab, tp, H, W, x0, y0, y1, mu, em);
+    StoreRows<OutT, T, false, Q, kPack> em{out, W, ip.x0, ip.y0 * W + ip.x0};
+    walk_fwd<SEG, T, kOffset, !kTail, kInt, Q>(tab, tp, H, W, ip.x0, ip.y0, min(ip.y0 + SEG, H), mu, em);
   }
 }
 
 // Forward, table in LDS: one block per (map, group of bpg boxes).  The block
 // builds the map's table once and evaluates every box of its group.
-// kW > 0: the map width compiled in (W is then ignored), as in the LDS
-// backward.  Q: columns per item; kPack: packed bf16 row stores (StoreRows).
-template <typename T, typename OutT, int SEG, bool kOffset, bool kInt, int kW = 0, int Q = kQ, bool kPack = false>
+// kPitch > 0: the table's row pitch compiled in (as in the LDS backward).  Q:
+// columns per item; kPack: how rows are stored (StoreRows).
+template <typename T, typename OutT, int SEG, bool kOffset, bool kInt, int kPitch, int Q, int kPack, bool kTail>
 __global__ __launch_bounds__(256) void k_box_fwd_lds(const T* __restrict__ x, const int* __restrict__ taps,
-                                                     OutT* __restrict__ y, int C, int H, int W_arg, int B, int bpg,
+                                                     OutT* __restrict__ y, int C, int H, int W, int B, int bpg,
                                                      int per_box_p) {
-  const int W = kW > 0 ? kW : W_arg;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T* S = reinterpret_cast<T*>(smem_raw);
   __shared__ float red[16];
-  const int pitch = lds_pitch_dev(W);
+  const int pitch = kPitch > 0 ? kPitch : lds_pitch_dev(W);
   const int ngrp = (B + bpg - 1) / bpg;
   const int map = blockIdx.x / ngrp, grp = blockIdx.x - map * ngrp;
   const T* src = x + (size_t)map * H * W;
@@ -49,8 +67,8 @@ __global__ __launch_bounds__(256) void k_box_fwd_lds(const T* __restrict__ x, co
   if (kOffset) mu = block_mean(reinterpret_cast<const float*>(src), H * W, red);
   build_table_lds<T, true>(src, S, H, W, pitch, mu, kOffset);
   const int b0 = grp * bpg;
-  fwd_boxes<T, OutT, SEG, kOffset, kInt, Q, kPack>(LdsTable<T>{S, pitch, W, H}, taps, y, map, map % C, b0,
-                                                   min(bpg, B - b0), H, W, B, per_box_p, mu);
+  fwd_boxes<T, OutT, SEG, kOffset, kInt, Q, kPack, kTail>(LdsTable<T>{S, pitch, W, H}, taps, y, map, map % C, b0,
+                                                          min(bpg, B - b0), H, W, B, per_box_p, mu);
 }
 
 // Strided forward (stride s > 1) on a map's table in LDS, boxes b0 .. b0+nb-1
@@ -75,15 +93,14 @@ __device__ __forceinline__ void fwd_boxes_strided(const LdsTable<T>& tab, const 
   }
 }
 
-template <typename T, typename OutT, bool kOffset, bool kInt, int kW = 0>
+template <typename T, typename OutT, bool kOffset, bool kInt, int kPitch>
 __global__ __launch_bounds__(256) void k_box_fwd_lds_strided(const T* __restrict__ x, const int* __restrict__ taps,
-                                                             OutT* __restrict__ y, int C, int H, int W_arg, int B, int s,
+                                                             OutT* __restrict__ y, int C, int H, int W, int B, int s,
                                                              int Ho, int Wo, int bpg, int per_box_p) {
-  const int W = kW > 0 ? kW : W_arg;  // kW > 0: the map width compiled in
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T* S = reinterpret_cast<T*>(smem_raw);
   __shared__ float red[16];
-  const int pitch = lds_pitch_dev(W);
+  const int pitch = kPitch > 0 ? kPitch : lds_pitch_dev(W);
   const int ngrp = (B + bpg - 1) / bpg;
   const int map = blockIdx.x / ngrp, grp = blockIdx.x - map * ngrp;
   const T* src = x + (size_t)map * H * W;
@@ -109,34 +126,39 @@ __global__ __launch_bounds__(256) void k_box_fwd_lds_strided(const T* __restrict
 // 8-row items fit without spilling once the final stores recompute their
 // addresses (below); pose-layer backward 172.5 -> 151.5 us, results
 // bit-identical.  The 4-row items take 92.
-// kW > 0: the map width as a compile-time constant (W is then ignored), so
-// the table pitch is one too and every row offset of the scans, the walk and
-// the item loads and stores is an immediate of its LDS or global access
-// instead of a per-element address add; the results are the same bits.
-template <int SEG, bool kInt, bool kUp, int kMaxT, bool kRelu, int kW = 0>
+// kPitch > 0: the table's row pitch as a compile-time constant, so that every
+// row offset of the scans and the walk is an immediate of its LDS access
+// instead of a per-element address add.
+// Items end at the map's edges (ItemPos): every lane runs the one unguarded
+// walk.  Values an item shares with its neighbour enter the edge sums as 0
+// there, so each is counted once; its input gradient is written twice with the
+// same bits.
+// kTail: maps smaller than an item, every row and column guarded.
+template <int SEG, bool kInt, bool kUp, int kMaxT, bool kRelu, int kPitch, bool kTail>
 __global__ __launch_bounds__(kMaxT) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_box_bwd_lds(
     const float* __restrict__ x, const int* __restrict__ taps, const float* __restrict__ gy, void* __restrict__ gx,
-    float* __restrict__ partials, int C, int H, int W_arg, int B, int s, int Ho, int Wo) {
+    float* __restrict__ partials, int C, int H, int W, int B, int s, int Ho, int Wo) {
   static_assert(!(kInt && kRelu), "the ReLU mask needs x");
-  const int W = kW > 0 ? kW : W_arg;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int pitch = lds_pitch_dev(W);
+  const int pitch = kPitch > 0 ? kPitch : lds_pitch_dev(W);
   float* SG = reinterpret_cast<float*>(smem_raw);
   const int map = blockIdx.x, n = map / C, c = map - n * C;
   const int nw = blockDim.x >> 6, wave = threadIdx.x >> 6;
   const int nch = (W + kQ - 1) / kQ, nseg = (H + SEG - 1) / SEG;
-  const int it = threadIdx.x;
-  const bool active = it < nch * nseg;
-  const int seg = it / nch, ch = it - seg * nch;
-  const int x0 = ch * kQ, y0 = seg * SEG, y1 = min(y0 + SEG, H);
-  const bool full = y0 + SEG <= H && x0 + kQ <= W;
+  const bool active = (int)threadIdx.x < nch * nseg;
+  const ItemPos<SEG, kQ> ip(active || kTail ? threadIdx.x : 0, nch, H, W, kTail);
+  const int x0 = ip.x0, y0 = ip.y0, y1 = min(y0 + SEG, H);
   const size_t plane = (size_t)H * W;
   const size_t gplane = kUp ? (size_t)Ho * Wo : plane;
   const float* g0 = gy + (size_t)map * B * gplane;
   float v[SEG][kQ], acc[SEG][kQ];
-  if constexpr (!kInt) load_item<SEG>(x + (size_t)map * plane, H, W, x0, y0, active, v);
   uint32_t rmask = 0;
-  if constexpr (kRelu) rmask = relu_mask<SEG>(v);
+  if constexpr (!kInt) {
+    if constexpr (kTail) load_item<SEG>(x + (size_t)map * plane, H, W, x0, y0, active, v);
+    else load_item_full<SEG>(x + (size_t)map * plane, W, x0, y0, v);
+    if constexpr (kRelu) rmask = relu_mask<SEG>(v);
+    if constexpr (!kTail) keep_own<SEG>(v, ip.xo - x0, ip.yo - y0);
+  }
 #pragma unroll
   for (int s = 0; s < SEG; ++s)
 #pragma unroll
@@ -150,72 +172,109 @@ __global__ __launch_bounds__(kMaxT) __attribute__((amdgpu_waves_per_eu(4, 8))) v
     const Taps<float> tp = load_taps(adj + (size_t)(c * B + b) * 16, W, H);
     if constexpr (kInt) {  // integer corners: input gradient only
       AccRows<SEG> em{acc};
-      if (active) {
-        if (full) box_walk_int<SEG, float, false, true>(tg, tp, H, W, x0, y0, y1, 0.f, em);
-        else box_walk_int<SEG, float, false, false>(tg, tp, H, W, x0, y0, y1, 0.f, em);
-      }
+      if (active) box_walk_int<SEG, float, false, !kTail>(tg, tp, H, W, x0, y0, y1, 0.f, em);
       continue;
     }
     float E[4] = {0.f, 0.f, 0.f, 0.f};
-    if (active) {
-      if (full) adjoint_walk<SEG, true>(tg, tp, x0, y0, y1, v, acc, E);
-      else adjoint_walk<SEG, false>(tg, tp, x0, y0, y1, v, acc, E);
-    }
+    if (active) adjoint_walk<SEG, !kTail>(tg, tp, x0, y0, y1, v, acc, E);
     float g4[4] = {-E[1], E[0], -E[3], E[2]};   // dL/da, dL/db, dL/dc, dL/dd
     store_wave_partial(g4, partials + (((size_t)n * nw + wave) * C * B + (size_t)c * B + b) * 4);
   }
   if (active && gx != nullptr) {
-    if constexpr (kRelu) store_item_relu_bf16<SEG>(static_cast<uint16_t*>(gx) + (size_t)map * plane, H, W, x0, y0, acc, rmask);
-    else store_item<SEG>(static_cast<float*>(gx) + (size_t)map * plane, H, W, x0, y0, acc);
+    if constexpr (kRelu) store_item_relu_bf16<SEG, !kTail>(static_cast<uint16_t*>(gx) + (size_t)map * plane, H, W, x0, y0, acc, rmask);
+    else store_item<SEG, !kTail>(static_cast<float*>(gx) + (size_t)map * plane, H, W, x0, y0, acc);
   }
 }
 
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
+// f(std::integral_constant<int, pitch>) for a compiled pitch (0: run-time pitch).
+template <typename F>
+static void with_pitch(int pitch, F&& f) {
+  switch (pitch) {
+    case 55: f(std::integral_constant<int, 55>{}); return;
+    case 71: f(std::integral_constant<int, 71>{}); return;
+    case 103: f(std::integral_constant<int, 103>{}); return;
+    default: f(std::integral_constant<int, 0>{});
+  }
+}
+
+// Rows per item of the forward: a box's items fill whole waves, and each item
+// reads one row more than it writes (and its start costs about two rows), so
+// the segment length with the least waves x (rows + 3) is taken; 8 rows on
+// 64x48 maps (64 items, one wave), 13 on 64x64 (55 items; 8 rows would need
+// 88 items in two waves).
+static int fwd_seg(int H, int nch) {
+  int best = 8;
+  long cost = 0;
+  for (int seg : {8, 10, 13}) {
+    if (H < seg) continue;
+    const long c = (long)((nch * n_segs(H, seg) + 63) / 64) * (seg + 3);
+    if (cost == 0 || c < cost) { cost = c; best = seg; }
+  }
+  return best;
+}
+
 template <typename T, typename OutT, bool kOffset>
 static void fwd_lds_t(const void* x, const int* taps, void* y, int N, int C, int H, int W, int B, bool rounded,
                       int stride, hipStream_t s) {
-  constexpr int SEG = 16;
-  const size_t shm = (size_t)(H + 1) * lds_pitch(W) * sizeof(T);
+  const int pc = kOffset || std::is_same<T, int>::value ? 0 : lds_pitch_class(H, W);
+  const size_t shm = (size_t)(H + 1) * (pc ? pc : lds_pitch(W)) * sizeof(T);
   if (stride == 1) {
-    // bf16 output of 48-column maps, 4-byte aligned: items of 6 columns x 8
-    // rows (still 64 per box on 64-row maps), each row stored as 3 packed
-    // words
-    if constexpr (std::is_same<T, float>::value && std::is_same<OutT, uint16_t>::value) {
-      if (W == kPoseW && ((uintptr_t)y & 3) == 0) {  // the ABI also requires 16-byte aligned tensors
-        constexpr int kSeg6 = 8, kQ6 = 6;
-        const FwdGeom g6 = fwd_geom_items(N, C, B, ((W + kQ6 - 1) / kQ6) * n_segs(H, kSeg6));
-        with_flag(rounded, [&](auto ki) {
-          hipLaunchKernelGGL((k_box_fwd_lds<T, OutT, kSeg6, kOffset, decltype(ki)::value, kPoseW, kQ6, true>),
-                             dim3(N * C * g6.ngrp), dim3(g6.threads), shm, s, (const T*)x, taps, (OutT*)y, C, H, W,
-                             B, g6.bpg, g6.per_box_p);
-        });
-        return;
-      }
+    constexpr int Q = 6;
+    if (W < Q || H < 8) {  // smaller than one item
+      constexpr int SEG = 16;
+      const FwdGeom g = fwd_geom(N, C, H, W, B, SEG);
+      const size_t shm0 = (size_t)(H + 1) * lds_pitch(W) * sizeof(T);
+      with_flag(rounded, [&](auto ki) {
+        hipLaunchKernelGGL((k_box_fwd_lds<T, OutT, SEG, kOffset, decltype(ki)::value, 0, kQ, 0, true>),
+                           dim3(N * C * g.ngrp), dim3(g.threads), shm0, s, (const T*)x, taps, (OutT*)y, C, H, W, B,
+                           g.bpg, g.per_box_p);
+      });
+      return;
     }
-    const FwdGeom g = fwd_geom(N, C, H, W, B, SEG);
+    const int nch = (W + Q - 1) / Q, seg = pc ? fwd_seg(H, nch) : 8;
+    const FwdGeom g = fwd_geom_items(N, C, B, nch * n_segs(H, seg));
+    auto go = [&](auto ki, auto kseg, auto kp, auto kpack) {
+      hipLaunchKernelGGL((k_box_fwd_lds<T, OutT, decltype(kseg)::value, kOffset, decltype(ki)::value,
+                                        decltype(kp)::value, Q, decltype(kpack)::value, false>),
+                         dim3(N * C * g.ngrp), dim3(g.threads), shm, s, (const T*)x, taps, (OutT*)y, C, H, W, B, g.bpg,
+                         g.per_box_p);
+    };
     with_flag(rounded, [&](auto ki) {
-      if (std::is_same<T, float>::value && W == kPoseW)
-        hipLaunchKernelGGL((k_box_fwd_lds<T, OutT, SEG, kOffset, decltype(ki)::value, kPoseW>), dim3(N * C * g.ngrp),
-                           dim3(g.threads), shm, s, (const T*)x, taps, (OutT*)y, C, H, W, B, g.bpg, g.per_box_p);
-      else
-        hipLaunchKernelGGL((k_box_fwd_lds<T, OutT, SEG, kOffset, decltype(ki)::value>), dim3(N * C * g.ngrp),
-                           dim3(g.threads), shm, s, (const T*)x, taps, (OutT*)y, C, H, W, B, g.bpg, g.per_box_p);
+      auto packed = [&](auto kseg, auto kp) {
+        // bf16 rows of an even width go out as aligned packed words
+        if constexpr (std::is_same<OutT, uint16_t>::value) {
+          if ((W & 1) == 0) go(ki, kseg, kp, std::integral_constant<int, 2>{});
+          else go(ki, kseg, kp, std::integral_constant<int, 1>{});
+        } else {
+          go(ki, kseg, kp, std::integral_constant<int, 0>{});
+        }
+      };
+      if constexpr (kOffset || std::is_same<T, int>::value) {
+        packed(std::integral_constant<int, 8>{}, std::integral_constant<int, 0>{});
+      } else {
+        with_pitch(pc, [&](auto kp) {
+          if constexpr (decltype(kp)::value == 0) packed(std::integral_constant<int, 8>{}, kp);
+          else if (seg == 13) packed(std::integral_constant<int, 13>{}, kp);
+          else if (seg == 10) packed(std::integral_constant<int, 10>{}, kp);
+          else packed(std::integral_constant<int, 8>{}, kp);
+        });
+      }
     });
     return;
   }
   const int Ho = (H + stride - 1) / stride, Wo = (W + stride - 1) / stride;
   const FwdGeom g = fwd_geom_items(N, C, B, Wo * ((Ho + kSegS - 1) / kSegS));
   with_flag(rounded, [&](auto ki) {
-    if (std::is_same<T, float>::value && W == kPoseW)
-      hipLaunchKernelGGL((k_box_fwd_lds_strided<T, OutT, kOffset, decltype(ki)::value, kPoseW>), dim3(N * C * g.ngrp),
-                         dim3(g.threads), shm, s, (const T*)x, taps, (OutT*)y, C, H, W, B, stride, Ho, Wo, g.bpg,
-                         g.per_box_p);
-    else
-      hipLaunchKernelGGL((k_box_fwd_lds_strided<T, OutT, kOffset, decltype(ki)::value>), dim3(N * C * g.ngrp),
-                         dim3(g.threads), shm, s, (const T*)x, taps, (OutT*)y, C, H, W, B, stride, Ho, Wo, g.bpg,
-                         g.per_box_p);
+    auto go = [&](auto kp) {
+      hipLaunchKernelGGL((k_box_fwd_lds_strided<T, OutT, kOffset, decltype(ki)::value, decltype(kp)::value>),
+                         dim3(N * C * g.ngrp), dim3(g.threads), shm, s, (const T*)x, taps, (OutT*)y, C, H, W, B, stride,
+                         Ho, Wo, g.bpg, g.per_box_p);
+    };
+    if constexpr (kOffset || std::is_same<T, int>::value) go(std::integral_constant<int, 0>{});
+    else with_pitch(pc, go);
   });
 }
 
@@ -238,15 +297,23 @@ static void bwd_lds_t(const float* x, const int* taps, const float* gy, void* gx
                       int H, int W, int B, bool rounded, bool relu_bf16, int stride, hipStream_t s) {
   const int items = n_chunks(W) * n_segs(H, SEG);
   const int threads = ((items + 63) / 64) * 64;
-  const size_t shm = (size_t)(H + 1) * lds_pitch(W) * sizeof(float);
   const int Ho = (H + stride - 1) / stride, Wo = (W + stride - 1) / stride;
+  const bool tail = W < kQ || H < SEG;
+  const int pc = tail ? 0 : lds_pitch_class(H, W);
+  const size_t shm = (size_t)(H + 1) * (pc ? pc : lds_pitch(W)) * sizeof(float);
   auto go = [&](auto ki, auto ku, auto kr) {
-    if (SEG == 8 && W == kPoseW)
-      hipLaunchKernelGGL((k_box_bwd_lds<SEG, decltype(ki)::value, decltype(ku)::value, kMaxT, decltype(kr)::value, kPoseW>),
+    auto launch = [&](auto kp, auto kt) {
+      hipLaunchKernelGGL((k_box_bwd_lds<SEG, decltype(ki)::value, decltype(ku)::value, kMaxT, decltype(kr)::value,
+                                        decltype(kp)::value, decltype(kt)::value>),
                          dim3(N * C), dim3(threads), shm, s, x, taps, gy, gx, partials, C, H, W, B, stride, Ho, Wo);
-    else
-      hipLaunchKernelGGL((k_box_bwd_lds<SEG, decltype(ki)::value, decltype(ku)::value, kMaxT, decltype(kr)::value>),
-                         dim3(N * C), dim3(threads), shm, s, x, taps, gy, gx, partials, C, H, W, B, stride, Ho, Wo);
+    };
+    if (tail) launch(std::integral_constant<int, 0>{}, std::true_type{});
+    else with_pitch(pc, [&](auto kp) {
+      // more than 256 items of 4 rows: maps wider than the two narrow classes
+      if constexpr (kMaxT > 256 && (decltype(kp)::value == 55 || decltype(kp)::value == 71))
+        launch(std::integral_constant<int, 0>{}, std::false_type{});
+      else launch(kp, std::false_type{});
+    });
   };
   with_flag(stride > 1, [&](auto ku) {
     if (rounded) go(std::true_type{}, ku, std::false_type{});

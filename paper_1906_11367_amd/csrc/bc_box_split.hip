@@ -506,6 +506,11 @@ hipError_t launch_box_prep_corners_adj(const float* boxes, const float* piece_w,
   return last_error();
 }
 
+// The pose network's maps are 48 columns wide (a 192-pixel-wide input at
+// stride 4): the LDS forward and backward take instances with that width
+// compiled in.
+constexpr int kPoseW = 48;
+
 template <int SEG, int NXC, int NYC, int kMaxT>
 static void bwd_split_t(const float* x, const int* rec, const float* gy, float* gx, float* partials, int N, int C,
                         int H, int W, int B, hipStream_t s) {

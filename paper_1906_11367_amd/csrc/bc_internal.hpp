@@ -12,6 +12,16 @@ namespace bc {
 // different rows of one column hit distinct banks.
 inline int lds_pitch(int W) { return (W + 7) | 1; }
 
+// Row pitches compiled into the LDS kernels (0: none applies): the smallest of
+// three, for maps up to 48, 64 and 96 wide, whose rows then have constant
+// offsets; narrower maps waste the difference, so the table must still leave
+// room for four blocks per CU (40 KiB), which all maps up to 96x96 do.
+constexpr size_t kLdsClassBytes = 40 * 1024;
+inline int lds_pitch_class(int H, int W) {
+  const int p = W <= 48 ? 55 : W <= 64 ? 71 : W <= 96 ? 103 : 0;
+  return (size_t)(H + 1) * p * 4 <= kLdsClassBytes ? p : 0;
+}
+
 // Items of the sliding-window walk: kQ-column chunks x seg-row segments.
 inline int n_chunks(int W) { return (W + 2) / 3; }
 inline int n_segs(int H, int seg) { return (H + seg - 1) / seg; }
