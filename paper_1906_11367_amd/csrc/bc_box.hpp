@@ -91,6 +91,37 @@ __device__ __forceinline__ void table_row_pass(T* S, int H, int W, int pitch) {
   }
 }
 
+// The row pass of a HalfRowTable: column sums of the W columns at every other
+// entry, each prefix written to its two entries of the W_up = 2 W or 2 W - 1.
+template <typename T>
+__device__ __forceinline__ void table_row_pass_up2(T* S, int H, int W, int W_up, int pitch) {
+  constexpr int kScan = 8;
+  T* R = S + kPad;
+  for (int u = threadIdx.x + 1; u <= H; u += blockDim.x) {
+    T* row = R + u * pitch + 1;
+    T run = (T)0;
+    int v = 0;
+    for (; v + kScan <= W; v += kScan) {
+      T r[kScan];
+#pragma unroll
+      for (int k = 0; k < kScan; ++k) r[k] = row[2 * (v + k)];
+#pragma unroll
+      for (int k = 0; k < kScan; ++k) {
+        run += r[k];
+        row[2 * (v + k)] = run;
+        row[2 * (v + k) + 1] = run;  // past the last column: padding, the same total
+      }
+    }
+    for (; v < W; ++v) {
+      run += row[2 * v];
+      row[2 * v] = run;
+      row[2 * v + 1] = run;
+    }
+#pragma unroll
+    for (int k = 0; k < kPad; ++k) row[W_up + k] = run;
+  }
+}
+
 // Column pass (lanes own columns) and row pass of a padded LDS table whose
 // interior holds the map, each reading kScan elements ahead before it writes.
 template <typename T>
@@ -182,17 +213,142 @@ __device__ void build_table_lds(const T* __restrict__ src, T* S, int H, int W, i
     }
   } else {
     const int di = nt / W, dj = nt - di * W;
-    int i = tid / W, j = tid - i * W;
-    for (int k = tid; k < n; k += nt) {
-      const T v = __builtin_nontemporal_load(src + k);
-      R[(i + 1) * pitch + j + 1] = sub ? (T)((float)v - mu) : v;
-      i += di;
-      j += dj;
-      if (j >= W) { j -= W; ++i; }
+    int j = tid % W;
+    int o = (tid / W + 1) * pitch + j + 1;
+    const int step = di * pitch + dj, wrap = pitch - W;
+    constexpr int kBatch1 = kSkip ? 8 : 4;
+    for (int base = 0; base < n; base += nt * kBatch1) {
+      T q[kBatch1];
+#pragma unroll
+      for (int b = 0; b < kBatch1; ++b)
+        if (!kSkip || base + b * nt < n) q[b] = __builtin_nontemporal_load(src + min(base + b * nt + tid, n - 1));
+#pragma unroll
+      for (int b = 0; b < kBatch1; ++b) {
+        if (kSkip && base + b * nt >= n) break;
+        if (tid < n - base - b * nt) R[o] = sub ? (T)((float)q[b] - mu) : q[b];
+        o += step;
+        j += dj;
+        if (j >= W) { j -= W; o += wrap; }
+      }
     }
   }
   __syncthreads();
   table_scans(S, H, W, pitch);
+}
+
+// The same table with its column sums formed in registers, for maps up to 64 *
+// CPL wide: lane l owns columns l (and l + 64), wave w the RPW rows from w *
+// RPW on, so a map row is one coalesced load per wave with a wave-uniform row
+// offset, all RPW of them in flight.  Each lane sums down its rows, the waves
+// exchange their column totals through LDS (part), and each column sum is
+// written once, where staging the map and summing it in place takes four LDS
+// accesses and a pass that leaves most of the block waiting.  The row pass
+// (table_row_pass) stays one row per lane: scanning across lanes instead needs
+// no LDS but six moves per row, and these kernels wait on their vector
+// arithmetic first (box backward, 64x48 maps: 143 us staged, 146 scanned
+// across lanes, 126 this way; 64x64: 128 and 98).  Row 0 and the left padding
+// stay zero (table_zero_edges, once per block).
+template <typename T, int RPW, int CPL>
+struct BandTable {
+  T r[RPW][CPL];
+
+  // rows [row0, row0 + RPW) of the map; rows past it repeat the last one and
+  // are not written; lanes past the map read 0 (the descriptor's range check)
+  __device__ __forceinline__ void load(const T* src, int H, int W, int row0) {
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(src), (short)0, H * W * 4, 0x00020000);
+    const int lane = threadIdx.x & 63;
+    unsigned vo[CPL];
+#pragma unroll
+    for (int k = 0; k < CPL; ++k) vo[k] = lane + 64 * k < W ? 4u * (lane + 64 * k) : 0x40000000u;
+#pragma unroll
+    for (int i = 0; i < RPW; ++i)
+#pragma unroll
+      for (int k = 0; k < CPL; ++k)
+        r[i][k] = __builtin_bit_cast(
+            T, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)vo[k], min(row0 + i, H - 1) * W * 4, 2));
+  }
+
+  // column sums within the band (of the map minus mu with `sub`); the totals
+  // go to part[wave]
+  __device__ __forceinline__ void sum_rows(T* part, int wave, bool sub, float mu) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int k = 0; k < CPL; ++k) {
+      if (sub) {
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) r[i][k] = (T)((float)r[i][k] - mu);
+      }
+#pragma unroll
+      for (int i = 1; i < RPW; ++i) r[i][k] += r[i - 1][k];
+      part[(wave * CPL + k) * 64 + lane] = r[RPW - 1][k];
+    }
+  }
+
+  // after a barrier: adds the bands above (and carry, the strips above, which
+  // then takes this strip's total) and writes the column sums, kStep entries
+  // apart
+  template <int kStep = 1>
+  __device__ __forceinline__ void finish(const T* part, int nw, int wave, T (&carry)[CPL], T* S, int H, int W,
+                                         int pitch, int row0) {
+    const int lane = threadIdx.x & 63;
+    const int rows = min(RPW, H - row0);
+#pragma unroll
+    for (int k = 0; k < CPL; ++k) {
+      T above = carry[k], total = carry[k];
+      for (int h = 0; h < nw; ++h) {
+        const T t = part[(h * CPL + k) * 64 + lane];
+        if (h < wave) above += t;
+        total += t;
+      }
+      carry[k] = total;
+#pragma unroll
+      for (int i = 0; i < RPW; ++i) r[i][k] += above;
+    }
+    T* row = S + kPad + 1 + lane * kStep + (row0 + 1) * pitch;
+#pragma unroll
+    for (int k = 0; k < CPL; ++k) {
+      if (lane + 64 * k < W) {
+        if (rows == RPW) {
+#pragma unroll
+          for (int i = 0; i < RPW; ++i) row[i * pitch + 64 * k * kStep] = r[i][k];
+        } else {
+#pragma unroll
+          for (int i = 0; i < RPW; ++i)
+            if (i < rows) row[i * pitch + 64 * k * kStep] = r[i][k];
+        }
+      }
+    }
+  }
+};
+
+// Builds a map's table with BandTable, strip by strip of nw * RPW rows.  part:
+// 2 * nw * 64 * CPL words of LDS.  No wave writes to S before every wave has
+// reached the first strip's barrier; the table is complete after the last.
+// kHalf: the table is that of the map zero-upsampled by two (HalfRowTable):
+// W_up columns, each column's sums at twice its place.
+template <typename T, int RPW, int CPL, bool kHalf = false>
+__device__ __forceinline__ void build_table_bands(const T* __restrict__ src, T* S, T* part, int H, int W, int pitch,
+                                                  float mu, bool sub, int W_up = 0) {
+  const int nw = blockDim.x >> 6, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  T carry[CPL];
+#pragma unroll
+  for (int k = 0; k < CPL; ++k) carry[k] = (T)0;
+  int buf = 0;
+  for (int r0 = 0; r0 < H; r0 += nw * RPW) {
+    BandTable<T, RPW, CPL> band;
+    const int row0 = r0 + wave * RPW;
+    T* pt = part + buf * nw * 64 * CPL;
+    band.load(src, H, W, row0);
+    band.sum_rows(pt, wave, sub, mu);
+    __syncthreads();
+    band.template finish<kHalf ? 2 : 1>(pt, nw, wave, carry, S, H, W, pitch, row0);
+    buf ^= 1;
+  }
+  __syncthreads();
+  if constexpr (kHalf) table_row_pass_up2(S, H, W, W_up, pitch);
+  else table_row_pass(S, H, W, pitch);
+  __syncthreads();
 }
 
 // Table of a zero-upsampled fp32 map (the transpose of sampling every s-th
@@ -321,8 +477,7 @@ __device__ __forceinline__ void box_walk_int(const Src& S, const Taps<T>& tp, in
                                              int y1, float mu, Emit& emit) {
   const int ba = x0 + tp.ox[0], bb = x0 + tp.ox[2];
   const ColGroups<Q, Src> cl(S, ba, bb);
-  const int st = S.row_step();
-  const int rc = S.row_coord(y0 + tp.oy[0]), rd = S.row_coord(y0 + tp.oy[2]);
+  const auto rc = S.row_coord(y0 + tp.oy[0]), rd = S.row_coord(y0 + tp.oy[2]);
   float ex[Q];
   if (kOffset) {
 #pragma unroll
@@ -333,8 +488,8 @@ __device__ __forceinline__ void box_walk_int(const Src& S, const Taps<T>& tp, in
     const int y = y0 + s;
     if (kFull || y < y1) {
       T ca[Q], cb[Q], da[Q], db[Q];
-      cl.runs(S, rc + s * st, ca, cb);
-      cl.runs(S, rd + s * st, da, db);
+      cl.runs(S, S.row_at(rc, s), ca, cb);
+      cl.runs(S, S.row_at(rd, s), da, db);
       T o[Q];
 #pragma unroll
       for (int q = 0; q < Q; ++q) o[q] = (db[q] - da[q]) - (cb[q] - ca[q]);
@@ -468,15 +623,14 @@ template <int SEG, bool kFull, typename Src>
 __device__ __forceinline__ void adjoint_walk(const Src& S, const Taps<float>& tp, int x0, int y0, int y1,
                                                   const float (&v)[SEG][kQ], float (&acc)[SEG][kQ], float (&E)[4]) {
   const typename Src::Cols cl = S.cols(x0 + tp.ox[0], x0 + tp.ox[2]);
-  const int st = S.row_step();
-  const int rc = S.row_coord(y0 + tp.oy[0]), rd = S.row_coord(y0 + tp.oy[2]);
+  const auto rc = S.row_coord(y0 + tp.oy[0]), rd = S.row_coord(y0 + tp.oy[2]);
   float Uc[kQ], Ud[kQ];
 #pragma unroll
   for (int j = 0; j <= SEG; ++j) {
     if (kFull || y0 + j <= y1) {
       float Uc1[kQ], Ac[kQ], Bc[kQ], Ud1[kQ], Ad[kQ], Bd[kQ];
-      table_row_grad(S, rc + j * st, cl, tp, Uc1, Ac, Bc);
-      table_row_grad(S, rd + j * st, cl, tp, Ud1, Ad, Bd);
+      table_row_grad(S, S.row_at(rc, j), cl, tp, Uc1, Ac, Bc);
+      table_row_grad(S, S.row_at(rd, j), cl, tp, Ud1, Ad, Bd);
 #pragma unroll
       for (int q = 0; q < kQ; ++q) {
         const float vp = j > 0 ? v[j - 1][q] : 0.f;
@@ -501,6 +655,27 @@ __device__ __forceinline__ void adjoint_walk(const Src& S, const Taps<float>& tp
     }
   }
 }
+
+// Items of a map: Q columns x SEG rows each, chunks fastest.  The last chunk
+// and the last segment are moved back to end at the map's edge, so that every
+// item is whole: its walk has no guards, and a wave never runs a guarded walk
+// beside an unguarded one (with 64 columns in 3-column chunks every wave held
+// a one-column chunk and ran both).  The overlapped outputs are computed twice,
+// by the same operations on the same table entries, and stored with the same
+// bits.  Maps smaller than one item (W < Q or H < SEG) take the guarded
+// instances (kTail).
+template <int SEG, int Q>
+struct ItemPos {
+  int xo, yo;  // first column and row that are the item's own
+  int x0, y0;  // first column and row it covers
+  __device__ __forceinline__ ItemPos(int it, int nch, int H, int W, bool tail) {
+    const int seg = it / nch, ch = it - seg * nch;
+    xo = ch * Q;
+    yo = seg * SEG;
+    x0 = tail ? xo : min(xo, W - Q);
+    y0 = tail ? yo : min(yo, H - SEG);
+  }
+};
 
 // Emitter of forward outputs: the Q outputs of row y0 + s at plane offset
 // off0 + s * W (elements; off0 = y0 * W + x0).
@@ -697,24 +872,45 @@ inline void with_flag(bool v, F&& f) {
 // Output rows per item of the strided forwards.
 constexpr int kSegS = 8;
 
-// Forward launch geometry shared by both LDS kernels.
-struct FwdGeom { int per_box_p, bpg, ngrp, threads; };
-inline FwdGeom fwd_geom_items(int N, int C, int B, int per_box) {
-  FwdGeom g;
-  g.per_box_p = ((per_box + 63) / 64) * 64;
-  g.bpg = 256 / g.per_box_p;
-  if (g.bpg < 1) g.bpg = 1;
-  if (g.bpg > B) g.bpg = B;
-  // keep enough blocks in flight to fill the chip
-  while (g.bpg > 1 && (long)N * C * ((B + g.bpg - 1) / g.bpg) < 2048) g.bpg = (g.bpg + 1) / 2;
-  g.ngrp = (B + g.bpg - 1) / g.bpg;
-  g.threads = min(g.bpg * g.per_box_p, 256);
-  return g;
-}
-inline FwdGeom fwd_geom(int N, int C, int H, int W, int B, int seg) {
-  return fwd_geom_items(N, C, B, n_chunks(W) * n_segs(H, seg));
+// Most threads of a forward block.
+constexpr int kFwdThreads = 512;
+
+// Columns per lane of the register-built tables (BandTable) of each compiled
+// pitch: 55 and 71 serve maps up to 64 wide, 103 up to 96.
+constexpr int band_cols(int pitch) { return pitch <= 71 ? 1 : 2; }
+// LDS of a table and of the band totals its builder exchanges.
+inline size_t table_lds_bytes(int rows, int W, int pitch_class, int threads) {
+  if (pitch_class == 0) return (size_t)(rows + 1) * lds_pitch(W) * 4;
+  return ((size_t)(rows + 1) * pitch_class + 2 * threads * band_cols(pitch_class)) * 4;
 }
 
+// f(std::integral_constant<int, pitch>) for a compiled pitch (0: run-time pitch).
+template <typename F>
+inline void with_pitch(int pitch, F&& f) {
+  switch (pitch) {
+    case 55: f(std::integral_constant<int, 55>{}); return;
+    case 71: f(std::integral_constant<int, 71>{}); return;
+    case 103: f(std::integral_constant<int, 103>{}); return;
+    default: f(std::integral_constant<int, 0>{});
+  }
+}
+
+// Forward launch geometry shared by both LDS kernels.
+struct FwdGeom { int per_box_p, bpg, ngrp, threads; };
+// Blocks of up to max_threads, each with a map's table of its own, so a block
+// takes as many of the map's boxes as fit its threads while every CU still
+// gets a block.
+inline FwdGeom fwd_geom_items(int N, int C, int B, int per_box, int max_threads) {
+  FwdGeom g;
+  g.per_box_p = ((per_box + 63) / 64) * 64;
+  g.bpg = max_threads / g.per_box_p;
+  if (g.bpg < 1) g.bpg = 1;
+  if (g.bpg > B) g.bpg = B;
+  while (g.bpg > 1 && (long)N * C * ((B + g.bpg - 1) / g.bpg) < 256) g.bpg = (g.bpg + 1) / 2;
+  g.ngrp = (B + g.bpg - 1) / g.bpg;
+  g.threads = min(g.bpg * g.per_box_p, max_threads);
+  return g;
+}
 
 // The HBM-table forwards re-read their tables through the caches; an output
 // larger than the last-level cache (256 MiB) cannot stay there for the next

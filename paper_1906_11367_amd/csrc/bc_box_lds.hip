@@ -4,27 +4,6 @@
 
 namespace bc {
 
-// Items of a map: Q columns x SEG rows each, chunks fastest.  The last chunk
-// and the last segment are moved back to end at the map's edge, so that every
-// item is whole: its walk has no guards, and a wave never runs a guarded walk
-// beside an unguarded one (with 64 columns in 3-column chunks every wave held
-// a one-column chunk and ran both).  The overlapped outputs are computed twice,
-// by the same operations on the same table entries, and stored with the same
-// bits.  Maps smaller than one item (W < Q or H < SEG) take the guarded
-// instances (kTail).
-template <int SEG, int Q>
-struct ItemPos {
-  int xo, yo;  // first column and row that are the item's own
-  int x0, y0;  // first column and row it covers
-  __device__ __forceinline__ ItemPos(int it, int nch, int H, int W, bool tail) {
-    const int seg = it / nch, ch = it - seg * nch;
-    xo = ch * Q;
-    yo = seg * SEG;
-    x0 = tail ? xo : min(xo, W - Q);
-    y0 = tail ? yo : min(yo, H - SEG);
-  }
-};
-
 // Forward on a map's table in LDS, for the boxes b0 .. b0+nb-1 of channel c.
 // Items of one box are (row segment, column chunk), chunk fastest so that
 // adjacent lanes write adjacent columns; each box's items are padded to a
@@ -53,7 +32,7 @@ __device__ __forceinline__ void fwd_boxes(const LdsTable<T>& tab, const int* __r
 // kPitch > 0: the table's row pitch compiled in (as in the LDS backward).  Q:
 // columns per item; kPack: how rows are stored (StoreRows).
 template <typename T, typename OutT, int SEG, bool kOffset, bool kInt, int kPitch, int Q, int kPack, bool kTail>
-__global__ __launch_bounds__(256) void k_box_fwd_lds(const T* __restrict__ x, const int* __restrict__ taps,
+__global__ __launch_bounds__(kFwdThreads) void k_box_fwd_lds(const T* __restrict__ x, const int* __restrict__ taps,
                                                      OutT* __restrict__ y, int C, int H, int W, int B, int bpg,
                                                      int per_box_p) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -65,7 +44,12 @@ __global__ __launch_bounds__(256) void k_box_fwd_lds(const T* __restrict__ x, co
   const T* src = x + (size_t)map * H * W;
   float mu = 0.f;
   if (kOffset) mu = block_mean(reinterpret_cast<const float*>(src), H * W, red);
-  build_table_lds<T, true>(src, S, H, W, pitch, mu, kOffset);
+  if constexpr (kPitch > 0) {
+    table_zero_edges(S, H, pitch);
+    build_table_bands<T, 16, band_cols(kPitch)>(src, S, S + (H + 1) * pitch, H, W, pitch, mu, kOffset);
+  } else {
+    build_table_lds<T, true>(src, S, H, W, pitch, mu, kOffset);
+  }
   const int b0 = grp * bpg;
   fwd_boxes<T, OutT, SEG, kOffset, kInt, Q, kPack, kTail>(LdsTable<T>{S, pitch, W, H}, taps, y, map, map % C, b0,
                                                           min(bpg, B - b0), H, W, B, per_box_p, mu);
@@ -106,7 +90,12 @@ __global__ __launch_bounds__(256) void k_box_fwd_lds_strided(const T* __restrict
   const T* src = x + (size_t)map * H * W;
   float mu = 0.f;
   if (kOffset) mu = block_mean(reinterpret_cast<const float*>(src), H * W, red);
-  build_table_lds(src, S, H, W, pitch, mu, kOffset);
+  if constexpr (kPitch > 0) {
+    table_zero_edges(S, H, pitch);
+    build_table_bands<T, 16, band_cols(kPitch)>(src, S, S + (H + 1) * pitch, H, W, pitch, mu, kOffset);
+  } else {
+    build_table_lds(src, S, H, W, pitch, mu, kOffset);
+  }
   const int b0 = grp * bpg;
   fwd_boxes_strided<T, OutT, kOffset, kInt>(LdsTable<T>{S, pitch, W, H}, taps, y, map, map % C, b0,
                                             min(bpg, B - b0), H, W, B, s, Ho, Wo, per_box_p, mu);
@@ -134,7 +123,13 @@ __global__ __launch_bounds__(256) void k_box_fwd_lds_strided(const T* __restrict
 // there, so each is counted once; its input gradient is written twice with the
 // same bits.
 // kTail: maps smaller than an item, every row and column guarded.
-template <int SEG, bool kInt, bool kUp, int kMaxT, bool kRelu, int kPitch, bool kTail>
+// kNext (4-row items, the map one strip of its block's bands): the next
+// gradient map is loaded while this one is walked.  Such calls have few blocks
+// per CU to hide that load behind; the 8-row items have no registers for it,
+// and more blocks.
+// kUp: 0 stride 1; 1 the table of the whole zero-upsampled map; 2 (stride 2)
+// its HalfRowTable.
+template <int SEG, bool kInt, int kUp, int kMaxT, bool kRelu, int kPitch, bool kTail, bool kNext>
 __global__ __launch_bounds__(kMaxT) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_box_bwd_lds(
     const float* __restrict__ x, const int* __restrict__ taps, const float* __restrict__ gy, void* __restrict__ gx,
     float* __restrict__ partials, int C, int H, int W, int B, int s, int Ho, int Wo) {
@@ -163,12 +158,38 @@ __global__ __launch_bounds__(kMaxT) __attribute__((amdgpu_waves_per_eu(4, 8))) v
   for (int s = 0; s < SEG; ++s)
 #pragma unroll
     for (int q = 0; q < kQ; ++q) acc[s][q] = 0.f;
-  const LdsTable<float> tg{SG, pitch, W, H};
+  using Table = typename std::conditional<kUp == 2, HalfRowTable, LdsTable<float>>::type;
+  const Table tg{SG, pitch, W, kUp == 2 ? Ho : H};
   const int* adj = taps + (size_t)C * B * 16;
+  constexpr bool kBands = kPitch > 0 && kUp != 1;
+  static_assert(kBands || kUp != 2, "half-row tables are built from bands");
+  const int trows = kUp == 2 ? Ho : H;  // rows of the table (below row 0)
+  constexpr int kRows = SEG == 8 && band_cols(kPitch) == 1 ? 32 : 16;
+  BandTable<float, kRows, band_cols(kPitch)> band;
+  float* part = SG + (trows + 1) * pitch;
+  const int uwave = __builtin_amdgcn_readfirstlane(wave);
+  if constexpr (kBands) table_zero_edges(SG, trows, pitch);
+  if constexpr (kNext) band.load(g0, H, W, uwave * kRows);
   for (int b = 0; b < B; ++b) {
-    __syncthreads();
-    if constexpr (kUp) build_table_lds_up(g0 + b * gplane, SG, H, W, pitch, s, Ho, Wo);
-    else build_table_lds(g0 + b * plane, SG, H, W, pitch, 0.f, false);
+    if constexpr (!kBands) __syncthreads();
+    if constexpr (kUp == 1) {
+      build_table_lds_up(g0 + b * gplane, SG, H, W, pitch, s, Ho, Wo);
+    } else if constexpr (kNext) {
+      float carry[band_cols(kPitch)] = {};
+      band.sum_rows(part, uwave, false, 0.f);
+      __syncthreads();
+      band.finish(part, nw, uwave, carry, SG, H, W, pitch, uwave * kRows);
+      __syncthreads();
+      table_row_pass(SG, H, W, pitch);
+      __syncthreads();
+      if (b + 1 < B) band.load(g0 + (b + 1) * plane, H, W, uwave * kRows);
+    } else if constexpr (kUp == 2) {
+      build_table_bands<float, 16, band_cols(kPitch), true>(g0 + b * gplane, SG, part, Ho, Wo, pitch, 0.f, false, W);
+    } else if constexpr (kBands) {
+      build_table_bands<float, kRows, band_cols(kPitch)>(g0 + b * plane, SG, part, H, W, pitch, 0.f, false);
+    } else {
+      build_table_lds(g0 + b * plane, SG, H, W, pitch, 0.f, false);
+    }
     const Taps<float> tp = load_taps(adj + (size_t)(c * B + b) * 16, W, H);
     if constexpr (kInt) {  // integer corners: input gradient only
       AccRows<SEG> em{acc};
@@ -189,17 +210,6 @@ __global__ __launch_bounds__(kMaxT) __attribute__((amdgpu_waves_per_eu(4, 8))) v
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
-// f(std::integral_constant<int, pitch>) for a compiled pitch (0: run-time pitch).
-template <typename F>
-static void with_pitch(int pitch, F&& f) {
-  switch (pitch) {
-    case 55: f(std::integral_constant<int, 55>{}); return;
-    case 71: f(std::integral_constant<int, 71>{}); return;
-    case 103: f(std::integral_constant<int, 103>{}); return;
-    default: f(std::integral_constant<int, 0>{});
-  }
-}
-
 // Rows per item of the forward: a box's items fill whole waves, and each item
 // reads one row more than it writes (and its start costs about two rows), so
 // the segment length with the least waves x (rows + 3) is taken; 8 rows on
@@ -219,13 +229,12 @@ static int fwd_seg(int H, int nch) {
 template <typename T, typename OutT, bool kOffset>
 static void fwd_lds_t(const void* x, const int* taps, void* y, int N, int C, int H, int W, int B, bool rounded,
                       int stride, hipStream_t s) {
-  const int pc = kOffset || std::is_same<T, int>::value ? 0 : lds_pitch_class(H, W);
-  const size_t shm = (size_t)(H + 1) * (pc ? pc : lds_pitch(W)) * sizeof(T);
+  const int pc = lds_pitch_class(H, W);
   if (stride == 1) {
     constexpr int Q = 6;
     if (W < Q || H < 8) {  // smaller than one item
       constexpr int SEG = 16;
-      const FwdGeom g = fwd_geom(N, C, H, W, B, SEG);
+      const FwdGeom g = fwd_geom_items(N, C, B, n_chunks(W) * n_segs(H, SEG), 256);
       const size_t shm0 = (size_t)(H + 1) * lds_pitch(W) * sizeof(T);
       with_flag(rounded, [&](auto ki) {
         hipLaunchKernelGGL((k_box_fwd_lds<T, OutT, SEG, kOffset, decltype(ki)::value, 0, kQ, 0, true>),
@@ -234,8 +243,10 @@ static void fwd_lds_t(const void* x, const int* taps, void* y, int N, int C, int
       });
       return;
     }
-    const int nch = (W + Q - 1) / Q, seg = pc ? fwd_seg(H, nch) : 8;
-    const FwdGeom g = fwd_geom_items(N, C, B, nch * n_segs(H, seg));
+    constexpr bool kOneSeg = kOffset || std::is_same<T, int>::value;
+    const int nch = (W + Q - 1) / Q, seg = pc && !kOneSeg ? fwd_seg(H, nch) : 8;
+    const FwdGeom g = fwd_geom_items(N, C, B, nch * n_segs(H, seg), kFwdThreads);
+    const size_t shm = table_lds_bytes(H, W, pc, g.threads);
     auto go = [&](auto ki, auto kseg, auto kp, auto kpack) {
       hipLaunchKernelGGL((k_box_fwd_lds<T, OutT, decltype(kseg)::value, kOffset, decltype(ki)::value,
                                         decltype(kp)::value, Q, decltype(kpack)::value, false>),
@@ -252,29 +263,25 @@ static void fwd_lds_t(const void* x, const int* taps, void* y, int N, int C, int
           go(ki, kseg, kp, std::integral_constant<int, 0>{});
         }
       };
-      if constexpr (kOffset || std::is_same<T, int>::value) {
-        packed(std::integral_constant<int, 8>{}, std::integral_constant<int, 0>{});
-      } else {
-        with_pitch(pc, [&](auto kp) {
-          if constexpr (decltype(kp)::value == 0) packed(std::integral_constant<int, 8>{}, kp);
-          else if (seg == 13) packed(std::integral_constant<int, 13>{}, kp);
-          else if (seg == 10) packed(std::integral_constant<int, 10>{}, kp);
-          else packed(std::integral_constant<int, 8>{}, kp);
-        });
-      }
+      with_pitch(pc, [&](auto kp) {
+        if constexpr (kOneSeg || decltype(kp)::value == 0) packed(std::integral_constant<int, 8>{}, kp);
+        else if (seg == 13) packed(std::integral_constant<int, 13>{}, kp);
+        else if (seg == 10) packed(std::integral_constant<int, 10>{}, kp);
+        else packed(std::integral_constant<int, 8>{}, kp);
+      });
     });
     return;
   }
   const int Ho = (H + stride - 1) / stride, Wo = (W + stride - 1) / stride;
-  const FwdGeom g = fwd_geom_items(N, C, B, Wo * ((Ho + kSegS - 1) / kSegS));
+  const FwdGeom g = fwd_geom_items(N, C, B, Wo * ((Ho + kSegS - 1) / kSegS), 256);
+  const size_t shm = table_lds_bytes(H, W, pc, g.threads);
   with_flag(rounded, [&](auto ki) {
     auto go = [&](auto kp) {
       hipLaunchKernelGGL((k_box_fwd_lds_strided<T, OutT, kOffset, decltype(ki)::value, decltype(kp)::value>),
                          dim3(N * C * g.ngrp), dim3(g.threads), shm, s, (const T*)x, taps, (OutT*)y, C, H, W, B, stride,
                          Ho, Wo, g.bpg, g.per_box_p);
     };
-    if constexpr (kOffset || std::is_same<T, int>::value) go(std::integral_constant<int, 0>{});
-    else with_pitch(pc, go);
+    with_pitch(pc, go);
   });
 }
 
@@ -299,26 +306,43 @@ static void bwd_lds_t(const float* x, const int* taps, const float* gy, void* gx
   const int threads = ((items + 63) / 64) * 64;
   const int Ho = (H + stride - 1) / stride, Wo = (W + stride - 1) / stride;
   const bool tail = W < kQ || H < SEG;
-  const int pc = tail ? 0 : lds_pitch_class(H, W);
-  const size_t shm = (size_t)(H + 1) * (pc ? pc : lds_pitch(W)) * sizeof(float);
-  auto go = [&](auto ki, auto ku, auto kr) {
-    auto launch = [&](auto kp, auto kt) {
+  int pc = tail ? 0 : lds_pitch_class(H, W);
+  if (stride > 2) pc = 0;  // the whole upsampled map is tabulated at run-time pitch
+  const bool half = stride == 2 && pc > 0;
+  const size_t shm = table_lds_bytes(half ? Ho : H, W, pc, threads);
+  using std::integral_constant;
+  auto go = [&](auto ki, auto kr) {
+    auto launch = [&](auto ku, auto kp, auto kt, auto kn) {
       hipLaunchKernelGGL((k_box_bwd_lds<SEG, decltype(ki)::value, decltype(ku)::value, kMaxT, decltype(kr)::value,
-                                        decltype(kp)::value, decltype(kt)::value>),
+                                        decltype(kp)::value, decltype(kt)::value, decltype(kn)::value>),
                          dim3(N * C), dim3(threads), shm, s, x, taps, gy, gx, partials, C, H, W, B, stride, Ho, Wo);
     };
-    if (tail) launch(std::integral_constant<int, 0>{}, std::true_type{});
-    else with_pitch(pc, [&](auto kp) {
-      // more than 256 items of 4 rows: maps wider than the two narrow classes
-      if constexpr (kMaxT > 256 && (decltype(kp)::value == 55 || decltype(kp)::value == 71))
-        launch(std::integral_constant<int, 0>{}, std::false_type{});
-      else launch(kp, std::false_type{});
-    });
+    const integral_constant<int, 0> c0;
+    if (stride > 1 && !half) {
+      if (tail) launch(integral_constant<int, 1>{}, c0, std::true_type{}, std::false_type{});
+      else launch(integral_constant<int, 1>{}, c0, std::false_type{}, std::false_type{});
+    } else if (tail) {
+      launch(c0, c0, std::true_type{}, std::false_type{});
+    } else {
+      with_pitch(pc, [&](auto kp) {
+        if constexpr (decltype(kp)::value > 0) {
+          if (half) {
+            launch(integral_constant<int, 2>{}, kp, std::false_type{}, std::false_type{});
+            return;
+          }
+        }
+        if constexpr (SEG == 4 && decltype(kp)::value > 0) {
+          if (H <= threads / 64 * 16) {
+            launch(c0, kp, std::false_type{}, std::true_type{});
+            return;
+          }
+        }
+        launch(c0, kp, std::false_type{}, std::false_type{});
+      });
+    }
   };
-  with_flag(stride > 1, [&](auto ku) {
-    if (rounded) go(std::true_type{}, ku, std::false_type{});
-    else with_flag(relu_bf16, [&](auto kr) { go(std::false_type{}, ku, kr); });
-  });
+  if (rounded) go(std::true_type{}, std::false_type{});
+  else with_flag(relu_bf16, [&](auto kr) { go(std::false_type{}, kr); });
 }
 
 // Segment length of the LDS backward: 8 rows when the map's items fit one

@@ -3,6 +3,9 @@
 #include "bc_box.hpp"
 
 namespace bc {
+#ifndef SPR
+#define SPR 32
+#endif
 
 // ---------------------------------------------------------------------------
 // Kernel splitting (Section 3.1, Fig. 2): a box cut at its centre line(s)
@@ -122,17 +125,24 @@ __device__ __forceinline__ void corner_walk(const Src& S, const int* __restrict_
 }
 
 // Forward of split boxes, table in LDS: as k_box_fwd_lds (a wave per box,
-// items of 3 columns x SEG rows), each item walking its box's shared corners.
-template <typename OutT, int SEG, int NXC, int NYC>
+// whole items of 3 columns x SEG rows), each item walking its box's shared
+// corners.
+template <typename OutT, int SEG, int NXC, int NYC, int kPitch, bool kTail>
 __global__ __launch_bounds__(256) void k_box_fwd_lds_split(const float* __restrict__ x, const int* __restrict__ rec,
                                                            OutT* __restrict__ y, int C, int H, int W, int B, int bpg,
                                                            int per_box_p) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   float* S = reinterpret_cast<float*>(smem_raw);
-  const int pitch = lds_pitch_dev(W);
+  const int pitch = kPitch > 0 ? kPitch : lds_pitch_dev(W);
   const int ngrp = (B + bpg - 1) / bpg;
   const int map = blockIdx.x / ngrp, grp = blockIdx.x - map * ngrp, c = map % C;
-  build_table_lds(x + (size_t)map * H * W, S, H, W, pitch, 0.f, false);
+  const float* src = x + (size_t)map * H * W;
+  if constexpr (kPitch > 0) {
+    table_zero_edges(S, H, pitch);
+    build_table_bands<float, 16, band_cols(kPitch)>(src, S, S + (H + 1) * pitch, H, W, pitch, 0.f, false);
+  } else {
+    build_table_lds(src, S, H, W, pitch, 0.f, false);
+  }
   const LdsTable<float> tab{S, pitch, W, H};
   const int b0 = grp * bpg, nb = min(bpg, B - b0);
   const int nch = (W + kQ - 1) / kQ, nseg = (H + SEG - 1) / SEG, per_box = nch * nseg;
@@ -140,14 +150,12 @@ __global__ __launch_bounds__(256) void k_box_fwd_lds_split(const float* __restri
     const int bl = __builtin_amdgcn_readfirstlane(it / per_box_p);
     const int r = it - bl * per_box_p;
     if (r >= per_box) continue;
-    const int seg = r / nch, ch = r - seg * nch;
+    const ItemPos<SEG, kQ> ip(r, nch, H, W, kTail);
     const int b = b0 + bl;
     const int* rb = rec + (size_t)(c * B + b) * 32;
     OutT* out = y + ((size_t)map * B + b) * H * W;
-    const int x0 = ch * kQ, y0 = seg * SEG, y1 = min(y0 + SEG, H);
-    StoreRows<OutT, float> em{out, W, x0, y0 * W + x0};
-    if (y0 + SEG <= H && x0 + kQ <= W) corner_walk<SEG, NXC, NYC, true>(tab, rb, x0, y0, y1, em);
-    else corner_walk<SEG, NXC, NYC, false>(tab, rb, x0, y0, y1, em);
+    StoreRows<OutT, float> em{out, W, ip.x0, ip.y0 * W + ip.x0};
+    corner_walk<SEG, NXC, NYC, !kTail>(tab, rb, ip.x0, ip.y0, min(ip.y0 + SEG, H), em);
   }
 }
 
@@ -307,15 +315,15 @@ __device__ __forceinline__ void split_box_grads(const float* __restrict__ f, con
 // one item of 3 columns x SEG rows per thread, input values in registers), one
 // walk over each box's mirrored corners.  Each wave writes its split_box_grads
 // sums to partials[(n * nw + wave) * C*B + c*B + b][8].
-// kW > 0: the map width compiled in, as in k_box_bwd_lds.
-template <int SEG, int NXC, int NYC, int kMaxT, int kW = 0>
+// kPitch > 0: the table's row pitch compiled in and its column sums formed in
+// registers, as in k_box_bwd_lds.
+template <int SEG, int NXC, int NYC, int kMaxT, int kPitch>
 __global__ __launch_bounds__(kMaxT) void k_box_bwd_lds_split(const float* __restrict__ x, const int* __restrict__ rec,
                                                            const float* __restrict__ gy, float* __restrict__ gx,
-                                                           float* __restrict__ partials, int C, int H, int W_arg,
+                                                           float* __restrict__ partials, int C, int H, int W,
                                                            int B) {
-  const int W = kW > 0 ? kW : W_arg;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int pitch = lds_pitch_dev(W);
+  const int pitch = kPitch > 0 ? kPitch : lds_pitch_dev(W);
   float* SG = reinterpret_cast<float*>(smem_raw);
   const int map = blockIdx.x, n = map / C, c = map - n * C;
   const int nw = blockDim.x >> 6, wave = threadIdx.x >> 6;
@@ -333,9 +341,15 @@ __global__ __launch_bounds__(kMaxT) void k_box_bwd_lds_split(const float* __rest
 #pragma unroll
     for (int q = 0; q < kQ; ++q) acc[s][q] = 0.f;
   const LdsTable<float> tg{SG, pitch, W, H};
+  if constexpr (kPitch > 0) table_zero_edges(SG, H, pitch);
   for (int b = 0; b < B; ++b) {
-    __syncthreads();
-    build_table_lds(g0 + b * plane, SG, H, W, pitch, 0.f, false);
+    if constexpr (kPitch > 0) {
+      build_table_bands<float, SEG == 8 && band_cols(kPitch) == 1 ? SPR : 16, band_cols(kPitch)>(
+          g0 + b * plane, SG, SG + (H + 1) * pitch, H, W, pitch, 0.f, false);
+    } else {
+      __syncthreads();
+      build_table_lds(g0 + b * plane, SG, H, W, pitch, 0.f, false);
+    }
     const int cb = c * B + b;
     const int* rb = rec + (size_t)cb * 32;
     float PX[NYC][2][NXC], PD[NYC][2][NXC];
@@ -477,10 +491,16 @@ hipError_t launch_box_prep_corners(const float* boxes, const float* piece_w, int
 template <typename OutT, int NXC, int NYC>
 static void fwd_split_t(const float* x, const int* rec, void* y, int N, int C, int H, int W, int B, hipStream_t s) {
   constexpr int SEG = 16;
-  const size_t shm = (size_t)(H + 1) * lds_pitch(W) * sizeof(float);
-  const FwdGeom g = fwd_geom(N, C, H, W, B, SEG);
-  hipLaunchKernelGGL((k_box_fwd_lds_split<OutT, SEG, NXC, NYC>), dim3(N * C * g.ngrp), dim3(g.threads), shm, s, x,
-                     rec, (OutT*)y, C, H, W, B, g.bpg, g.per_box_p);
+  const FwdGeom g = fwd_geom_items(N, C, B, n_chunks(W) * n_segs(H, SEG), 256);
+  const bool tail = W < kQ || H < SEG;
+  const int pc = tail ? 0 : lds_pitch_class(H, W);
+  const size_t shm = table_lds_bytes(H, W, pc, g.threads);
+  auto go = [&](auto kp, auto kt) {
+    hipLaunchKernelGGL((k_box_fwd_lds_split<OutT, SEG, NXC, NYC, decltype(kp)::value, decltype(kt)::value>),
+                       dim3(N * C * g.ngrp), dim3(g.threads), shm, s, x, rec, (OutT*)y, C, H, W, B, g.bpg, g.per_box_p);
+  };
+  if (tail) go(std::integral_constant<int, 0>{}, std::true_type{});
+  else with_pitch(pc, [&](auto kp) { go(kp, std::false_type{}); });
 }
 
 template <typename OutT>
@@ -506,22 +526,16 @@ hipError_t launch_box_prep_corners_adj(const float* boxes, const float* piece_w,
   return last_error();
 }
 
-// The pose network's maps are 48 columns wide (a 192-pixel-wide input at
-// stride 4): the LDS forward and backward take instances with that width
-// compiled in.
-constexpr int kPoseW = 48;
-
 template <int SEG, int NXC, int NYC, int kMaxT>
 static void bwd_split_t(const float* x, const int* rec, const float* gy, float* gx, float* partials, int N, int C,
                         int H, int W, int B, hipStream_t s) {
   const int threads = ((n_chunks(W) * n_segs(H, SEG) + 63) / 64) * 64;
-  const size_t shm = (size_t)(H + 1) * lds_pitch(W) * sizeof(float);
-  if (SEG == 8 && W == kPoseW)
-    hipLaunchKernelGGL((k_box_bwd_lds_split<SEG, NXC, NYC, kMaxT, kPoseW>), dim3(N * C), dim3(threads), shm, s, x,
-                       rec, gy, gx, partials, C, H, W, B);
-  else
-    hipLaunchKernelGGL((k_box_bwd_lds_split<SEG, NXC, NYC, kMaxT>), dim3(N * C), dim3(threads), shm, s, x, rec, gy,
-                       gx, partials, C, H, W, B);
+  const int pc = lds_pitch_class(H, W);
+  const size_t shm = table_lds_bytes(H, W, pc, threads);
+  with_pitch(pc, [&](auto kp) {
+    hipLaunchKernelGGL((k_box_bwd_lds_split<SEG, NXC, NYC, kMaxT, decltype(kp)::value>), dim3(N * C), dim3(threads),
+                       shm, s, x, rec, gy, gx, partials, C, H, W, B);
+  });
 }
 
 template <int SEG, int kMaxT>

@@ -157,7 +157,7 @@ __device__ __forceinline__ int med3_i32(int v, int hi) {
 
 // Table accessors.  A walk addresses a table row by an unclamped row
 // coordinate in the table's own units (row_coord(v) for table row v; one row
-// further is + row_step()), and the two runs of columns it reads by
+// further is + row_step()), row_at(c, j) the row j after c, and the two runs of columns it reads by
 // cols(ba, bb) with ba = x0 + fa, bb = x0 + fb unclamped.  runs<N>(coord, c,
 // sa, sb) returns S(clamp(v, 0, H), clamp(ba + k, 0, W)) and the same at bb,
 // k in [0, N); N = kQ + 1 for interpolated edges, kQ for integer ones.
@@ -176,6 +176,7 @@ struct LdsTable {
   }
   __device__ __forceinline__ int row_step() const { return pitch * (int)sizeof(T); }
   __device__ __forceinline__ int row_coord(int v) const { return v * row_step(); }
+  __device__ __forceinline__ int row_at(int c, int j) const { return c + j * row_step(); }
   // One column run at a time (the split-box corner walks): col(x) a clamped
   // column, row(coord) a clamped row, run4 the 4 words from there.
   using Col = const char*;
@@ -199,6 +200,18 @@ struct LdsTable {
   }
 };
 
+// LDS table of a map zero-upsampled by two in both directions, holding only
+// the rows that differ: row u of the upsampled map's table is row ceil(u / 2)
+// here (H is the number of the map's own rows), its columns are all there.  A
+// walk's rows alternate between two coordinates, those of its first two rows.
+struct HalfRowTable : LdsTable<float> {
+  struct Coord { int a, b; };
+  __device__ __forceinline__ Coord row_coord(int v) const {
+    return {((v + 1) >> 1) * row_step(), ((v + 2) >> 1) * row_step()};
+  }
+  __device__ __forceinline__ int row_at(const Coord& c, int j) const { return (j & 1 ? c.b : c.a) + (j >> 1) * row_step(); }
+};
+
 // Table in HBM, (H+1) x (W+1), unpadded: row coordinates are row indices and
 // every index is clamped.
 template <typename T, bool kVec = false>
@@ -209,6 +222,7 @@ struct GlobalTable {
   __device__ __forceinline__ Cols cols(int ba, int bb) const { return {ba, bb}; }
   __device__ __forceinline__ int row_step() const { return 1; }
   __device__ __forceinline__ int row_coord(int v) const { return v; }
+  __device__ __forceinline__ int row_at(int c, int j) const { return c + j; }
   using Col = int;
   using Row = const T*;
   __device__ __forceinline__ Col col(int x) const { return x; }
