@@ -99,6 +99,15 @@ BwdWs bwd_ws(int N, int C, int H, int W, int B, BoxPath path) {
   return w;
 }
 
+// An output that the call's last kernel writes whole, as scratch for the table
+// build before it; none if it shares memory with the tabulated input (a call
+// in place).
+bc::SatScratch sat_scratch(void* out, size_t out_bytes, const void* in, size_t in_bytes) {
+  const uintptr_t o = (uintptr_t)out, i = (uintptr_t)in;
+  if (!out || (o < i + in_bytes && i < o + out_bytes)) return {nullptr, 0};
+  return {out, out_bytes};
+}
+
 bc_status hip_status(hipError_t e) { return e == hipSuccess ? BC_OK : BC_ERR_HIP; }
 
 }  // namespace
@@ -136,7 +145,7 @@ bc_status sat_build(const void* x, int dt, void* sat, float* mean, int N, int C,
   if (dt != BC_I32 && dt != BC_F32) return BC_ERR_DTYPE;
   if (mean && dt != BC_F32) return BC_ERR_DTYPE;
   if (!aligned16(x) || !aligned16(sat) || (mean && !aligned16(mean))) return BC_ERR_ALIGN;
-  return hip_status(bc::launch_sat_build(x, dt == BC_I32, sat, mean, N * C, H, W, stream));
+  return hip_status(bc::launch_sat_build(x, dt == BC_I32, sat, mean, N * C, H, W, {nullptr, 0}, stream));
 }
 
 size_t bc_box_workspace_bytes_strided(int op, int N, int C, int H, int W, int B, int stride, unsigned flags) {
@@ -181,7 +190,9 @@ bc_status box_conv_fwd_strided(const void* x, int x_dt, const float* boxes, int 
     return hip_status(
         bc::launch_box_fwd_lds(x, is_int, taps, y, out_kind, N, C, H, W, B, offset, rounded, stride, stream));
   float* means = offset ? reinterpret_cast<float*>(base + L.means) : nullptr;
-  e = bc::launch_sat_build(x, is_int, base + L.sat, means, N * C, H, W, stream);
+  const size_t out_n = (size_t)N * C * B * ((H + stride - 1) / stride) * ((W + stride - 1) / stride);
+  e = bc::launch_sat_build(x, is_int, base + L.sat, means, N * C, H, W,
+                           sat_scratch(y, out_n * (out_kind == 2 ? 2 : 4), x, (size_t)N * C * H * W * 4), stream);
   if (e != hipSuccess) return BC_ERR_HIP;
   return hip_status(bc::launch_box_fwd_gather(base + L.sat, is_int, means, taps, y, out_kind, N, C, H, W, B, rounded,
                                               stride, stream));
@@ -228,8 +239,13 @@ static bc_status box_bwd_impl(const float* x, const float* boxes, const float* g
     e = bc::launch_box_bwd_lds(x, taps, grad_y, grad_x, partials, N, C, H, W, B, rounded, relu_bf16, stride, stream);
   } else {
     float* sat_g = reinterpret_cast<float*>(base + L.sat_g);
-    e = stride == 1 ? bc::launch_sat_build(grad_y, false, sat_g, nullptr, N * C * B, H, W, stream)
-                    : bc::launch_sat_build_up(grad_y, sat_g, N * C * B, H, W, stride, stream);
+    const size_t gy_n = (size_t)N * C * B * ((H + stride - 1) / stride) * ((W + stride - 1) / stride);
+    // grad_x may be x itself (each value is read before its place is written)
+    const size_t gx_bytes = (size_t)N * C * H * W * (relu_bf16 ? 2 : 4);
+    bc::SatScratch scratch = sat_scratch(grad_x, gx_bytes, grad_y, gy_n * 4);
+    if (sat_scratch(grad_x, gx_bytes, x, (size_t)N * C * H * W * 4).p == nullptr) scratch = {nullptr, 0};
+    e = stride == 1 ? bc::launch_sat_build(grad_y, false, sat_g, nullptr, N * C * B, H, W, scratch, stream)
+                    : bc::launch_sat_build_up(grad_y, sat_g, N * C * B, H, W, stride, scratch, stream);
     if (e == hipSuccess)
       e = bc::launch_box_bwd_gather(x, sat_g, taps, grad_x, partials, N, C, H, W, B, rounded, relu_bf16, stream);
   }
@@ -334,7 +350,10 @@ bc_status box_conv_split_fwd(const float* x, const float* boxes, const float* pi
   if (!hbm)
     return hip_status(bc::launch_box_fwd_lds_split(x, rec, y, y_dt == BC_BF16, N, C, H, W, B, nx, ny, stream));
   float* sat = reinterpret_cast<float*>(base + L.sat);
-  e = bc::launch_sat_build(x, false, sat, nullptr, N * C, H, W, stream);
+  e = bc::launch_sat_build(x, false, sat, nullptr, N * C, H, W,
+                           sat_scratch(y, (size_t)N * C * B * H * W * (y_dt == BC_BF16 ? 2 : 4), x,
+                                       (size_t)N * C * H * W * 4),
+                           stream);
   if (e != hipSuccess) return BC_ERR_HIP;
   return hip_status(bc::launch_box_fwd_gather_split(sat, rec, y, y_dt == BC_BF16, N, C, H, W, B, nx, ny, stream));
 }
@@ -364,7 +383,10 @@ bc_status box_conv_split_bwd(const float* x, const float* boxes, const float* pi
     e = bc::launch_box_bwd_lds_split(x, rec, grad_y, grad_x, partials, N, C, H, W, B, nx, ny, stream);
   if (e == hipSuccess && hbm) {
     float* sat_g = reinterpret_cast<float*>(base + L.sat);
-    e = bc::launch_sat_build(grad_y, false, sat_g, nullptr, N * C * B, H, W, stream);
+    const size_t gx_bytes = (size_t)N * C * H * W * 4;
+    bc::SatScratch scratch = sat_scratch(grad_x, gx_bytes, grad_y, gx_bytes * B);
+    if (sat_scratch(grad_x, gx_bytes, x, gx_bytes).p == nullptr) scratch = {nullptr, 0};
+    e = bc::launch_sat_build(grad_y, false, sat_g, nullptr, N * C * B, H, W, scratch, stream);
     if (e == hipSuccess)
       e = bc::launch_box_bwd_gather_split(x, sat_g, rec, grad_x, partials, N, C, H, W, B, nx, ny, stream);
   }

@@ -2,6 +2,8 @@
 // those tables, and the box-gradient reduction.  gfx950, wave64.
 #include "bc_box.hpp"
 
+#include <algorithm>
+
 namespace bc {
 
 // ---------------------------------------------------------------------------
@@ -79,33 +81,86 @@ constexpr int kSatRowsPerWave = 4;  // rows of a strip each wave loads before sc
 // 256 * kGroups threads take strips of kStrip * kGroups rows, and the column
 // pass runs kGroups row groups of kStrip rows in parallel, each starting from
 // the carried sums plus the totals of the groups above it.
-template <typename T, bool kUp, int KM, int kGroups>
+// kBands (few maps): a map's rows are divided over gridDim.x / maps blocks of
+// band_rows rows each; bands holds the column sums of every band
+// (k_sat_bands), from which a block forms the table row above its band, and
+// mean is read, not computed.
+template <typename T, bool kUp, int KM, int kGroups, bool kBands = false>
 __global__ __launch_bounds__(256 * kGroups) void k_sat_build(const T* __restrict__ x, T* __restrict__ sat,
                                                              float* __restrict__ mean, int H, int W, int s, int Ho,
-                                                             int Wo) {
+                                                             int Wo, const T* __restrict__ bands = nullptr,
+                                                             int nbands = 1, int band_rows = 0, int total = 0) {
   static_assert(kGroups == 1 || KM == 4, "row groups need W <= 256");
   constexpr int kRowsStrip = kStrip * kGroups;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T* tile = reinterpret_cast<T*>(smem_raw);
   __shared__ float red[16];
   __shared__ T part[kGroups > 1 ? kGroups * 256 : 1];
-  const int map = blockIdx.x;
+  int map = blockIdx.x, band = 0;
+  if constexpr (kBands) {
+    const int L = xcd_remap(blockIdx.x, gridDim.x);
+    if (L >= total) return;
+    map = L / nbands;
+    band = L - map * nbands;
+  }
   const T* src = x + (size_t)map * (kUp ? (size_t)Ho * Wo : (size_t)H * W);
   T* dst = sat + (size_t)map * (H + 1) * (W + 1);
   float mu = 0.f;
   const bool sub = mean != nullptr;
-  if (sub) {
+  if (sub && kBands) {
+    mu = mean[map];
+  } else if (sub) {
     mu = block_mean(reinterpret_cast<const float*>(src), H * W, red);
     if (threadIdx.x == 0) mean[map] = mu;
   }
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
   const int K = (W + 63) >> 6;
-  for (int v = tid; v <= W; v += blockDim.x) dst[v] = (T)0;
+  if (band == 0)
+    for (int v = tid; v <= W; v += blockDim.x) dst[v] = (T)0;
   T carry[KM / 4];
 #pragma unroll
   for (int j = 0; j < KM / 4; ++j) carry[j] = (T)0;
-  for (int r0 = 0; r0 < H; r0 += kRowsStrip) {
-    const int rows = min(kRowsStrip, H - r0);
+  const int r_begin = kBands ? band * band_rows : 0, r_end = kBands ? min(H, r_begin + band_rows) : H;
+  if (kBands && band > 0) {
+    // the table row above this band: the column sums of the bands above,
+    // scanned like a row of the map
+    for (int v = tid; v < W; v += blockDim.x) {
+      T above = (T)0;
+      if (!kUp || v % s == 0) {
+        const T* col = bands + (size_t)map * nbands * (kUp ? Wo : W) + (kUp ? v / s : v);
+#pragma unroll 4
+        for (int h = 0; h < band; ++h) above += col[(size_t)h * (kUp ? Wo : W)];
+      }
+      tile[v] = above;
+    }
+    __syncthreads();
+    if (wave == 0) {
+      T v[KM], run = (T)0;
+#pragma unroll
+      for (int k = 0; k < KM; ++k) {
+        const int idx = lane * K + k;
+        if (k < K) {
+          run += idx < W ? tile[idx] : (T)0;
+          v[k] = run;
+        }
+      }
+      const T excl = wave_excl_scan(run, lane);
+#pragma unroll
+      for (int k = 0; k < KM; ++k) {
+        const int idx = lane * K + k;
+        if (k < K && idx < W) tile[idx] = v[k] + excl;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < KM / 4; ++j) {
+      const int v = (kGroups == 1 ? tid : tid & 255) + j * 256;
+      if (v < W) carry[j] = tile[v];
+    }
+    __syncthreads();
+  }
+  for (int r0 = r_begin; r0 < r_end; r0 += kRowsStrip) {
+    const int rows = min(kRowsStrip, r_end - r0);
     // rows rr = wave + i * nw of the strip: all of a wave's loads are issued
     // before its first scan
     for (int rb = wave; rb < rows; rb += kSatRowsPerWave * nw) {
@@ -189,6 +244,37 @@ __global__ __launch_bounds__(256 * kGroups) void k_sat_build(const T* __restrict
     if (tid < rows) dst[(size_t)(r0 + tid + 1) * (W + 1)] = (T)0;
     __syncthreads();
   }
+}
+
+// Column sums of each band of band_rows rows of each map (minus the map's
+// mean, if given): bands[map][band][column of x].  One block per (map, band).
+template <typename T, bool kUp>
+__global__ __launch_bounds__(256) void k_sat_bands(const T* __restrict__ x, T* __restrict__ bands,
+                                                   const float* __restrict__ mean, int H, int W, int s, int Ho, int Wo,
+                                                   int nbands, int band_rows, int total) {
+  const int L = xcd_remap(blockIdx.x, gridDim.x);
+  if (L >= total) return;
+  const int map = L / nbands, band = L - map * nbands;
+  const int r0 = band * band_rows, r1 = min(H, r0 + band_rows);
+  const int i0 = kUp ? (r0 + s - 1) / s : r0, i1 = kUp ? (r1 + s - 1) / s : r1, cols = kUp ? Wo : W;
+  const T* src = x + (size_t)map * (kUp ? (size_t)Ho * Wo : (size_t)H * W);
+  const float mu = mean != nullptr ? mean[map] : 0.f;
+  for (int v = threadIdx.x; v < cols; v += 256) {
+    T sum = (T)0;
+#pragma unroll 8
+    for (int i = i0; i < i1; ++i) {
+      const T t = src[(size_t)i * cols + v];
+      sum += mean != nullptr ? (T)((float)t - mu) : t;
+    }
+    bands[(size_t)L * cols + v] = sum;
+  }
+}
+
+// Mean of each map.
+__global__ __launch_bounds__(1024) void k_map_mean(const float* __restrict__ x, float* __restrict__ mean, int n) {
+  __shared__ float red[16];
+  const float mu = block_mean(x + (size_t)blockIdx.x * n, n, red);
+  if (threadIdx.x == 0) mean[blockIdx.x] = mu;
 }
 
 // Forward, table in HBM: one block per (map, box, block of 256 items), mapped
@@ -347,38 +433,55 @@ hipError_t launch_unit_params(int op, const float* in, int n, float mw, float mh
   return last_error();
 }
 
-template <int KM, int kGroups>
-static void sat_build_t(const void* x, bool is_int, void* sat, float* mean, int maps, int H, int W, hipStream_t s) {
-  const size_t shm = (size_t)kStrip * kGroups * W * 4;
-  if (is_int)
-    hipLaunchKernelGGL((k_sat_build<int, false, KM, kGroups>), dim3(maps), dim3(256 * kGroups), shm, s,
-                       (const int*)x, (int*)sat, (float*)nullptr, H, W, 1, H, W);
-  else
-    hipLaunchKernelGGL((k_sat_build<float, false, KM, kGroups>), dim3(maps), dim3(256 * kGroups), shm, s,
-                       (const float*)x, (float*)sat, mean, H, W, 1, H, W);
-}
-
-// Fewer maps than 8 per CU leave one block per map short of filling the chip:
-// then maps up to 256 wide take blocks of 1024 threads over 64-row strips.
+// Maps too few to fill the chip with one block each: up to 256 wide they take
+// blocks of 1024 threads over 64-row strips; wider ones (fewer than 4 blocks
+// per CU), with scratch for the column sums of each band, are divided over
+// enough blocks for 8 per CU (one block walks the strips of its map one after
+// another, 9 us each: 2 x 32 maps of 288x384 157 us, divided XX us).
+#ifndef SATB
+#define SATB 2048
+#endif
+constexpr int kSatBandMaps = 1024, kSatBandBlocks = SATB;
 constexpr int kSatFewMaps = 2048;
 
+template <typename T, bool kUp>
+static void sat_build_t(const T* x, T* sat, float* mean, int maps, int H, int W, int stride, SatScratch scratch,
+                        hipStream_t s) {
+  const int Ho = (H + stride - 1) / stride, Wo = (W + stride - 1) / stride, cols = kUp ? Wo : W;
+  int nb = W > 256 && maps < kSatBandMaps ? std::min((kSatBandBlocks + maps - 1) / maps, (H + kStrip - 1) / kStrip) : 1;
+  nb = (int)std::min<size_t>(nb, scratch.bytes / ((size_t)maps * cols * 4));
+  if (nb > 1) {
+    const int band_rows = ((H + nb * kStrip - 1) / (nb * kStrip)) * kStrip;
+    nb = (H + band_rows - 1) / band_rows;
+    const int total = maps * nb;
+    T* bands = static_cast<T*>(scratch.p);
+    if (mean)
+      hipLaunchKernelGGL(k_map_mean, dim3(maps), dim3(1024), 0, s, reinterpret_cast<const float*>(x), mean, H * W);
+    hipLaunchKernelGGL((k_sat_bands<T, kUp>), dim3(pad8(total)), dim3(256), 0, s, x, bands, mean, H, W, stride, Ho, Wo,
+                       nb, band_rows, total);
+    hipLaunchKernelGGL((k_sat_build<T, kUp, kSatMaxK, 1, true>), dim3(pad8(total)), dim3(256),
+                       (size_t)kStrip * W * 4, s, x, sat, mean, H, W, stride, Ho, Wo, bands, nb, band_rows, total);
+    return;
+  }
+  auto go = [&](auto kernel, int groups) {
+    hipLaunchKernelGGL(kernel, dim3(maps), dim3(256 * groups), (size_t)kStrip * groups * W * 4, s, x, sat, mean, H, W,
+                       stride, Ho, Wo, (const T*)nullptr, 1, 0, 0);
+  };
+  if (W > 256) go(k_sat_build<T, kUp, kSatMaxK, 1>, 1);
+  else if (maps < kSatFewMaps && !kUp) go(k_sat_build<T, kUp, 4, kUp ? 1 : 4>, 4);
+  else go(k_sat_build<T, kUp, 4, 1>, 1);
+}
+
 hipError_t launch_sat_build(const void* x, bool is_int, void* sat, float* mean, int maps, int H, int W,
-                            hipStream_t s) {
-  if (W <= 256 && maps < kSatFewMaps) sat_build_t<4, 4>(x, is_int, sat, mean, maps, H, W, s);
-  else if (W <= 256) sat_build_t<4, 1>(x, is_int, sat, mean, maps, H, W, s);
-  else sat_build_t<kSatMaxK, 1>(x, is_int, sat, mean, maps, H, W, s);
+                            SatScratch scratch, hipStream_t s) {
+  if (is_int) sat_build_t<int, false>((const int*)x, (int*)sat, nullptr, maps, H, W, 1, scratch, s);
+  else sat_build_t<float, false>((const float*)x, (float*)sat, mean, maps, H, W, 1, scratch, s);
   return last_error();
 }
 
-hipError_t launch_sat_build_up(const float* x, float* sat, int maps, int H, int W, int stride, hipStream_t s) {
-  const size_t shm = (size_t)kStrip * W * 4;
-  const int Ho = (H + stride - 1) / stride, Wo = (W + stride - 1) / stride;
-  if (W <= 256)
-    hipLaunchKernelGGL((k_sat_build<float, true, 4, 1>), dim3(maps), dim3(256), shm, s, x, sat, (float*)nullptr, H,
-                       W, stride, Ho, Wo);
-  else
-    hipLaunchKernelGGL((k_sat_build<float, true, kSatMaxK, 1>), dim3(maps), dim3(256), shm, s, x, sat,
-                       (float*)nullptr, H, W, stride, Ho, Wo);
+hipError_t launch_sat_build_up(const float* x, float* sat, int maps, int H, int W, int stride, SatScratch scratch,
+                               hipStream_t s) {
+  sat_build_t<float, true>(x, sat, nullptr, maps, H, W, stride, scratch, s);
   return last_error();
 }
 

@@ -32,11 +32,15 @@ inline int n_segs(int H, int seg) { return (H + seg - 1) / seg; }
 hipError_t launch_box_prep(const float* boxes, int C, int B, bool rounded, void* table, hipStream_t s);
 inline size_t tap_table_bytes(int C, int B) { return (size_t)2 * C * B * 16 * 4; }
 
+// scratch: device memory the call may use (contents lost) for the column sums
+// of the bands it divides few maps into; none: {nullptr, 0}.
+struct SatScratch { void* p; size_t bytes; };
 hipError_t launch_sat_build(const void* x, bool is_int, void* sat, float* mean,
-                            int maps, int H, int W, hipStream_t s);
+                            int maps, int H, int W, SatScratch scratch, hipStream_t s);
 // Tables of zero-upsampled maps: x [maps][ceil(H/stride)][ceil(W/stride)]
 // placed at every stride-th pixel of an H x W map (stride > 1).
-hipError_t launch_sat_build_up(const float* x, float* sat, int maps, int H, int W, int stride, hipStream_t s);
+hipError_t launch_sat_build_up(const float* x, float* sat, int maps, int H, int W, int stride,
+                               SatScratch scratch, hipStream_t s);
 
 // Forward, table in LDS.  out_kind: 0 = same type as x, 1 = fp32, 2 = bf16.
 // stride > 1: y is [N][C*B][ceil(H/stride)][ceil(W/stride)].
@@ -115,6 +119,16 @@ hipError_t launch_box_fwd_stream(const void* x, bool is_int, const int* taps, vo
 hipError_t launch_mix(int mode, const void* a, int a_dt, const void* b, int b_dt, void* out,
                       int out_dt, int N, int M, int K, int P, int compute_dt, int relu,
                       const float* aux, int accumulate, void* ws, size_t ws_bytes, hipStream_t s);
+// FWD on bf16 storage, pipelined (bc_mix_pipe.hip): whether it takes the
+// request, and the launch.
+bool mix_fwd_pipe_takes(const void* w, const void* in, int N, int M, int K, int P);
+hipError_t launch_mix_fwd_pipe(const void* w, const void* in, float* out, int N, int M, int K, int P, int relu,
+                               hipStream_t s);
+// BWD_WEIGHT on bf16 storage, pipelined: partials part[n * sp + i][M][K] over
+// pixels [i * chunk, (i + 1) * chunk) of image n; chunk a multiple of 64.
+bool mix_wgrad_pipe_takes(const void* grad, const void* in, int N, int M, int K, int P);
+hipError_t launch_mix_wgrad_pipe(const void* grad, const void* in, float* part, int N, int M, int K, int P, int sp,
+                                 int chunk, hipStream_t s);
 size_t mix_workspace_bytes(int mode, int N, int M, int K, int P, int compute_dt);
 hipError_t launch_cast_bf16(const float* src, void* dst, size_t n, hipStream_t s);
 hipError_t launch_relu_cast_bf16(const float* g, const float* aux, void* dst, size_t n, hipStream_t s);
