@@ -20,8 +20,9 @@ namespace bc {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
-constexpr int kBM = 128, kBN = 128;
-constexpr int kMixThreads = 256;  // 4 waves in a 2 x 2 arrangement of 64 x 64 sub-tiles
+// Block tiles are kTile x kTile, kTile = 128 or 64: 4 waves in a 2 x 2
+// arrangement of sub-tiles of half the side (mix_tile chooses).
+constexpr int kMixThreads = 256;
 
 // Storage dtype codes follow bc_dtype: 0 = int32, 1 = fp32, 2 = bf16.
 template <int DT> struct StoreBytes { static constexpr int v = DT == 2 ? 2 : 4; };
@@ -33,33 +34,43 @@ __device__ __forceinline__ uint32_t ld_bits(const char* base, size_t idx) {
   else return reinterpret_cast<const uint32_t*>(base)[idx];
 }
 
-// N consecutive elements as raw bits (one 32-bit word per element; bf16 in
-// the low half).  `vec` = in range and aligned for one wide load.
+// kBytes from memory of the element type's own alignment (2 or 4 bytes): one
+// wide load, which global memory accesses may be at any alignment here, so
+// that rows of an odd length cost no more instructions than aligned ones.
+template <int kBytes, int kAlign> struct __attribute__((packed, aligned(kAlign))) Bytes { uint32_t w[kBytes / 4]; };
+
+// N consecutive elements as stored: N words, or N / 2 packed pairs of bf16.
 template <int DT, int N>
-__device__ __forceinline__ void ld_run(const char* base, size_t idx, bool vec, int avail, uint32_t* w) {
-  if (vec) {
-    if constexpr (DT == 2) {
-      static_assert(N == 4 || N == 8, "bf16 runs are 4 or 8 long");
-      if constexpr (N == 8) {
-        const uint4 q = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(base) + idx);
-        const uint32_t p[4] = {q.x, q.y, q.z, q.w};
+__device__ __forceinline__ void ld_vec(const char* base, size_t idx, uint32_t* w) {
+  constexpr int kSize = N * StoreBytes<DT>::v;
+  const auto t = *reinterpret_cast<const Bytes<kSize, StoreBytes<DT>::v>*>(base + idx * StoreBytes<DT>::v);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) { w[2 * k] = p[k] & 0xffffu; w[2 * k + 1] = p[k] >> 16; }
-      } else {
-        const uint2 q = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(base) + idx);
-        w[0] = q.x & 0xffffu; w[1] = q.x >> 16; w[2] = q.y & 0xffffu; w[3] = q.y >> 16;
-      }
-    } else {
+  for (int k = 0; k < kSize / 4; ++k) w[k] = t.w[k];
+}
+
+// The same, element by element, those from `avail` on 0: for the last
+// elements of an operand, which a wide load would run past.
+template <int DT, int N>
+__device__ __forceinline__ void ld_few(const char* base, size_t idx, int avail, uint32_t* w) {
 #pragma unroll
-      for (int k = 0; k < N; k += 4) {
-        const uint4 q = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(base) + idx + k);
-        w[k] = q.x; w[k + 1] = q.y; w[k + 2] = q.z; w[k + 3] = q.w;
-      }
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < N; ++k) w[k] = k < avail ? ld_bits<DT>(base, idx + k) : 0u;
+  for (int k = 0; k < N; ++k) {
+    const uint32_t b = k < avail ? ld_bits<DT>(base, idx + k) : 0u;
+    if constexpr (DT != 2) w[k] = b;
+    else if (k & 1) w[k / 2] |= b << 16;
+    else w[k / 2] = b;
   }
+}
+
+// N consecutive elements as raw bits (one 32-bit word per element; bf16 in
+// the low half), of which `avail` lie in the operand; `wide`: all N lie in its
+// memory (whatever row they belong to).
+template <int DT, int N>
+__device__ __forceinline__ void ld_run(const char* base, size_t idx, bool wide, int avail, uint32_t* w) {
+  uint32_t t[DT == 2 ? N / 2 : N];
+  if (wide) ld_vec<DT, N>(base, idx, t);
+  else ld_few<DT, N>(base, idx, avail, t);
+#pragma unroll
+  for (int k = 0; k < N; ++k) w[k] = DT == 2 ? ((k & 1) ? t[k / 2] >> 16 : t[k / 2] & 0xffffu) : t[k];
 }
 
 // Buffer-resource loads: a wave-uniform descriptor of one operand (base and
@@ -137,36 +148,43 @@ __device__ __forceinline__ int bf16_tile_off(int r, int l) {
 // at p[l * ld + r] (r contiguous).  Optional fp32 mask with the same indexing:
 // elements whose mask is not > 0 read as zero (ReLU derivative).
 //
-// A block stages rows [r0, r0 + 128) x l in [l0, l0 + BK) into an LDS tile
-// T[128][PITCH] in the compute type with l contiguous (what the MFMA operand
+// A block stages rows [r0, r0 + ROWS) x l in [l0, l0 + BK) into an LDS tile
+// T[ROWS][PITCH] in the compute type with l contiguous (what the MFMA operand
 // registers hold).  Loading (global -> registers, issued a whole K-step ahead)
 // is split from storing (registers -> LDS), so the loads of the next tile are
 // in flight while the current one feeds the MFMAs.
-//   KC:     a unit is UL consecutive l of one row        (NU = 4 per thread)
-//   not KC: a unit is UL consecutive l x 4 consecutive r (1 per thread); the
-//           4 x UL block is transposed in registers so every LDS write is
-//           16 contiguous bytes of one row.
-// bf16 storage without a mask is kept packed and never converted.
-template <bool BF16, int DT, bool KC, bool MASK, int kDeep = 0>
+//   KC:     a unit is UL consecutive l of one row
+//   not KC: a unit is UL consecutive l x 4 consecutive r; the 4 x UL block is
+//           transposed in registers so every LDS write is 16 contiguous bytes
+//           of one row.
+// NU units per thread.  bf16 storage without a mask is kept packed and never
+// converted.
+template <bool BF16, int DT, bool KC, bool MASK, int ROWS, int kBK>
 struct Stager {
-  static constexpr int BK = kDeep > 0 ? kDeep : (BF16 ? 64 : 32);
+  static constexpr int BK = kBK;
   static constexpr int PITCH = BF16 ? BK + 8 : BK + 1;  // elements; bf16 rows are 16-byte aligned
   static constexpr int UL = BF16 ? 8 : 4;               // l per unit
-  static constexpr int NU = KC ? (kBM * BK / UL) / kMixThreads : 1;
+  static constexpr int NU = KC ? (ROWS * BK / UL) / kMixThreads : (ROWS / 4) * (BK / UL) / kMixThreads;
+  static_assert(NU >= 1, "every thread has a unit");
   static constexpr bool kRaw = BF16 && DT == 2 && !MASK;
-  // words held per thread: packed bf16 pairs, or one word per element
-  static constexpr int NW = kRaw ? (KC ? NU * UL / 2 : UL * 2) : (KC ? NU * UL : 4 * UL);
+  // words of one unit: packed bf16 pairs, or one word per element
+  static constexpr int UW = KC ? (kRaw ? UL / 2 : UL) : (kRaw ? UL * 2 : 4 * UL);
+  static constexpr int NW = NU * UW;
   using E = typename std::conditional<BF16, uint16_t, float>::type;
 
   // Byte offset of this thread's first load inside a tile (the same for every
   // K-step); its other loads sit a wave-uniform step further each: KC units
-  // are kMixThreads / (BK / UL) rows apart, non-KC rows one l apart.
+  // are kMixThreads / (BK / UL) rows apart, non-KC rows one l apart (and
+  // units kUnitL l apart).
+  static constexpr int kUnitL = KC ? 0 : kMixThreads / (ROWS / 4) * UL;
   static constexpr int SB = DT == 2 ? 2 : 4;
 
   const char* p;
   const float* mask;
   long ld;
   int rows, depth;
+  long extent;  // elements of this image's operand
+  int lrem;     // reduction indices left from the loaded tile's first
   bool vec_ok;
   uint32_t off0;
   __amdgpu_buffer_rsrc_t rs, mrs;
@@ -177,8 +195,8 @@ struct Stager {
   __device__ __forceinline__ void init_offsets() {
     const int tid = threadIdx.x;
     if constexpr (KC) off0 = (uint32_t)(((long)(tid / (BK / UL)) * ld + (tid % (BK / UL)) * UL) * SB);
-    else off0 = (uint32_t)(((long)((tid / (kBM / 4)) * UL) * ld + (tid % (kBM / 4)) * 4) * SB);
-    const long extent = KC ? (long)(rows - 1) * ld + depth : (long)(depth - 1) * ld + rows;  // elements
+    else off0 = (uint32_t)(((long)((tid / (ROWS / 4)) * UL) * ld + (tid % (ROWS / 4)) * 4) * SB);
+    extent = KC ? (long)(rows - 1) * ld + depth : (long)(depth - 1) * ld + rows;  // elements
     rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(p), (short)0, (int)(extent * SB), kBufWord3);
     if constexpr (MASK)
       mrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(mask), (short)0, (int)(extent * 4), kBufWord3);
@@ -188,7 +206,6 @@ struct Stager {
   }
   // Whether an image's operand fits the 32-bit byte offsets of the buffer path.
   __device__ __forceinline__ bool buf_ok() const {
-    const long extent = KC ? (long)(rows - 1) * ld + depth : (long)(depth - 1) * ld + rows;
     return extent * 4 < (1L << 31);
   }
 
@@ -198,103 +215,100 @@ struct Stager {
   // the buffer descriptor: the thread's one offset plus a wave-uniform offset
   // per K-step and unit, so no address is computed in the loop.
   __device__ __forceinline__ void load(int r0, int l0) {
-    if (vec_ok && r0 + kBM <= rows && l0 + BK <= depth) load_full(r0, l0);
-    else load_tile<false>(r0, l0);
+    lrem = depth - l0;
+    if (vec_ok && r0 + ROWS <= rows && lrem >= BK) load_full(r0, l0);
+    else load_edge(r0, l0);
   }
 
   __device__ __forceinline__ void load_full(int r0, int l0) {
     const uint32_t origin = (uint32_t)(KC ? (long)r0 * ld + l0 : (long)l0 * ld + r0);
     const uint32_t step = (uint32_t)unit_step();
     const uint32_t moff = off0 / SB * 4;
-    if constexpr (KC) {
 #pragma unroll
-      for (int u = 0; u < NU; ++u) {
+    for (int u = 0; u < NU; ++u) {
+      if constexpr (KC) {
         const uint32_t so = origin * SB + u * step;
         if constexpr (kRaw) {
           const uint4 q = buf_ld16(rs, off0, so);
-          uint32_t* w = v + u * (UL / 2);
+          uint32_t* w = v + u * UW;
           w[0] = q.x; w[1] = q.y; w[2] = q.z; w[3] = q.w;
         } else {
-          buf_run<DT, UL>(rs, off0, so, v + u * UL);
-          if constexpr (MASK) buf_run<1, UL>(mrs, moff, origin * 4 + u * (step / SB * 4), m + u * UL);
+          buf_run<DT, UL>(rs, off0, so, v + u * UW);
+          if constexpr (MASK) buf_run<1, UL>(mrs, moff, origin * 4 + u * (step / SB * 4), m + u * UW);
         }
-      }
-    } else {
+      } else {
 #pragma unroll
-      for (int e = 0; e < UL; ++e) {
-        const uint32_t so = origin * SB + e * step;
-        if constexpr (kRaw) {
-          const uint2 q = buf_ld8(rs, off0, so);
-          v[e * 2] = q.x; v[e * 2 + 1] = q.y;
-        } else {
-          buf_run<DT, 4>(rs, off0, so, v + e * 4);
-          if constexpr (MASK) buf_run<1, 4>(mrs, moff, origin * 4 + e * (step / SB * 4), m + e * 4);
+        for (int e = 0; e < UL; ++e) {
+          const uint32_t so = origin * SB + (u * kUnitL + e) * step;
+          if constexpr (kRaw) {
+            const uint2 q = buf_ld8(rs, off0, so);
+            v[u * UW + e * 2] = q.x; v[u * UW + e * 2 + 1] = q.y;
+          } else {
+            buf_run<DT, 4>(rs, off0, so, v + u * UW + e * 4);
+            if constexpr (MASK) buf_run<1, 4>(mrs, moff, origin * 4 + (u * kUnitL + e) * (step / SB * 4), m + u * UW + e * 4);
+          }
         }
       }
     }
   }
 
-  template <bool kFull>
-  __device__ __forceinline__ void load_tile(int r0, int l0) {
+  // Tiles at the operand's edges and operands of any alignment: the same wide
+  // loads from clamped addresses, unaligned.  What lies outside needs no
+  // guard where it only reaches outputs that are not stored (rows past the
+  // last: the last row again, or, row-contiguous, the next l's values); l past
+  // the range is zeroed when the tile is stored to LDS.  Only the operand's
+  // last few elements, which a wide load would run past, are read one by one.
+  __device__ __forceinline__ void load_edge(int r0, int l0) {
     const int tid = threadIdx.x;
-    if constexpr (KC) {
 #pragma unroll
-      for (int u = 0; u < NU; ++u) {
+    for (int u = 0; u < NU; ++u) {
+      if constexpr (KC) {
         const int unit = tid + u * kMixThreads;
-        const int r = r0 + unit / (BK / UL), l = l0 + (unit % (BK / UL)) * UL;
-        if constexpr (kRaw) {
-          uint32_t* w = v + u * (UL / 2);
-          if (kFull) {
-            const uint4 q = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(p) + (size_t)r * ld + l);
-            w[0] = q.x; w[1] = q.y; w[2] = q.z; w[3] = q.w;
-          } else {
-            uint32_t e[UL];
-            const bool in = r < rows;
-            const int avail = in ? min(UL, max(0, depth - l)) : 0;
-            ld_run<2, UL>(p, (size_t)(in ? r : 0) * ld + (avail > 0 ? l : 0), false, avail, e);
+        const int r = min(r0 + unit / (BK / UL), rows - 1), l = l0 + (unit % (BK / UL)) * UL;
+        const long idx = (long)r * ld + min(l, depth - 1);
+        load_unit<UL>(idx, min(UL, depth - l), v + u * UW, m + (MASK ? u * UW : 0));
+      } else {
+        const int unit = tid + u * kMixThreads;
+        const int r = r0 + (unit % (ROWS / 4)) * 4, lb = l0 + (unit / (ROWS / 4)) * UL;
 #pragma unroll
-            for (int k = 0; k < UL / 2; ++k) w[k] = e[2 * k] | (e[2 * k + 1] << 16);
-          }
-        } else if constexpr (kFull) {
-          const size_t idx = (size_t)r * ld + l;
-          ld_run<DT, UL>(p, idx, true, UL, v + u * UL);
-          if constexpr (MASK) ld_run<1, UL>(reinterpret_cast<const char*>(mask), idx, true, UL, m + u * UL);
-        } else {
-          const bool in = r < rows;
-          const int avail = in ? min(UL, max(0, depth - l)) : 0;
-          const size_t idx = (size_t)(in ? r : 0) * ld + (avail > 0 ? l : 0);
-          ld_run<DT, UL>(p, idx, false, avail, v + u * UL);
-          if constexpr (MASK) ld_run<1, UL>(reinterpret_cast<const char*>(mask), idx, false, avail, m + u * UL);
+        for (int e = 0; e < UL; ++e) {
+          const long idx = (long)min(lb + e, depth - 1) * ld + min(r, rows - 1);
+          load_unit<4>(idx, rows - r, v + u * UW + e * (UW / UL), m + (MASK ? u * UW + e * 4 : 0));
         }
       }
+    }
+  }
+
+  template <int N>
+  __device__ __forceinline__ void load_unit(long idx, int avail, uint32_t* w, uint32_t* mw) const {
+    const bool wide = idx + N <= extent;
+    if constexpr (kRaw) {
+      if (wide) ld_vec<DT, N>(p, idx, w);
+      else ld_few<DT, N>(p, idx, avail, w);
     } else {
-      const int r = r0 + (tid % (kBM / 4)) * 4, lb = l0 + (tid / (kBM / 4)) * UL;
-      const int ravail = max(0, min(4, rows - r));
+      ld_run<DT, N>(p, idx, wide, avail, w);
+      if constexpr (MASK) ld_run<1, N>(reinterpret_cast<const char*>(mask), idx, wide, avail, mw);
+    }
+  }
+
+  // Zeroes the loaded values of reduction indices past the range.
+  __device__ __forceinline__ void zero_past() {
+    const int tid = threadIdx.x;
 #pragma unroll
-      for (int e = 0; e < UL; ++e) {
-        const int l = lb + e;
-        if constexpr (kRaw) {
-          uint32_t* w = v + e * 2;
-          if (kFull) {
-            const uint2 q = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(p) + (size_t)l * ld + r);
-            w[0] = q.x; w[1] = q.y;
-          } else {
-            uint32_t t[4];
-            const int avail = l < depth ? ravail : 0;
-            ld_run<2, 4>(p, (size_t)(avail > 0 ? l : 0) * ld + (avail > 0 ? r : 0), false, avail, t);
-            w[0] = t[0] | (t[1] << 16);
-            w[1] = t[2] | (t[3] << 16);
-          }
-        } else if constexpr (kFull) {
-          const size_t idx = (size_t)l * ld + r;
-          ld_run<DT, 4>(p, idx, true, 4, v + e * 4);
-          if constexpr (MASK) ld_run<1, 4>(reinterpret_cast<const char*>(mask), idx, true, 4, m + e * 4);
-        } else {
-          const int avail = l < depth ? ravail : 0;
-          const size_t idx = (size_t)(avail > 0 ? l : 0) * ld + (avail > 0 ? r : 0);
-          ld_run<DT, 4>(p, idx, false, avail, v + e * 4);
-          if constexpr (MASK) ld_run<1, 4>(reinterpret_cast<const char*>(mask), idx, false, avail, m + e * 4);
+    for (int u = 0; u < NU; ++u) {
+      if constexpr (KC) {
+        const int left = lrem - (tid % (BK / UL)) * UL;
+#pragma unroll
+        for (int k = 0; k < UW; ++k) {
+          if constexpr (kRaw) v[u * UW + k] &= left >= 2 * k + 2 ? 0xffffffffu : left == 2 * k + 1 ? 0xffffu : 0u;
+          else v[u * UW + k] = left > k ? v[u * UW + k] : 0u;
         }
+      } else {
+        const int left = lrem - (tid / (ROWS / 4)) * UL - u * kUnitL;
+#pragma unroll
+        for (int e = 0; e < UL; ++e)
+#pragma unroll
+          for (int k = 0; k < UW / UL; ++k) v[u * UW + e * (UW / UL) + k] = left > e ? v[u * UW + e * (UW / UL) + k] : 0u;
       }
     }
   }
@@ -302,19 +316,19 @@ struct Stager {
   __device__ __forceinline__ uint32_t mk(int i) const { return MASK ? m[i] : 0u; }
   __device__ __forceinline__ float f(int i) const { return operand_f32<DT, MASK>(v[i], mk(i)); }
 
-  __device__ __forceinline__ void store(E* T) const {
+  __device__ __forceinline__ void store(E* T) {
     const int tid = threadIdx.x;
-    if constexpr (KC) {
+    if (lrem < BK) zero_past();
 #pragma unroll
-      for (int u = 0; u < NU; ++u) {
-        const int unit = tid + u * kMixThreads;
+    for (int u = 0; u < NU; ++u) {
+      const int unit = tid + u * kMixThreads, b = u * UW;
+      if constexpr (KC) {
         const int r = unit / (BK / UL), l = (unit % (BK / UL)) * UL;
         if constexpr (BF16) {
           uint4 q;
           if constexpr (kRaw) {
-            q.x = v[u * 4 + 0]; q.y = v[u * 4 + 1]; q.z = v[u * 4 + 2]; q.w = v[u * 4 + 3];
+            q.x = v[b + 0]; q.y = v[b + 1]; q.z = v[b + 2]; q.w = v[b + 3];
           } else {
-            const int b = u * UL;
             q.x = pack2_bf16(f(b + 0), f(b + 1)); q.y = pack2_bf16(f(b + 2), f(b + 3));
             q.z = pack2_bf16(f(b + 4), f(b + 5)); q.w = pack2_bf16(f(b + 6), f(b + 7));
           }
@@ -322,51 +336,51 @@ struct Stager {
         } else {
           E* dst = T + r * PITCH + l;
 #pragma unroll
-          for (int k = 0; k < UL; ++k) dst[k] = f(u * UL + k);
+          for (int k = 0; k < UL; ++k) dst[k] = f(b + k);
         }
-      }
-    } else {
-      const int r = (tid % (kBM / 4)) * 4, lb = (tid / (kBM / 4)) * UL;
+      } else {
+        const int r = (unit % (ROWS / 4)) * 4, lb = (unit / (ROWS / 4)) * UL;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if constexpr (BF16) {
-          uint4 q;
-          if constexpr (kRaw) {
-            // element i of rows (l, l+1) -> one packed word: bytes of the
-            // low (i even) or high (i odd) halves of the two source words
-            const uint32_t sel = (i & 1) ? 0x07060302u : 0x05040100u;
-            const int h = i >> 1;
-            q.x = __builtin_amdgcn_perm(v[1 * 2 + h], v[0 * 2 + h], sel);
-            q.y = __builtin_amdgcn_perm(v[3 * 2 + h], v[2 * 2 + h], sel);
-            q.z = __builtin_amdgcn_perm(v[5 * 2 + h], v[4 * 2 + h], sel);
-            q.w = __builtin_amdgcn_perm(v[7 * 2 + h], v[6 * 2 + h], sel);
+        for (int i = 0; i < 4; ++i) {
+          if constexpr (BF16) {
+            uint4 q;
+            if constexpr (kRaw) {
+              // element i of rows (l, l+1) -> one packed word: bytes of the
+              // low (i even) or high (i odd) halves of the two source words
+              const uint32_t sel = (i & 1) ? 0x07060302u : 0x05040100u;
+              const int h = b + (i >> 1);
+              q.x = __builtin_amdgcn_perm(v[1 * 2 + h], v[0 * 2 + h], sel);
+              q.y = __builtin_amdgcn_perm(v[3 * 2 + h], v[2 * 2 + h], sel);
+              q.z = __builtin_amdgcn_perm(v[5 * 2 + h], v[4 * 2 + h], sel);
+              q.w = __builtin_amdgcn_perm(v[7 * 2 + h], v[6 * 2 + h], sel);
+            } else {
+              q.x = pack2_bf16(f(b + 0 * 4 + i), f(b + 1 * 4 + i));
+              q.y = pack2_bf16(f(b + 2 * 4 + i), f(b + 3 * 4 + i));
+              q.z = pack2_bf16(f(b + 4 * 4 + i), f(b + 5 * 4 + i));
+              q.w = pack2_bf16(f(b + 6 * 4 + i), f(b + 7 * 4 + i));
+            }
+            *reinterpret_cast<uint4*>(T + bf16_tile_off<PITCH>(r + i, lb)) = q;
           } else {
-            q.x = pack2_bf16(f(0 * 4 + i), f(1 * 4 + i));
-            q.y = pack2_bf16(f(2 * 4 + i), f(3 * 4 + i));
-            q.z = pack2_bf16(f(4 * 4 + i), f(5 * 4 + i));
-            q.w = pack2_bf16(f(6 * 4 + i), f(7 * 4 + i));
-          }
-          *reinterpret_cast<uint4*>(T + bf16_tile_off<PITCH>(r + i, lb)) = q;
-        } else {
-          E* dst = T + (r + i) * PITCH + lb;
+            E* dst = T + (r + i) * PITCH + lb;
 #pragma unroll
-          for (int e = 0; e < UL; ++e) dst[e] = f(e * 4 + i);
+            for (int e = 0; e < UL; ++e) dst[e] = f(b + e * 4 + i);
+          }
         }
       }
     }
   }
 };
 
-// Stores the 2 x 2 accumulator tiles of one wave.  OK: 0 = fp32, 1 = int32
+// Stores the TT x TT accumulator tiles of one wave.  OK: 0 = fp32, 1 = int32
 // (exact integer values), 3 = fp32 accumulate, 4 = fp32 with ReLU.  `full`
 // (block-uniform) skips the bounds checks.  NT: non-temporal stores (0, 1, 4).
-template <int OK, bool NT>
-__device__ __forceinline__ void epilogue(const f32x16_t (&acc)[2][2], char* cbase, int ib, int jb, int rows,
+template <int OK, bool NT, int TT>
+__device__ __forceinline__ void epilogue(const f32x16_t (&acc)[TT][TT], char* cbase, int ib, int jb, int rows,
                                          int cols, long ldc, bool full) {
 #pragma unroll
-  for (int x = 0; x < 2; ++x)
+  for (int x = 0; x < TT; ++x)
 #pragma unroll
-    for (int y = 0; y < 2; ++y)
+    for (int y = 0; y < TT; ++y)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int i = ib + x * 32 + 8 * (r >> 2) + (r & 3);
@@ -408,21 +422,31 @@ constexpr int mix_waves() {
 // kOutNT for non-temporal stores of 0 and 1.
 constexpr int kOutNT = 8;
 
-template <bool BF16, int ADT, bool AKC, bool AMASK, int BDT, bool BKC, bool BMASK>
+// K-step depth.  bf16 storage on both operands, both contiguous along the
+// reduction (BWD_WEIGHT): 128, so that each operand row is read as 256-byte
+// runs; 64-wide tiles take twice the depth of 128-wide ones, which keeps a
+// unit for every thread and halves the K-steps.
+template <bool BF16, int ADT, bool AKC, bool AMASK, int BDT, bool BKC, bool BMASK, int kTile>
+constexpr int mix_depth() {
+  if (kTile == 64) return BF16 ? 128 : 64;
+  if (BF16 && AKC && BKC && !AMASK && !BMASK && ADT == 2 && BDT == 2) return 128;
+  return BF16 ? 64 : 32;
+}
+
+template <bool BF16, int ADT, bool AKC, bool AMASK, int BDT, bool BKC, bool BMASK, int kTile>
 __global__ __launch_bounds__(kMixThreads)
-__attribute__((amdgpu_waves_per_eu(mix_waves<BF16, ADT, AKC, AMASK, BDT, BKC, BMASK>(), 8))) void k_mix_gemm(
+__attribute__((amdgpu_waves_per_eu(kTile == 64 ? 3 : mix_waves<BF16, ADT, AKC, AMASK, BDT, BKC, BMASK>(), 8))) void k_mix_gemm(
     const void* __restrict__ a, const void* __restrict__ b, const float* __restrict__ aux, void* __restrict__ out,
     int rows, int cols, int depth, long lda, long ldb, long ldc, long a_bs, long b_bs, long c_bs,
     int mt, int nt, int zt, int nsplit_p, int pchunk, int out_kind, int relu) {
-  // bf16 storage on both operands, both contiguous along the reduction
-  // (BWD_WEIGHT): 128-deep K-steps, each operand row read as 256-byte runs
-  constexpr int kDeep = (BF16 && AKC && BKC && !AMASK && !BMASK && ADT == 2 && BDT == 2) ? 128 : 0;
-  using SA = Stager<BF16, ADT, AKC, AMASK, kDeep>;
-  using SB = Stager<BF16, BDT, BKC, BMASK, kDeep>;
+  constexpr int kDepth = mix_depth<BF16, ADT, AKC, AMASK, BDT, BKC, BMASK, kTile>();
+  using SA = Stager<BF16, ADT, AKC, AMASK, kTile, kDepth>;
+  using SB = Stager<BF16, BDT, BKC, BMASK, kTile, kDepth>;
   constexpr int BK = SA::BK, PITCH = SA::PITCH;
+  constexpr int TT = kTile / 64, kSub = kTile / 2;  // 32 x 32 tiles and rows per wave, each way
   using E = typename SA::E;
-  __shared__ __align__(16) E As[kBM * PITCH];
-  __shared__ __align__(16) E Bs[kBN * PITCH];
+  __shared__ __align__(16) E As[kTile * PITCH];
+  __shared__ __align__(16) E Bs[kTile * PITCH];
 
   // logical tile id: XCD-contiguous, row tiles fastest (blocks sharing one B
   // tile run together on one XCD)
@@ -459,14 +483,14 @@ __attribute__((amdgpu_waves_per_eu(mix_waves<BF16, ADT, AKC, AMASK, BDT, BKC, BM
   sa.depth = l_end;
   sb.depth = l_end;
 
-  const int i0 = tm * kBM, j0 = tn * kBN;
+  const int i0 = tm * kTile, j0 = tn * kTile;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int wm = wave >> 1, wn = wave & 1;
-  f32x16_t acc[2][2];
+  f32x16_t acc[TT][TT];
 #pragma unroll
-  for (int x = 0; x < 2; ++x)
+  for (int x = 0; x < TT; ++x)
 #pragma unroll
-    for (int y = 0; y < 2; ++y)
+    for (int y = 0; y < TT; ++y)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[x][y][r] = 0.f;
 
@@ -486,31 +510,31 @@ __attribute__((amdgpu_waves_per_eu(mix_waves<BF16, ADT, AKC, AMASK, BDT, BKC, BM
     if constexpr (BF16) {
 #pragma unroll
       for (int kk = 0; kk < BK; kk += 16) {
-        bf16x8_t af[2], bfr[2];
+        bf16x8_t af[TT], bfr[TT];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          af[t] = *reinterpret_cast<const bf16x8_t*>(As + bf16_tile_off<PITCH>(wm * 64 + t * 32 + (lane & 31), kk + 8 * (lane >> 5)));
-          bfr[t] = *reinterpret_cast<const bf16x8_t*>(Bs + bf16_tile_off<PITCH>(wn * 64 + t * 32 + (lane & 31), kk + 8 * (lane >> 5)));
+        for (int t = 0; t < TT; ++t) {
+          af[t] = *reinterpret_cast<const bf16x8_t*>(As + bf16_tile_off<PITCH>(wm * kSub + t * 32 + (lane & 31), kk + 8 * (lane >> 5)));
+          bfr[t] = *reinterpret_cast<const bf16x8_t*>(Bs + bf16_tile_off<PITCH>(wn * kSub + t * 32 + (lane & 31), kk + 8 * (lane >> 5)));
         }
 #pragma unroll
-        for (int x = 0; x < 2; ++x)
+        for (int x = 0; x < TT; ++x)
 #pragma unroll
-          for (int y = 0; y < 2; ++y)
+          for (int y = 0; y < TT; ++y)
             acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[x], bfr[y], acc[x][y], 0, 0, 0);
       }
     } else {
 #pragma unroll
       for (int kk = 0; kk < BK; kk += 2) {
-        float af[2], bfr[2];
+        float af[TT], bfr[TT];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          af[t] = As[(wm * 64 + t * 32 + (lane & 31)) * PITCH + kk + (lane >> 5)];
-          bfr[t] = Bs[(wn * 64 + t * 32 + (lane & 31)) * PITCH + kk + (lane >> 5)];
+        for (int t = 0; t < TT; ++t) {
+          af[t] = As[(wm * kSub + t * 32 + (lane & 31)) * PITCH + kk + (lane >> 5)];
+          bfr[t] = Bs[(wn * kSub + t * 32 + (lane & 31)) * PITCH + kk + (lane >> 5)];
         }
 #pragma unroll
-        for (int x = 0; x < 2; ++x)
+        for (int x = 0; x < TT; ++x)
 #pragma unroll
-          for (int y = 0; y < 2; ++y)
+          for (int y = 0; y < TT; ++y)
             acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[x], bfr[y], acc[x][y], 0, 0, 0);
       }
     }
@@ -525,8 +549,8 @@ __attribute__((amdgpu_waves_per_eu(mix_waves<BF16, ADT, AKC, AMASK, BDT, BKC, BM
   // Epilogue.  Accumulator element r of lane t in a 32 x 32 tile is
   // C[8 * (r / 4) + 4 * (t / 32) + r % 4][t % 32].
   char* cbase = reinterpret_cast<char*>(out) + (size_t)z * c_bs * 4;
-  const bool full = i0 + kBM <= rows && j0 + kBN <= cols;
-  const int ib = i0 + wm * 64 + 4 * (lane >> 5), jb = j0 + wn * 64 + (lane & 31);
+  const bool full = i0 + kTile <= rows && j0 + kTile <= cols;
+  const int ib = i0 + wm * kSub + 4 * (lane >> 5), jb = j0 + wn * kSub + (lane & 31);
   switch (out_kind) {
     case 1: epilogue<1, false>(acc, cbase, ib, jb, rows, cols, ldc, full); break;
     case 1 | kOutNT: epilogue<1, true>(acc, cbase, ib, jb, rows, cols, ldc, full); break;
@@ -606,7 +630,6 @@ __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(3, 
   // grad[n][m][p0 + j] -> Bs[j * pitch + m]: units of 8 m x 4 p, transposed
   // in registers so each LDS write is 16 contiguous bytes of one row.
   {
-    const bool vec = (P & 3) == 0;
     const char* gb = reinterpret_cast<const char*>(g) + (size_t)n * plane * StoreBytes<BDT>::v;
     const float* mb = BMASK ? aux + (size_t)n * plane : nullptr;
     const int units = (msteps * 16 / 8) * (kStripP / 4);
@@ -620,8 +643,11 @@ __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(3, 
         const int avail = m < M ? max(0, min(4, P - pp)) : 0;
         const size_t idx = avail > 0 ? (size_t)m * P + pp : 0;
         uint32_t raw[4], mk[4] = {0u, 0u, 0u, 0u};
-        ld_run<BDT, 4>(gb, idx, vec && avail == 4, avail, raw);
-        if constexpr (BMASK) ld_run<1, 4>(reinterpret_cast<const char*>(mb), idx, vec && avail == 4, avail, mk);
+        // columns past P are not stored, so only the image's last elements
+        // need the narrow loads (any P: the wide ones may be unaligned)
+        const bool wide = avail > 0 && idx + 4 <= plane;
+        ld_run<BDT, 4>(gb, idx, wide, avail, raw);
+        if constexpr (BMASK) ld_run<1, 4>(reinterpret_cast<const char*>(mb), idx, wide, avail, mk);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           if constexpr (BDT == 2 && !BMASK) v[e][i] = raw[i] & 0xffffu;
@@ -816,14 +842,59 @@ __global__ void k_mix_reduce4(const float4* __restrict__ part, int S, size_t n4,
   out[i] = s;
 }
 
+// The same for few outputs of many partials, where a thread per output leaves
+// the chip idle (48 x 128 outputs of 512 partials: 6 blocks, 27 us): a block
+// takes 16 outputs, 16 threads each summing every 16th partial, combined in a
+// fixed order.
+constexpr size_t kReduceFew = 65536;
+__global__ __launch_bounds__(256) void k_mix_reduce_few(const float4* __restrict__ part, int S, size_t n4,
+                                                        float4* __restrict__ out, int accumulate) {
+  __shared__ float4 red[16][16];
+  const int j = threadIdx.x & 15, g = threadIdx.x >> 4;
+  const size_t i = (size_t)blockIdx.x * 16 + j;
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (i < n4) {
+#pragma unroll 4
+    for (int k = g; k < S; k += 16) {
+      const float4 p = part[(size_t)k * n4 + i];
+      s.x += p.x; s.y += p.y; s.z += p.z; s.w += p.w;
+    }
+  }
+  red[g][j] = s;
+  __syncthreads();
+  if (g == 0 && i < n4) {
+    float4 t = accumulate ? out[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const float4 p = red[k][j];
+      t.x += p.x; t.y += p.y; t.z += p.z; t.w += p.w;
+    }
+    out[i] = t;
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
-struct WeightSplit { int sp, chunk, S; };
+// Tile side of a GEMM of rows x cols outputs over zt images (or splits): 64
+// where 128-wide tiles would leave CUs without a block or spend a third of
+// their rows on padding.
+#ifndef MIXB
+#define MIXB 512
+#endif
+static int mix_tile(int rows, int cols, long zt) {
+  const long t128 = (long)((rows + 127) / 128) * ((cols + 127) / 128);
+  const long t64 = (long)((rows + 63) / 64) * ((cols + 63) / 64);
+  if (t128 * zt < MIXB) return 64;
+  return 3 * t64 <= 8 * t128 ? 64 : 128;  // a third or more of the area is padding
+}
+
+struct WeightSplit { int tile, sp, chunk, S; };
 
 static WeightSplit weight_split(int N, int M, int K, int P, bool bf16) {
   const int BK = bf16 ? 64 : 32;
-  const long tiles = (long)((M + kBM - 1) / kBM) * ((K + kBN - 1) / kBN);
+  const int tile = 3L * ((M + 63) / 64) * ((K + 63) / 64) <= 8L * ((M + 127) / 128) * ((K + 127) / 128) ? 64 : 128;
+  const long tiles = (long)((M + tile - 1) / tile) * ((K + tile - 1) / tile);
   const int max_sp = (P + BK - 1) / BK;
   int sp = (int)std::min<long>(512, (512 + tiles * N - 1) / (tiles * N));
   if (sp < 1) sp = 1;
@@ -831,7 +902,7 @@ static WeightSplit weight_split(int N, int M, int K, int P, bool bf16) {
   int chunk = (P + sp - 1) / sp;
   chunk = ((chunk + BK - 1) / BK) * BK;
   sp = (P + chunk - 1) / chunk;
-  return {sp, chunk, N * sp};
+  return {tile, sp, chunk, N * sp};
 }
 
 size_t mix_workspace_bytes(int mode, int N, int M, int K, int P, int compute_dt) {
@@ -843,15 +914,19 @@ size_t mix_workspace_bytes(int mode, int N, int M, int K, int P, int compute_dt)
 }
 
 template <bool BF16, int ADT, bool AKC, bool AMASK, int BDT, bool BKC, bool BMASK>
-static void gemm_launch(const void* a, const void* b, const float* aux, void* out, int rows, int cols, int depth,
-                        long lda, long ldb, long ldc, long a_bs, long b_bs, long c_bs, int zt, int nsplit_p,
-                        int pchunk, int out_kind, int relu, hipStream_t s) {
-  const int mt = (rows + kBM - 1) / kBM, nt = (cols + kBN - 1) / kBN;
+static void gemm_launch(int tile, const void* a, const void* b, const float* aux, void* out, int rows, int cols,
+                        int depth, long lda, long ldb, long ldc, long a_bs, long b_bs, long c_bs, int zt,
+                        int nsplit_p, int pchunk, int out_kind, int relu, hipStream_t s) {
+  const int mt = (rows + tile - 1) / tile, nt = (cols + tile - 1) / tile;
   const int total = mt * nt * zt;
   const int grid = (total + 7) & ~7;
-  hipLaunchKernelGGL((k_mix_gemm<BF16, ADT, AKC, AMASK, BDT, BKC, BMASK>), dim3(grid), dim3(kMixThreads), 0, s,
-                     a, b, aux, out, rows, cols, depth, lda, ldb, ldc, a_bs, b_bs, c_bs, mt, nt, zt, nsplit_p,
-                     pchunk, out_kind, relu);
+  auto go = [&](auto kt) {
+    hipLaunchKernelGGL((k_mix_gemm<BF16, ADT, AKC, AMASK, BDT, BKC, BMASK, decltype(kt)::value>), dim3(grid),
+                       dim3(kMixThreads), 0, s, a, b, aux, out, rows, cols, depth, lda, ldb, ldc, a_bs, b_bs, c_bs, mt,
+                       nt, zt, nsplit_p, pchunk, out_kind, relu);
+  };
+  if (tile == 64) go(std::integral_constant<int, 64>{});
+  else go(std::integral_constant<int, 128>{});
 }
 
 // Stored operand dtypes instantiated per compute type: bf16 compute reads
@@ -889,7 +964,7 @@ static hipError_t launch_mix_t(int mode, const void* a, int a_dt, const void* b,
     with_dt<BF16>(a_dt, [&](auto ad) {
       with_dt<BF16>(b_dt, [&](auto bd) {
         gemm_launch<BF16, decltype(ad)::value, true, false, decltype(bd)::value, false, false>(
-            a, b, nullptr, out, M, P, K, K, P, P, 0, (long)K * P, (long)M * P, N, 0, 0, ok_fwd, relu, s);
+            mix_tile(M, P, N), a, b, nullptr, out, M, P, K, K, P, P, 0, (long)K * P, (long)M * P, N, 0, 0, ok_fwd, relu, s);
       });
     });
     return hipGetLastError();
@@ -921,10 +996,10 @@ static hipError_t launch_mix_t(int mode, const void* a, int a_dt, const void* b,
       with_dt<BF16>(b_dt, [&](auto bd) {
         if (relu)
           gemm_launch<BF16, decltype(ad)::value, false, false, decltype(bd)::value, false, true>(
-              a, b, aux, out, K, P, M, K, P, P, 0, (long)M * P, (long)K * P, N, 0, 0, ok_bwd_data, 0, s);
+              mix_tile(K, P, N), a, b, aux, out, K, P, M, K, P, P, 0, (long)M * P, (long)K * P, N, 0, 0, ok_bwd_data, 0, s);
         else
           gemm_launch<BF16, decltype(ad)::value, false, false, decltype(bd)::value, false, false>(
-              a, b, nullptr, out, K, P, M, K, P, P, 0, (long)M * P, (long)K * P, N, 0, 0, ok_bwd_data, 0, s);
+              mix_tile(K, P, N), a, b, nullptr, out, K, P, M, K, P, P, 0, (long)M * P, (long)K * P, N, 0, 0, ok_bwd_data, 0, s);
       });
     });
     return hipGetLastError();
@@ -940,18 +1015,22 @@ static hipError_t launch_mix_t(int mode, const void* a, int a_dt, const void* b,
     with_dt<BF16>(b_dt, [&](auto bd) {
       if (relu)
         gemm_launch<BF16, decltype(ad)::value, true, true, decltype(bd)::value, true, false>(
-            a, b, aux, dst, M, K, P, P, P, K, (long)M * P, (long)K * P, direct ? 0 : (long)M * K, sp.S, sp.sp,
+            sp.tile, a, b, aux, dst, M, K, P, P, P, K, (long)M * P, (long)K * P, direct ? 0 : (long)M * K, sp.S, sp.sp,
             sp.chunk, ok, 0, s);
       else
         gemm_launch<BF16, decltype(ad)::value, true, false, decltype(bd)::value, true, false>(
-            a, b, nullptr, dst, M, K, P, P, P, K, (long)M * P, (long)K * P, direct ? 0 : (long)M * K, sp.S, sp.sp,
+            sp.tile, a, b, nullptr, dst, M, K, P, P, P, K, (long)M * P, (long)K * P, direct ? 0 : (long)M * K, sp.S, sp.sp,
             sp.chunk, ok, 0, s);
     });
   });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || direct) return e;
   const size_t n = (size_t)M * K;
-  if ((n & 3) == 0 && ((uintptr_t)out & 15) == 0) {
+  if ((n & 3) == 0 && ((uintptr_t)out & 15) == 0 && n / 4 < kReduceFew && sp.S >= 64) {
+    const size_t n4 = n / 4;
+    hipLaunchKernelGGL(k_mix_reduce_few, dim3((unsigned)((n4 + 15) / 16)), dim3(256), 0, s, (const float4*)ws, sp.S,
+                       n4, (float4*)out, accumulate);
+  } else if ((n & 3) == 0 && ((uintptr_t)out & 15) == 0) {
     const size_t n4 = n / 4;
     hipLaunchKernelGGL(k_mix_reduce4, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, (const float4*)ws, sp.S,
                        n4, (float4*)out, accumulate);
