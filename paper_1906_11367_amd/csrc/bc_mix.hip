@@ -961,6 +961,10 @@ static hipError_t launch_mix_t(int mode, const void* a, int a_dt, const void* b,
   const int ok_bwd_data = out_kind_plain | (kNtBwdData ? kOutNT : 0);
   if (mode == 0) {
     // C = out[n] (M x P): A = w (row-major M x K), B(l=k, j=p) = in[n][k][p]
+    if constexpr (BF16) {
+      if (a_dt == 2 && b_dt == 2 && out_dt == 1 && mix_fwd_pipe_takes(a, b, N, M, K, P))
+        return launch_mix_fwd_pipe(a, b, (float*)out, N, M, K, P, relu, s);
+    }
     with_dt<BF16>(a_dt, [&](auto ad) {
       with_dt<BF16>(b_dt, [&](auto bd) {
         gemm_launch<BF16, decltype(ad)::value, true, false, decltype(bd)::value, false, false>(
@@ -1011,7 +1015,15 @@ static hipError_t launch_mix_t(int mode, const void* a, int a_dt, const void* b,
   const bool direct = sp.S == 1;
   void* dst = direct ? out : ws;
   const int ok = direct ? (accumulate ? 3 : 0) : 2;
-  with_dt<BF16>(a_dt, [&](auto ad) {
+  bool piped = false;
+  if constexpr (BF16) {
+    if (a_dt == 2 && b_dt == 2 && !relu && !direct && mix_wgrad_pipe_takes(a, b, N, M, K, P)) {
+      const hipError_t e = launch_mix_wgrad_pipe(a, b, (float*)ws, N, M, K, P, sp.sp, sp.chunk, s);
+      if (e != hipSuccess) return e;
+      piped = true;
+    }
+  }
+  if (!piped) with_dt<BF16>(a_dt, [&](auto ad) {
     with_dt<BF16>(b_dt, [&](auto bd) {
       if (relu)
         gemm_launch<BF16, decltype(ad)::value, true, true, decltype(bd)::value, true, false>(
