@@ -1,0 +1,211 @@
+"""GPU parity at the edges of the kernels' tiles and dispatch rules.
+
+Small shapes where a new item, table or tile ends: widths and heights around
+the item sizes and the compiled table pitches, maps of several bands, operands
+with rows of no alignment, tiles cut by both output sizes, reductions that end
+inside a step.  References are the CPU oracle's; the bars are the repository's
+fp32 bar (1e-4 of |r| + rms), for bf16 operands too, since both sides then sum
+the same rounded operands in fp32 (at most 1024 terms: below 1e-6).
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_1906_11367_amd import boxconv as bc
+from test_gpu_parity import RTOL_F32, check, dev, host, real_boxes, say
+
+pytestmark = pytest.mark.gpu
+
+
+def case(seed, N, C, H, W, B, stride=1):
+    rng = np.random.default_rng(seed)
+    x = rng.standard_normal((N, C, H, W)).astype(np.float32)
+    bx = real_boxes(rng, C, B, min(H, W) / 4, 0.3, max(1.0, min(H, W) / 2))
+    Ho, Wo = (H + stride - 1) // stride, (W + stride - 1) // stride
+    g = rng.standard_normal((N, C * B, Ho, Wo)).astype(np.float32)
+    return x, bx, g
+
+
+# Widths around the items (3 and 6 columns) and the compiled pitches (48, 64,
+# 96 columns; lanes end at 64), heights around the segments (4, 8, 10, 13 rows)
+# and the bands (16 and 32 rows per wave, several strips for narrow tall maps).
+SHAPES = [(5, 7), (7, 6), (8, 2), (8, 3), (9, 47), (10, 48), (13, 49), (16, 61), (17, 62), (33, 63), (64, 64), (31, 65),
+          (40, 95), (65, 96), (12, 97), (100, 17), (130, 31), (128, 48)]
+
+
+@pytest.mark.parametrize("H,W", SHAPES)
+@pytest.mark.parametrize("B", [1, 5])
+def test_lds_box_edges(H, W, B):
+    N, C = 2, 3
+    say(f"edges {H}x{W} B={B}")
+    x, bx, g = case(H * 100 + W, N, C, H, W, B)
+    xd, bd, gd = dev(x), dev(bx), dev(g)
+    ref = O.box_forward(x, bx)
+    y = torch.empty((N, C * B, H, W), device="cuda")
+    check(host(bc.box_conv_fwd(xd, bd, y)), ref, RTOL_F32, "y")
+    # the bf16 output is this fp32 output rounded, whatever the width's stores
+    yb = torch.empty_like(y, dtype=torch.bfloat16)
+    assert torch.equal(bc.box_conv_fwd(xd, bd, yb), y.to(torch.bfloat16))
+    dx, db = torch.empty_like(xd), torch.empty((C, B, 4), device="cuda")
+    bc.box_conv_bwd(xd, bd, gd, dx, db)
+    check(host(dx), O.box_backward_input(g, bx, H, W), RTOL_F32, "dx")
+    check(host(db), O.box_backward_params(x, g, bx), RTOL_F32, "dboxes")
+    xr = torch.relu(xd)
+    dxb = torch.empty_like(xd, dtype=torch.bfloat16)
+    bc.box_conv_bwd_relu_bf16(xr, bd, gd, dxb, db)
+    assert torch.equal(dxb, torch.where(xr > 0, dx, torch.zeros_like(dx)).to(torch.bfloat16))
+    check(host(db), O.box_backward_params(np.maximum(x, 0), g, bx), RTOL_F32, "dboxes of rectified maps")
+    bc.box_conv_bwd(xd, bd, gd, dx, None, bc.BC_FLAG_INTEGER_CORNERS)
+    check(host(dx), O.box_backward_input(g, bx, H, W, integer_corners=True), RTOL_F32, "dx, integer corners")
+
+
+@pytest.mark.parametrize("H,W", [(9, 47), (16, 61), (17, 62), (33, 63), (64, 64), (31, 65), (40, 95)])
+def test_lds_box_edges_many_maps(H, W):
+    """Enough maps for the 8-row items (2048 waves of them)."""
+    N, C, B = 16, 128, 2
+    x, bx, g = case(H + W, N, C, H, W, B)
+    dx, db = torch.empty((N, C, H, W), device="cuda"), torch.empty((C, B, 4), device="cuda")
+    say(f"many maps {H}x{W}")
+    bc.box_conv_bwd(dev(x), dev(bx), dev(g), dx, db)
+    check(host(dx), O.box_backward_input(g, bx, H, W), RTOL_F32, "dx")
+    check(host(db), O.box_backward_params(x, g, bx), RTOL_F32, "dboxes")
+
+
+@pytest.mark.parametrize("stride", [2, 3])
+@pytest.mark.parametrize("H,W", [(8, 3), (9, 47), (13, 48), (33, 63), (64, 64), (31, 65), (41, 95), (70, 17)])
+def test_strided_edges(H, W, stride):
+    """Stride 2 tabulates only the rows that differ; odd sizes end on either
+    half of a pair."""
+    N, C, B = 2, 3, 2
+    say(f"stride {stride} {H}x{W}")
+    x, bx, g = case(H * 7 + W, N, C, H, W, B, stride)
+    xd, bd, gd = dev(x), dev(bx), dev(g)
+    y = torch.empty(tuple(g.shape), device="cuda")
+    check(host(bc.box_conv_fwd(xd, bd, y, stride=stride)), O.box_forward(x, bx, stride=stride), RTOL_F32, "y")
+    dx, db = torch.empty_like(xd), torch.empty((C, B, 4), device="cuda")
+    bc.box_conv_bwd(xd, bd, gd, dx, db, stride=stride)
+    up = np.zeros((N, C * B, H, W), dtype=np.float32)
+    up[:, :, ::stride, ::stride] = g
+    check(host(dx), O.box_backward_input(up, bx, H, W), RTOL_F32, "dx")
+    check(host(db), O.box_backward_params(x, up, bx), RTOL_F32, "dboxes")
+    bc.box_conv_bwd(xd, bd, gd, dx, None, bc.BC_FLAG_INTEGER_CORNERS, stride=stride)
+    check(host(dx), O.box_backward_input(up, bx, H, W, integer_corners=True), RTOL_F32, "dx, integer corners")
+
+
+@pytest.mark.parametrize("mode", ["2x", "2y", "4"])
+@pytest.mark.parametrize("H,W", [(8, 2), (9, 47), (16, 49), (33, 63), (31, 65), (65, 96)])
+def test_split_edges(H, W, mode):
+    N, C, B = 2, 3, 2
+    say(f"split {mode} {H}x{W}")
+    x, bx, g = case(H * 3 + W, N, C, H, W, B)
+    pieces = 4 if mode == "4" else 2
+    pw = np.random.default_rng(5).uniform(-1, 1, (C, B, pieces)).astype(np.float32)
+    xd, bd, wd, gd = dev(x), dev(bx), dev(pw), dev(g)
+    y = torch.empty(tuple(g.shape), device="cuda")
+    check(host(bc.box_conv_split_fwd(xd, bd, wd, mode, y)), O.box_forward_split(x, bx, pw, mode), RTOL_F32, "y")
+    dx, db, dw = torch.empty_like(xd), torch.empty((C, B, 4), device="cuda"), torch.empty_like(wd)
+    bc.box_conv_split_bwd(xd, bd, wd, mode, gd, dx, db, dw)
+    rb, rw = O.box_backward_split_params(x, g, bx, pw, mode)
+    check(host(dx), O.box_backward_split_input(g, bx, pw, mode, H, W), RTOL_F32, "dx")
+    check(host(db), rb, RTOL_F32, "dboxes")
+    check(host(dw), rw, RTOL_F32, "dpieces")
+
+
+@pytest.mark.parametrize("H,W,stride", [(40, 257, 1), (100, 300, 1), (16, 300, 1), (50, 300, 2)])
+def test_wide_maps_in_bands(H, W, stride):
+    """Few maps wider than 256: tables divided into row bands; and in place
+    (the gradient written over the input), where they are not."""
+    N, C, B = 1, 3, 2
+    say(f"wide {H}x{W} stride {stride}")
+    x, bx, g = case(H + W, N, C, H, W, B, stride)
+    xd, bd, gd = dev(x), dev(bx), dev(g)
+    ref = O.box_forward(x, bx, stride=stride)
+    y = torch.empty(tuple(g.shape), device="cuda")
+    for flags in (0, bc.BC_FLAG_MEAN_OFFSET):
+        check(host(bc.box_conv_fwd(xd, bd, y, flags, stride=stride)), ref, RTOL_F32, f"y flags={flags}")
+    up = np.zeros((N, C * B, H, W), dtype=np.float32)
+    up[:, :, ::stride, ::stride] = g
+    rx, rb = O.box_backward_input(up, bx, H, W), O.box_backward_params(x, up, bx)
+    dx, db = torch.empty_like(xd), torch.empty((C, B, 4), device="cuda")
+    bc.box_conv_bwd(xd, bd, gd, dx, db, stride=stride)
+    check(host(dx), rx, RTOL_F32, "dx")
+    check(host(db), rb, RTOL_F32, "dboxes")
+    bc.box_conv_bwd(xd, bd, gd, None, db, stride=stride)
+    check(host(db), rb, RTOL_F32, "dboxes alone")
+    inplace = xd.clone()
+    bc.box_conv_bwd(inplace, bd, gd, inplace, db, stride=stride)
+    check(host(inplace), rx, RTOL_F32, "dx in place")
+    check(host(db), rb, RTOL_F32, "dboxes in place")
+    if stride == 1:
+        xi = dev(np.random.default_rng(3).integers(-8, 9, (N, C, H, W)).astype(np.int32))
+        bi = bx.copy()
+        bi[..., :2], bi[..., 2:] = np.floor(bi[..., :2]), np.floor(bi[..., 2:]) + 0.5
+        yi = torch.empty((N, C * B, H, W), dtype=torch.int32, device="cuda")
+        bc.box_conv_fwd(xi, dev(bi), yi)
+        np.testing.assert_array_equal(yi.cpu().numpy(), O.box_forward(xi.cpu().numpy(), bi))
+
+
+# (N, M, K, P): 64-wide tiles with ragged rows, columns and reductions; odd
+# rows (2-byte aligned bf16); the pipelined forward (M > 64, K % 64 == 0, P % 8
+# == 0, 192 tiles or more) with one and several row tiles, ragged in both
+# sizes, more tiles than blocks; the pipelined weight gradient (M > 128, P % 64
+# == 0) with ragged rows and columns; few outputs of many partials.
+MIX = [(1, 65, 63, 129), (2, 72, 480, 243), (3, 33, 70, 1001), (1, 200, 97, 515), (2, 129, 130, 127),
+       (24, 256, 64, 1032), (24, 136, 128, 1000), (9, 300, 128, 1544), (49, 100, 64, 1000), (40, 130, 192, 1032),
+       (32, 200, 136, 4096), (16, 300, 260, 2048), (2, 48, 128, 30000)]
+
+
+@pytest.mark.parametrize("dims", MIX)
+@pytest.mark.parametrize("compute", ["f32", "bf16"])
+def test_mix_edges(dims, compute):
+    N, M, K, P = dims
+    say(f"mix {dims} {compute}")
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    dt, ct = (torch.bfloat16, bc.BC_BF16) if compute == "bf16" else (torch.float32, bc.BC_F32)
+    w = (torch.randn(M, K, generator=gen, device="cuda") / K ** 0.5).to(dt)
+    o = torch.randn(N, K, P, generator=gen, device="cuda").to(dt)
+    gz = torch.randn(N, M, P, generator=gen, device="cuda").to(dt)
+    ref = np.matmul(host(w.float())[None].astype(np.float64), host(o.float()).astype(np.float64))
+    z = torch.empty(N, M, P, device="cuda")
+    for relu in (0, 1):
+        z.fill_(float("nan"))
+        bc.pointwise_mix(bc.BC_MIX_FWD, w, o, z, N, M, K, P, ct, relu=relu)
+        check(host(z), np.maximum(ref, 0) if relu else ref, RTOL_F32, f"Z relu={relu}")
+    do = torch.full((N, K, P), float("nan"), device="cuda")
+    bc.pointwise_mix(bc.BC_MIX_BWD_DATA, w, gz, do, N, M, K, P, ct)
+    check(host(do), np.matmul(host(w.float()).T[None].astype(np.float64), host(gz.float()).astype(np.float64)), RTOL_F32, "dO")
+    dw = torch.full((M, K), float("nan"), device="cuda")
+    bc.pointwise_mix(bc.BC_MIX_BWD_WEIGHT, gz, o, dw, N, M, K, P, ct)
+    refw = sum(host(gz[n].float()).astype(np.float64) @ host(o[n].float()).astype(np.float64).T for n in range(N))
+    check(host(dw), refw, RTOL_F32, "dW")
+
+
+@pytest.mark.parametrize("dims", [(2, 72, 97, 243), (24, 200, 64, 1032), (2, 140, 130, 640)])
+def test_mix_keeps_a_nan_in_its_place(dims):
+    """A NaN in one row of an operand, next to a tile's or a row's end, reaches
+    the outputs that row has part in and no other."""
+    N, M, K, P = dims
+    w, o, gz = (torch.ones(s, device="cuda", dtype=torch.bfloat16) for s in [(M, K), (N, K, P), (N, M, P)])
+    z, do, dw = torch.empty(N, M, P, device="cuda"), torch.empty(N, K, P, device="cuda"), torch.empty(M, K, device="cuda")
+
+    def mix(mode, a, b, out):
+        bc.pointwise_mix(mode, a, b, out, N, M, K, P, bc.BC_BF16)
+        return torch.isnan(out)
+
+    bad = w.clone()
+    bad[1, 0] = float("nan")          # the value after row 0's last
+    hit = mix(bc.BC_MIX_FWD, bad, o, z)
+    assert hit[:, 1].all() and int(hit.sum()) == N * P
+    hit = mix(bc.BC_MIX_BWD_DATA, bad, gz, do)
+    assert hit[:, 0].all() and int(hit.sum()) == N * P
+    bad = o.clone()
+    bad[0, 1, 0] = float("nan")
+    hit = mix(bc.BC_MIX_FWD, w, bad, z)
+    assert hit[0, :, 0].all() and int(hit.sum()) == M
+    hit = mix(bc.BC_MIX_BWD_WEIGHT, gz, bad, dw)
+    assert hit[:, 1].all() and int(hit.sum()) == M
+    bad = gz.clone()
+    bad[0, 1, 0] = float("nan")
+    hit = mix(bc.BC_MIX_BWD_WEIGHT, bad, o, dw)
+    assert hit[1].all() and int(hit.sum()) == K
