@@ -50,24 +50,24 @@ template <typename T> struct Vec4;
 template <> struct Vec4<float> { using type = float4; };
 template <> struct Vec4<int> { using type = int4; };
 
-// Zero row 0 and columns -kPad..0 of every row of a padded LDS table.
-template <typename T>
+// Zero row 0 and columns -PAD..0 of every row of a padded LDS table.
+template <int PAD = kPad, typename T>
 __device__ __forceinline__ void table_zero_edges(T* S, int H, int pitch) {
   const int tid = threadIdx.x, nt = blockDim.x;
   for (int v = tid; v < pitch; v += nt) S[v] = (T)0;
-  for (int k = tid; k < H * (kPad + 1); k += nt) {
-    const int u = 1 + k / (kPad + 1);
-    S[u * pitch + k - (u - 1) * (kPad + 1)] = (T)0;
+  for (int k = tid; k < H * (PAD + 1); k += nt) {
+    const int u = 1 + k / (PAD + 1);
+    S[u * pitch + k - (u - 1) * (PAD + 1)] = (T)0;
   }
 }
 
 // Row pass of a padded LDS table whose interior holds column prefix sums:
 // lanes own rows, reading kScan elements ahead before writing, so that a
 // lane's LDS reads overlap; also fills the right padding.
-template <typename T>
+template <int PAD = kPad, typename T>
 __device__ __forceinline__ void table_row_pass(T* S, int H, int W, int pitch) {
   constexpr int kScan = 16;
-  T* R = S + kPad;
+  T* R = S + PAD;
   for (int u = threadIdx.x + 1; u <= H; u += blockDim.x) {
     T* row = R + u * pitch;
     T run = (T)0;
@@ -87,7 +87,7 @@ __device__ __forceinline__ void table_row_pass(T* S, int H, int W, int pitch) {
       row[v] = run;
     }
 #pragma unroll
-    for (int k = 1; k <= kPad; ++k) row[W + k] = run;
+    for (int k = 1; k <= PAD; ++k) row[W + k] = run;
   }
 }
 
@@ -248,7 +248,7 @@ __device__ void build_table_lds(const T* __restrict__ src, T* S, int H, int W, i
 // arithmetic first (box backward, 64x48 maps: 143 us staged, 146 scanned
 // across lanes, 126 this way; 64x64: 128 and 98).  Row 0 and the left padding
 // stay zero (table_zero_edges, once per block).
-template <typename T, int RPW, int CPL>
+template <typename T, int RPW, int CPL, int PAD = kPad>
 struct BandTable {
   T r[RPW][CPL];
 
@@ -305,7 +305,7 @@ struct BandTable {
 #pragma unroll
       for (int i = 0; i < RPW; ++i) r[i][k] += above;
     }
-    T* row = S + kPad + 1 + lane * kStep + (row0 + 1) * pitch;
+    T* row = S + PAD + 1 + lane * kStep + (row0 + 1) * pitch;
 #pragma unroll
     for (int k = 0; k < CPL; ++k) {
       if (lane + 64 * k < W) {
@@ -327,7 +327,7 @@ struct BandTable {
 // reached the first strip's barrier; the table is complete after the last.
 // kHalf: the table is that of the map zero-upsampled by two (HalfRowTable):
 // W_up columns, each column's sums at twice its place.
-template <typename T, int RPW, int CPL, bool kHalf = false>
+template <typename T, int RPW, int CPL, bool kHalf = false, int PAD = kPad>
 __device__ __forceinline__ void build_table_bands(const T* __restrict__ src, T* S, T* part, int H, int W, int pitch,
                                                   float mu, bool sub, int W_up = 0) {
   const int nw = blockDim.x >> 6, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -336,7 +336,7 @@ __device__ __forceinline__ void build_table_bands(const T* __restrict__ src, T* 
   for (int k = 0; k < CPL; ++k) carry[k] = (T)0;
   int buf = 0;
   for (int r0 = 0; r0 < H; r0 += nw * RPW) {
-    BandTable<T, RPW, CPL> band;
+    BandTable<T, RPW, CPL, PAD> band;
     const int row0 = r0 + wave * RPW;
     T* pt = part + buf * nw * 64 * CPL;
     band.load(src, H, W, row0);
@@ -347,7 +347,7 @@ __device__ __forceinline__ void build_table_bands(const T* __restrict__ src, T* 
   }
   __syncthreads();
   if constexpr (kHalf) table_row_pass_up2(S, H, W, W_up, pitch);
-  else table_row_pass(S, H, W, pitch);
+  else table_row_pass<PAD>(S, H, W, pitch);
   __syncthreads();
 }
 
@@ -388,30 +388,30 @@ __device__ inline void build_table_lds_up(const float* __restrict__ src, float* 
 // Walks with compile-time segment length (registers indexed statically)
 // ---------------------------------------------------------------------------
 
-// The columns of a Q-column item (Q a multiple of kQ) as Q / kQ groups of
-// kQ, each with its own clamped run start: the LDS table's padding (kPad = 3
-// columns a side) covers runs of kQ + 1 words only, so a wider item reads
-// its runs group by group.
+// The columns of a Q-column item as groups of Src::kRun, each with its own
+// clamped run start: an LDS table's padding (PAD columns a side) covers runs
+// of PAD + 1 words only, so a wider item reads its runs group by group.
 template <int Q, typename Src>
 struct ColGroups {
-  static_assert(Q % kQ == 0, "items are whole groups of kQ columns");
-  static constexpr int NG = Q / kQ;
+  static constexpr int G = Q < Src::kRun ? Q : Src::kRun;
+  static_assert(Q % G == 0, "items are whole groups of columns");
+  static constexpr int NG = Q / G;
   typename Src::Cols c[NG];
   __device__ __forceinline__ ColGroups(const Src& S, int ba, int bb) {
 #pragma unroll
-    for (int g = 0; g < NG; ++g) c[g] = S.cols(ba + g * kQ, bb + g * kQ);
+    for (int g = 0; g < NG; ++g) c[g] = S.cols(ba + g * G, bb + g * G);
   }
   // x-interpolated row (table_row) for all Q columns
   template <typename T>
   __device__ __forceinline__ void row(const Src& S, int coord, const Taps<T>& tp, T* U) const {
 #pragma unroll
-    for (int g = 0; g < NG; ++g) table_row(S, coord, c[g], tp, U + g * kQ);
+    for (int g = 0; g < NG; ++g) table_row<G>(S, coord, c[g], tp, U + g * G);
   }
-  // the kQ-word runs at both x edges, for all Q columns
+  // the G-word runs at both x edges, for all Q columns
   template <typename T>
   __device__ __forceinline__ void runs(const Src& S, int coord, T* sa, T* sb) const {
 #pragma unroll
-    for (int g = 0; g < NG; ++g) S.template runs<kQ>(coord, c[g], sa + g * kQ, sb + g * kQ);
+    for (int g = 0; g < NG; ++g) S.template runs<G>(coord, c[g], sa + g * G, sb + g * G);
   }
 };
 
@@ -879,6 +879,7 @@ constexpr int kFwdThreads = 512;
 // pitch: 55 and 71 serve maps up to 64 wide, 103 up to 96.
 constexpr int band_cols(int pitch) { return pitch <= 71 ? 1 : 2; }
 // LDS of a table and of the band totals its builder exchanges.
+// (The 6-column forward items' tables are 6 wider, see kFwdPad.)
 inline size_t table_lds_bytes(int rows, int W, int pitch_class, int threads) {
   if (pitch_class == 0) return (size_t)(rows + 1) * lds_pitch(W) * 4;
   return ((size_t)(rows + 1) * pitch_class + 2 * threads * band_cols(pitch_class)) * 4;

@@ -4,13 +4,18 @@
 
 namespace bc {
 
+// Padding of the forward's tables of compiled pitch: a 6-column item then
+// reads each of its runs as 7 words from one clamped address instead of two
+// runs of 4.
+constexpr int kFwdPad = 6;
+
 // Forward on a map's table in LDS, for the boxes b0 .. b0+nb-1 of channel c.
 // Items of one box are (row segment, column chunk), chunk fastest so that
 // adjacent lanes write adjacent columns; each box's items are padded to a
 // multiple of 64 (per_box_p) so that a wave works on one box and reads its
 // taps through scalar loads.
-template <typename T, typename OutT, int SEG, bool kOffset, bool kInt, int Q, int kPack, bool kTail>
-__device__ __forceinline__ void fwd_boxes(const LdsTable<T>& tab, const int* __restrict__ taps,
+template <typename T, typename OutT, int SEG, bool kOffset, bool kInt, int Q, int kPack, bool kTail, typename Src>
+__device__ __forceinline__ void fwd_boxes(const Src& tab, const int* __restrict__ taps,
                                           OutT* __restrict__ y, int map, int c, int b0, int nb, int H, int W,
                                           int B, int per_box_p, float mu) {
   const int nch = (W + Q - 1) / Q, nseg = (H + SEG - 1) / SEG, per_box = nch * nseg;
@@ -38,20 +43,21 @@ __global__ __launch_bounds__(kFwdThreads) void k_box_fwd_lds(const T* __restrict
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T* S = reinterpret_cast<T*>(smem_raw);
   __shared__ float red[16];
-  const int pitch = kPitch > 0 ? kPitch : lds_pitch_dev(W);
+  constexpr int PAD = kPitch > 0 ? kFwdPad : kPad;
+  const int pitch = kPitch > 0 ? kPitch + 2 * (PAD - kPad) : lds_pitch_dev(W);
   const int ngrp = (B + bpg - 1) / bpg;
   const int map = blockIdx.x / ngrp, grp = blockIdx.x - map * ngrp;
   const T* src = x + (size_t)map * H * W;
   float mu = 0.f;
   if (kOffset) mu = block_mean(reinterpret_cast<const float*>(src), H * W, red);
   if constexpr (kPitch > 0) {
-    table_zero_edges(S, H, pitch);
-    build_table_bands<T, 16, band_cols(kPitch)>(src, S, S + (H + 1) * pitch, H, W, pitch, mu, kOffset);
+    table_zero_edges<PAD>(S, H, pitch);
+    build_table_bands<T, 16, band_cols(kPitch), false, PAD>(src, S, S + (H + 1) * pitch, H, W, pitch, mu, kOffset);
   } else {
     build_table_lds<T, true>(src, S, H, W, pitch, mu, kOffset);
   }
   const int b0 = grp * bpg;
-  fwd_boxes<T, OutT, SEG, kOffset, kInt, Q, kPack, kTail>(LdsTable<T>{S, pitch, W, H}, taps, y, map, map % C, b0,
+  fwd_boxes<T, OutT, SEG, kOffset, kInt, Q, kPack, kTail>(LdsTable<T, PAD>{S, pitch, W, H}, taps, y, map, map % C, b0,
                                                           min(bpg, B - b0), H, W, B, per_box_p, mu);
 }
 
@@ -246,7 +252,7 @@ static void fwd_lds_t(const void* x, const int* taps, void* y, int N, int C, int
     constexpr bool kOneSeg = kOffset || std::is_same<T, int>::value;
     const int nch = (W + Q - 1) / Q, seg = pc && !kOneSeg ? fwd_seg(H, nch) : 8;
     const FwdGeom g = fwd_geom_items(N, C, B, nch * n_segs(H, seg), kFwdThreads);
-    const size_t shm = table_lds_bytes(H, W, pc, g.threads);
+    const size_t shm = table_lds_bytes(H, W, pc, g.threads) + (pc ? (size_t)(H + 1) * 2 * (kFwdPad - kPad) * 4 : 0);
     auto go = [&](auto ki, auto kseg, auto kp, auto kpack) {
       hipLaunchKernelGGL((k_box_fwd_lds<T, OutT, decltype(kseg)::value, kOffset, decltype(ki)::value,
                                         decltype(kp)::value, Q, decltype(kpack)::value, false>),

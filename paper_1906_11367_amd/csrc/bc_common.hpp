@@ -162,17 +162,18 @@ __device__ __forceinline__ int med3_i32(int v, int hi) {
 // sa, sb) returns S(clamp(v, 0, H), clamp(ba + k, 0, W)) and the same at bb,
 // k in [0, N); N = kQ + 1 for interpolated edges, kQ for integer ones.
 //
-// LDS table, padded: S(u, v) at p[u * pitch + kPad + v], v in [-kPad, W+kPad];
+// LDS table, padded: S(u, v) at p[u * pitch + PAD + v], v in [-PAD, W + PAD];
 // coordinates are byte offsets, a row is clamped once (v_med3) and each run
 // is kQ + 1 consecutive words from one address.
-template <typename T>
+template <typename T, int PAD = kPad>
 struct LdsTable {
+  static constexpr int kRun = PAD;  // columns of an item one clamped run serves
   const T* p;
   int pitch, W, H;
   struct Cols { const char* a; const char* b; };  // first word of each run in table row 0
   __device__ __forceinline__ Cols cols(int ba, int bb) const {
-    const char* base = reinterpret_cast<const char*>(p + kPad);
-    return {base + clampi(ba, -kPad, W) * (int)sizeof(T), base + clampi(bb, -kPad, W) * (int)sizeof(T)};
+    const char* base = reinterpret_cast<const char*>(p + PAD);
+    return {base + clampi(ba, -PAD, W) * (int)sizeof(T), base + clampi(bb, -PAD, W) * (int)sizeof(T)};
   }
   __device__ __forceinline__ int row_step() const { return pitch * (int)sizeof(T); }
   __device__ __forceinline__ int row_coord(int v) const { return v * row_step(); }
@@ -182,7 +183,7 @@ struct LdsTable {
   using Col = const char*;
   using Row = int;
   __device__ __forceinline__ Col col(int x) const {
-    return reinterpret_cast<const char*>(p + kPad) + clampi(x, -kPad, W) * (int)sizeof(T);
+    return reinterpret_cast<const char*>(p + PAD) + clampi(x, -PAD, W) * (int)sizeof(T);
   }
   __device__ __forceinline__ Row row(int coord) const { return med3_i32(coord, H * row_step()); }
   __device__ __forceinline__ void run4(Row r, Col c, T* v) const {
@@ -216,6 +217,7 @@ struct HalfRowTable : LdsTable<float> {
 // every index is clamped.
 template <typename T, bool kVec = false>
 struct GlobalTable {
+  static constexpr int kRun = kQ;
   const T* __restrict__ p;
   int pitch, W, H;
   struct Cols { int a, b; };
@@ -270,15 +272,15 @@ __device__ __forceinline__ T add_offset(T o, float mu, float e) {
   else return o + (T)(mu * e);
 }
 
-// The x-interpolated table row for kQ consecutive outputs x0 + q: for q in
-// [0, kQ),  U[q] = sum_k wx[k] * S(v, clamp(x0 + q + ox[k])).
-template <typename T, typename Src>
+// The x-interpolated table row for N consecutive outputs x0 + q: for q in
+// [0, N),  U[q] = sum_k wx[k] * S(v, clamp(x0 + q + ox[k])).
+template <int N, typename T, typename Src>
 __device__ __forceinline__ void table_row(const Src& S, int coord, const typename Src::Cols& c, const Taps<T>& tp,
                                           T* U) {
-  T sa[kQ + 1], sb[kQ + 1];
-  S.runs(coord, c, sa, sb);
+  T sa[N + 1], sb[N + 1];
+  S.template runs<N + 1>(coord, c, sa, sb);
 #pragma unroll
-  for (int q = 0; q < kQ; ++q)
+  for (int q = 0; q < N; ++q)
     U[q] = wsum4(tp.wx[0], sa[q], tp.wx[1], sa[q + 1], tp.wx[2], sb[q], tp.wx[3], sb[q + 1]);
 }
 
