@@ -182,13 +182,16 @@ bc_status box_conv_fwd_strided(const void* x, int x_dt, const float* boxes, int 
   if (!aligned16(ws)) return BC_ERR_ALIGN;
   char* base = static_cast<char*>(ws);
   const int* taps = reinterpret_cast<const int*>(base + L.taps);
-  hipError_t e = bc::launch_box_prep(boxes, C, B, rounded, base + L.taps, stream);
+  hipError_t e = hipSuccess;
+  const bool here = path == BoxPath::Lds && bc::box_fwd_lds_computes_taps(N, C, H, W, B, stride);
+  if (!here) e = bc::launch_box_prep(boxes, C, B, rounded, base + L.taps, stream);
   if (e != hipSuccess) return BC_ERR_HIP;
   if (path == BoxPath::Stream)
     return hip_status(bc::launch_box_fwd_stream(x, is_int, taps, y, out_kind, N, C, H, W, B, offset, rounded, stream));
   if (!hbm)
     return hip_status(
-        bc::launch_box_fwd_lds(x, is_int, taps, y, out_kind, N, C, H, W, B, offset, rounded, stride, stream));
+        bc::launch_box_fwd_lds(x, is_int, taps, here ? boxes : nullptr, y, out_kind, N, C, H, W, B, offset,
+                                             rounded, stride, stream));
   float* means = offset ? reinterpret_cast<float*>(base + L.means) : nullptr;
   const size_t out_n = (size_t)N * C * B * ((H + stride - 1) / stride) * ((W + stride - 1) / stride);
   e = bc::launch_sat_build(x, is_int, base + L.sat, means, N * C, H, W,
@@ -231,12 +234,14 @@ static bc_status box_bwd_impl(const float* x, const float* boxes, const float* g
   char* base = static_cast<char*>(ws);
   float* partials = reinterpret_cast<float*>(base + L.partials);
   const int* taps = reinterpret_cast<const int*>(base + L.taps);
-  hipError_t e = bc::launch_box_prep(boxes, C, B, rounded, base + L.taps, stream);
+  hipError_t e = hipSuccess;
+  const bool here = path == BoxPath::Lds && bc::box_bwd_lds_computes_taps(N, C, H, W, B, stride);
+  if (!here) e = bc::launch_box_prep(boxes, C, B, rounded, base + L.taps, stream);
   if (e != hipSuccess) return BC_ERR_HIP;
   if (path == BoxPath::Stream) {
     e = bc::launch_box_bwd_stream(x, taps, grad_y, grad_x, partials, N, C, H, W, B, rounded, relu_bf16, stream);
   } else if (!hbm) {
-    e = bc::launch_box_bwd_lds(x, taps, grad_y, grad_x, partials, N, C, H, W, B, rounded, relu_bf16, stride, stream);
+    e = bc::launch_box_bwd_lds(x, taps, here ? boxes : nullptr, grad_y, grad_x, partials, N, C, H, W, B, rounded, relu_bf16, stride, stream);
   } else {
     float* sat_g = reinterpret_cast<float*>(base + L.sat_g);
     const size_t gy_n = (size_t)N * C * B * ((H + stride - 1) / stride) * ((W + stride - 1) / stride);

@@ -14,8 +14,9 @@ constexpr int kFwdPad = 6;
 // adjacent lanes write adjacent columns; each box's items are padded to a
 // multiple of 64 (per_box_p) so that a wave works on one box and reads its
 // taps through scalar loads.
-template <typename T, typename OutT, int SEG, bool kOffset, bool kInt, int Q, int kPack, bool kTail, typename Src>
+template <typename T, typename OutT, int SEG, bool kOffset, bool kInt, int Q, int kPack, bool kTail, bool kHere, typename Src>
 __device__ __forceinline__ void fwd_boxes(const Src& tab, const int* __restrict__ taps,
+                                          const float* __restrict__ boxes,
                                           OutT* __restrict__ y, int map, int c, int b0, int nb, int H, int W,
                                           int B, int per_box_p, float mu) {
   const int nch = (W + Q - 1) / Q, nseg = (H + SEG - 1) / SEG, per_box = nch * nseg;
@@ -25,7 +26,8 @@ __device__ __forceinline__ void fwd_boxes(const Src& tab, const int* __restrict_
     if (r >= per_box) continue;
     const ItemPos<SEG, Q> ip(r, nch, H, W, kTail);
     const int b = b0 + bl;
-    const Taps<T> tp = typed_taps<T>(load_taps(taps + (size_t)(c * B + b) * 16, W, H));
+    const Taps<T> tp = typed_taps<T>(kHere ? make_taps_here(boxes + (size_t)(c * B + b) * 4, false, kInt, W, H)
+                                           : load_taps(taps + (size_t)(c * B + b) * 16, W, H));
     OutT* out = y + ((size_t)map * B + b) * H * W;
     StoreRows<OutT, T, false, Q, kPack> em{out, W, ip.x0, ip.y0 * W + ip.x0};
     walk_fwd<SEG, T, kOffset, !kTail, kInt, Q>(tab, tp, H, W, ip.x0, ip.y0, min(ip.y0 + SEG, H), mu, em);
@@ -36,8 +38,11 @@ __device__ __forceinline__ void fwd_boxes(const Src& tab, const int* __restrict_
 // builds the map's table once and evaluates every box of its group.
 // kPitch > 0: the table's row pitch compiled in (as in the LDS backward).  Q:
 // columns per item; kPack: how rows are stored (StoreRows).
-template <typename T, typename OutT, int SEG, bool kOffset, bool kInt, int kPitch, int Q, int kPack, bool kTail>
+// kHere: the taps are computed from boxes (make_taps_here), else read.
+template <typename T, typename OutT, int SEG, bool kOffset, bool kInt, int kPitch, int Q, int kPack, bool kTail,
+          bool kHere>
 __global__ __launch_bounds__(kFwdThreads) void k_box_fwd_lds(const T* __restrict__ x, const int* __restrict__ taps,
+                                                     const float* __restrict__ boxes,
                                                      OutT* __restrict__ y, int C, int H, int W, int B, int bpg,
                                                      int per_box_p) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -57,7 +62,7 @@ __global__ __launch_bounds__(kFwdThreads) void k_box_fwd_lds(const T* __restrict
     build_table_lds<T, true>(src, S, H, W, pitch, mu, kOffset);
   }
   const int b0 = grp * bpg;
-  fwd_boxes<T, OutT, SEG, kOffset, kInt, Q, kPack, kTail>(LdsTable<T, PAD>{S, pitch, W, H}, taps, y, map, map % C, b0,
+  fwd_boxes<T, OutT, SEG, kOffset, kInt, Q, kPack, kTail, kHere>(LdsTable<T, PAD>{S, pitch, W, H}, taps, boxes, y, map, map % C, b0,
                                                           min(bpg, B - b0), H, W, B, per_box_p, mu);
 }
 
@@ -135,10 +140,12 @@ __global__ __launch_bounds__(256) void k_box_fwd_lds_strided(const T* __restrict
 // and more blocks.
 // kUp: 0 stride 1; 1 the table of the whole zero-upsampled map; 2 (stride 2)
 // its HalfRowTable.
-template <int SEG, bool kInt, int kUp, int kMaxT, bool kRelu, int kPitch, bool kTail, bool kNext>
+// kHere: the taps are computed from boxes (make_taps_here), else read.
+template <int SEG, bool kInt, int kUp, int kMaxT, bool kRelu, int kPitch, bool kTail, bool kNext, bool kHere>
 __global__ __launch_bounds__(kMaxT) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_box_bwd_lds(
-    const float* __restrict__ x, const int* __restrict__ taps, const float* __restrict__ gy, void* __restrict__ gx,
-    float* __restrict__ partials, int C, int H, int W, int B, int s, int Ho, int Wo) {
+    const float* __restrict__ x, const int* __restrict__ taps, const float* __restrict__ boxes,
+    const float* __restrict__ gy, void* __restrict__ gx, float* __restrict__ partials, int C, int H, int W, int B, int s,
+    int Ho, int Wo) {
   static_assert(!(kInt && kRelu), "the ReLU mask needs x");
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int pitch = kPitch > 0 ? kPitch : lds_pitch_dev(W);
@@ -196,7 +203,8 @@ __global__ __launch_bounds__(kMaxT) __attribute__((amdgpu_waves_per_eu(4, 8))) v
     } else {
       build_table_lds(g0 + b * plane, SG, H, W, pitch, 0.f, false);
     }
-    const Taps<float> tp = load_taps(adj + (size_t)(c * B + b) * 16, W, H);
+    const Taps<float> tp = kHere ? make_taps_here(boxes + (size_t)(c * B + b) * 4, true, kInt, W, H)
+                                 : load_taps(adj + (size_t)(c * B + b) * 16, W, H);
     if constexpr (kInt) {  // integer corners: input gradient only
       AccRows<SEG> em{acc};
       if (active) box_walk_int<SEG, float, false, !kTail>(tg, tp, H, W, x0, y0, y1, 0.f, em);
@@ -216,6 +224,11 @@ __global__ __launch_bounds__(kMaxT) __attribute__((amdgpu_waves_per_eu(4, 8))) v
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
+// Calls of at most this many filtered maps compute their taps in the kernel
+// instead of in a launch of box_prep before it (about 4 us; the arithmetic is
+// 0.3 us a wave, which larger calls would pay many times over).
+constexpr long kTapsHereBoxes = 4096;
+
 // Rows per item of the forward: a box's items fill whole waves, and each item
 // reads one row more than it writes (and its start costs about two rows), so
 // the segment length with the least waves x (rows + 3) is taken; 8 rows on
@@ -233,7 +246,7 @@ static int fwd_seg(int H, int nch) {
 }
 
 template <typename T, typename OutT, bool kOffset>
-static void fwd_lds_t(const void* x, const int* taps, void* y, int N, int C, int H, int W, int B, bool rounded,
+static void fwd_lds_t(const void* x, const int* taps, const float* boxes, void* y, int N, int C, int H, int W, int B, bool rounded,
                       int stride, hipStream_t s) {
   const int pc = lds_pitch_class(H, W);
   if (stride == 1) {
@@ -243,8 +256,8 @@ static void fwd_lds_t(const void* x, const int* taps, void* y, int N, int C, int
       const FwdGeom g = fwd_geom_items(N, C, B, n_chunks(W) * n_segs(H, SEG), 256);
       const size_t shm0 = (size_t)(H + 1) * lds_pitch(W) * sizeof(T);
       with_flag(rounded, [&](auto ki) {
-        hipLaunchKernelGGL((k_box_fwd_lds<T, OutT, SEG, kOffset, decltype(ki)::value, 0, kQ, 0, true>),
-                           dim3(N * C * g.ngrp), dim3(g.threads), shm0, s, (const T*)x, taps, (OutT*)y, C, H, W, B,
+        hipLaunchKernelGGL((k_box_fwd_lds<T, OutT, SEG, kOffset, decltype(ki)::value, 0, kQ, 0, true, false>),
+                           dim3(N * C * g.ngrp), dim3(g.threads), shm0, s, (const T*)x, taps, boxes, (OutT*)y, C, H, W, B,
                            g.bpg, g.per_box_p);
       });
       return;
@@ -254,10 +267,19 @@ static void fwd_lds_t(const void* x, const int* taps, void* y, int N, int C, int
     const FwdGeom g = fwd_geom_items(N, C, B, nch * n_segs(H, seg), kFwdThreads);
     const size_t shm = table_lds_bytes(H, W, pc, g.threads) + (pc ? (size_t)(H + 1) * 2 * (kFwdPad - kPad) * 4 : 0);
     auto go = [&](auto ki, auto kseg, auto kp, auto kpack) {
-      hipLaunchKernelGGL((k_box_fwd_lds<T, OutT, decltype(kseg)::value, kOffset, decltype(ki)::value,
-                                        decltype(kp)::value, Q, decltype(kpack)::value, false>),
-                         dim3(N * C * g.ngrp), dim3(g.threads), shm, s, (const T*)x, taps, (OutT*)y, C, H, W, B, g.bpg,
-                         g.per_box_p);
+      auto launch = [&](auto kh) {
+        hipLaunchKernelGGL((k_box_fwd_lds<T, OutT, decltype(kseg)::value, kOffset, decltype(ki)::value,
+                                          decltype(kp)::value, Q, decltype(kpack)::value, false, decltype(kh)::value>),
+                           dim3(N * C * g.ngrp), dim3(g.threads), shm, s, (const T*)x, taps, boxes, (OutT*)y, C, H, W,
+                           B, g.bpg, g.per_box_p);
+      };
+      if constexpr (decltype(kp)::value > 0) {
+        if (boxes) {
+          launch(std::true_type{});
+          return;
+        }
+      }
+      launch(std::false_type{});
     };
     with_flag(rounded, [&](auto ki) {
       auto packed = [&](auto kseg, auto kp) {
@@ -291,22 +313,26 @@ static void fwd_lds_t(const void* x, const int* taps, void* y, int N, int C, int
   });
 }
 
-hipError_t launch_box_fwd_lds(const void* x, bool is_int, const int* taps, void* y, int out_kind, int N, int C,
+bool box_fwd_lds_computes_taps(int N, int C, int H, int W, int B, int stride) {
+  return stride == 1 && W >= 6 && H >= 8 && lds_pitch_class(H, W) > 0 && (long)N * C * B <= kTapsHereBoxes;
+}
+
+hipError_t launch_box_fwd_lds(const void* x, bool is_int, const int* taps, const float* boxes, void* y, int out_kind, int N, int C,
                               int H, int W, int B, bool offset, bool rounded, int stride, hipStream_t s) {
   if (is_int) {
-    fwd_lds_t<int, int, false>(x, taps, y, N, C, H, W, B, rounded, stride, s);
+    fwd_lds_t<int, int, false>(x, taps, boxes, y, N, C, H, W, B, rounded, stride, s);
   } else if (out_kind == 2) {
-    if (offset) fwd_lds_t<float, uint16_t, true>(x, taps, y, N, C, H, W, B, rounded, stride, s);
-    else fwd_lds_t<float, uint16_t, false>(x, taps, y, N, C, H, W, B, rounded, stride, s);
+    if (offset) fwd_lds_t<float, uint16_t, true>(x, taps, boxes, y, N, C, H, W, B, rounded, stride, s);
+    else fwd_lds_t<float, uint16_t, false>(x, taps, boxes, y, N, C, H, W, B, rounded, stride, s);
   } else {
-    if (offset) fwd_lds_t<float, float, true>(x, taps, y, N, C, H, W, B, rounded, stride, s);
-    else fwd_lds_t<float, float, false>(x, taps, y, N, C, H, W, B, rounded, stride, s);
+    if (offset) fwd_lds_t<float, float, true>(x, taps, boxes, y, N, C, H, W, B, rounded, stride, s);
+    else fwd_lds_t<float, float, false>(x, taps, boxes, y, N, C, H, W, B, rounded, stride, s);
   }
   return last_error();
 }
 
 template <int SEG, int kMaxT>
-static void bwd_lds_t(const float* x, const int* taps, const float* gy, void* gx, float* partials, int N, int C,
+static void bwd_lds_t(const float* x, const int* taps, const float* boxes, const float* gy, void* gx, float* partials, int N, int C,
                       int H, int W, int B, bool rounded, bool relu_bf16, int stride, hipStream_t s) {
   const int items = n_chunks(W) * n_segs(H, SEG);
   const int threads = ((items + 63) / 64) * 64;
@@ -318,32 +344,34 @@ static void bwd_lds_t(const float* x, const int* taps, const float* gy, void* gx
   const size_t shm = table_lds_bytes(half ? Ho : H, W, pc, threads);
   using std::integral_constant;
   auto go = [&](auto ki, auto kr) {
-    auto launch = [&](auto ku, auto kp, auto kt, auto kn) {
+    auto launch = [&](auto ku, auto kp, auto kt, auto kn, auto kh) {
       hipLaunchKernelGGL((k_box_bwd_lds<SEG, decltype(ki)::value, decltype(ku)::value, kMaxT, decltype(kr)::value,
-                                        decltype(kp)::value, decltype(kt)::value, decltype(kn)::value>),
-                         dim3(N * C), dim3(threads), shm, s, x, taps, gy, gx, partials, C, H, W, B, stride, Ho, Wo);
+                                        decltype(kp)::value, decltype(kt)::value, decltype(kn)::value,
+                                        decltype(kh)::value>),
+                         dim3(N * C), dim3(threads), shm, s, x, taps, boxes, gy, gx, partials, C, H, W, B, stride, Ho, Wo);
     };
     const integral_constant<int, 0> c0;
     if (stride > 1 && !half) {
-      if (tail) launch(integral_constant<int, 1>{}, c0, std::true_type{}, std::false_type{});
-      else launch(integral_constant<int, 1>{}, c0, std::false_type{}, std::false_type{});
+      if (tail) launch(integral_constant<int, 1>{}, c0, std::true_type{}, std::false_type{}, std::false_type{});
+      else launch(integral_constant<int, 1>{}, c0, std::false_type{}, std::false_type{}, std::false_type{});
     } else if (tail) {
-      launch(c0, c0, std::true_type{}, std::false_type{});
+      launch(c0, c0, std::true_type{}, std::false_type{}, std::false_type{});
     } else {
       with_pitch(pc, [&](auto kp) {
         if constexpr (decltype(kp)::value > 0) {
           if (half) {
-            launch(integral_constant<int, 2>{}, kp, std::false_type{}, std::false_type{});
+            launch(integral_constant<int, 2>{}, kp, std::false_type{}, std::false_type{}, std::false_type{});
             return;
           }
         }
         if constexpr (SEG == 4 && decltype(kp)::value > 0) {
           if (H <= threads / 64 * 16) {
-            launch(c0, kp, std::false_type{}, std::true_type{});
+            if (boxes) launch(c0, kp, std::false_type{}, std::true_type{}, std::true_type{});
+            else launch(c0, kp, std::false_type{}, std::true_type{}, std::false_type{});
             return;
           }
         }
-        launch(c0, kp, std::false_type{}, std::false_type{});
+        launch(c0, kp, std::false_type{}, std::false_type{}, std::false_type{});
       });
     }
   };
@@ -384,15 +412,20 @@ int box_bwd_lds_waves_maps(int H, int W, long maps) {
   return seg == 0 ? 0 : (n_chunks(W) * n_segs(H, seg) + 63) / 64;
 }
 
-hipError_t launch_box_bwd_lds(const float* x, const int* taps, const float* gy, void* gx, float* partials, int N,
+bool box_bwd_lds_computes_taps(int N, int C, int H, int W, int B, int stride) {
+  return stride == 1 && W >= kQ && H >= 4 && lds_pitch_class(H, W) > 0 && (long)N * C * B <= kTapsHereBoxes &&
+         box_bwd_lds_seg_maps(H, W, (long)N * C) == 4 && H <= box_bwd_lds_waves_maps(H, W, (long)N * C) * 16;
+}
+
+hipError_t launch_box_bwd_lds(const float* x, const int* taps, const float* boxes, const float* gy, void* gx, float* partials, int N,
                               int C, int H, int W, int B, bool rounded, bool relu_bf16, int stride, hipStream_t s) {
   if (rounded && relu_bf16) return hipErrorInvalidValue;
   const int seg = box_bwd_lds_seg_maps(H, W, (long)N * C);
-  if (seg == 8) bwd_lds_t<8, 256>(x, taps, gy, gx, partials, N, C, H, W, B, rounded, relu_bf16, stride, s);
+  if (seg == 8) bwd_lds_t<8, 256>(x, taps, boxes, gy, gx, partials, N, C, H, W, B, rounded, relu_bf16, stride, s);
   else if (seg == 4 && n_chunks(W) * n_segs(H, 4) <= 256)
-    bwd_lds_t<4, 256>(x, taps, gy, gx, partials, N, C, H, W, B, rounded, relu_bf16, stride, s);
+    bwd_lds_t<4, 256>(x, taps, boxes, gy, gx, partials, N, C, H, W, B, rounded, relu_bf16, stride, s);
   else if (seg == 4)
-    bwd_lds_t<4, kBwdLdsItems>(x, taps, gy, gx, partials, N, C, H, W, B, rounded, relu_bf16, stride, s);
+    bwd_lds_t<4, kBwdLdsItems>(x, taps, boxes, gy, gx, partials, N, C, H, W, B, rounded, relu_bf16, stride, s);
   else return hipErrorInvalidValue;
   return last_error();
 }

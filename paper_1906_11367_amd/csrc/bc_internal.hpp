@@ -44,7 +44,10 @@ hipError_t launch_sat_build_up(const float* x, float* sat, int maps, int H, int 
 
 // Forward, table in LDS.  out_kind: 0 = same type as x, 1 = fp32, 2 = bf16.
 // stride > 1: y is [N][C*B][ceil(H/stride)][ceil(W/stride)].
-hipError_t launch_box_fwd_lds(const void* x, bool is_int, const int* taps, void* y, int out_kind,
+// boxes: null (taps are box_prep's records), or the boxes where the kernel
+// computes their taps itself (box_fwd_lds_computes_taps; taps is then unused).
+bool box_fwd_lds_computes_taps(int N, int C, int H, int W, int B, int stride);
+hipError_t launch_box_fwd_lds(const void* x, bool is_int, const int* taps, const float* boxes, void* y, int out_kind,
                               int N, int C, int H, int W, int B, bool offset, bool rounded, int stride,
                               hipStream_t s);
 // Forward, table read from HBM (built beforehand by sat_build into `sat`).
@@ -60,7 +63,9 @@ hipError_t launch_box_fwd_gather(const void* sat, bool is_int, const float* mean
 // rounded: input gradient only (partials unused).  stride > 1: gy is
 // [N][C*B][ceil(H/stride)][ceil(W/stride)] (tabulated zero-upsampled).
 // relu_bf16: gx is bf16 [N][C][H][W], bf16(x > 0 ? dx : 0) (not with rounded).
-hipError_t launch_box_bwd_lds(const float* x, const int* taps, const float* gy, void* gx,
+// boxes: as for the forward (box_bwd_lds_computes_taps).
+bool box_bwd_lds_computes_taps(int N, int C, int H, int W, int B, int stride);
+hipError_t launch_box_bwd_lds(const float* x, const int* taps, const float* boxes, const float* gy, void* gx,
                               float* partials, int N, int C, int H, int W, int B, bool rounded, bool relu_bf16,
                               int stride, hipStream_t s);
 constexpr int kBwdLdsItems = 1024;
