@@ -2,6 +2,8 @@
 // backward (input and box-parameter gradients).  gfx950, wave64.
 #include "bc_box.hpp"
 
+#include <algorithm>
+
 namespace bc {
 
 // Padding of the forward's tables of compiled pitch: a 6-column item then
@@ -9,24 +11,33 @@ namespace bc {
 // runs of 4.
 constexpr int kFwdPad = 6;
 
-// Forward on a map's table in LDS, for the boxes b0 .. b0+nb-1 of channel c.
-// Items of one box are (row segment, column chunk), chunk fastest so that
-// adjacent lanes write adjacent columns; each box's items are padded to a
-// multiple of 64 (per_box_p) so that a wave works on one box and reads its
-// taps through scalar loads.
-template <typename T, typename OutT, int SEG, bool kOffset, bool kInt, int Q, int kPack, bool kTail, bool kHere, typename Src>
+// Forward on a map's table in LDS, for the groups g0 .. g0+ng-1 of bpw boxes
+// of channel c.  Items of one box are (row segment, column chunk), chunk
+// fastest so that adjacent lanes write adjacent columns; a group's items are
+// padded to a multiple of 64 (per_grp) so that a wave works on one group.  One
+// box (bpw = 1): the wave reads its taps through scalar loads.  kLanes: maps of
+// at most 32 items, whose waves would be half empty, take as many boxes as fit
+// 64 lanes, each lane with its own box's taps.
+template <typename T, typename OutT, int SEG, bool kOffset, bool kInt, int Q, int kPack, bool kTail, bool kHere,
+          bool kLanes, typename Src>
 __device__ __forceinline__ void fwd_boxes(const Src& tab, const int* __restrict__ taps,
                                           const float* __restrict__ boxes,
-                                          OutT* __restrict__ y, int map, int c, int b0, int nb, int H, int W,
-                                          int B, int per_box_p, float mu) {
+                                          OutT* __restrict__ y, int map, int c, int g0, int ng, int H, int W,
+                                          int B, int bpw, int per_grp, float mu) {
   const int nch = (W + Q - 1) / Q, nseg = (H + SEG - 1) / SEG, per_box = nch * nseg;
-  for (int it = threadIdx.x; it < nb * per_box_p; it += blockDim.x) {
-    const int bl = __builtin_amdgcn_readfirstlane(it / per_box_p);
-    const int r = it - bl * per_box_p;
-    if (r >= per_box) continue;
+  for (int it = threadIdx.x; it < ng * per_grp; it += blockDim.x) {
+    const int gl = __builtin_amdgcn_readfirstlane(it / per_grp);
+    int r = it - gl * per_grp, b = (g0 + gl) * bpw;
+    if constexpr (kLanes) {
+      const int bl = r / per_box;
+      r -= bl * per_box;
+      b += bl;
+      if (bl >= bpw || b >= B) continue;
+    } else {
+      if (r >= per_box) continue;
+    }
     const ItemPos<SEG, Q> ip(r, nch, H, W, kTail);
-    const int b = b0 + bl;
-    const Taps<T> tp = typed_taps<T>(kHere ? make_taps_here(boxes + (size_t)(c * B + b) * 4, false, kInt, W, H)
+    const Taps<T> tp = typed_taps<T>(kHere ? make_taps_here<!kLanes>(boxes + (size_t)(c * B + b) * 4, false, kInt, W, H)
                                            : load_taps(taps + (size_t)(c * B + b) * 16, W, H));
     OutT* out = y + ((size_t)map * B + b) * H * W;
     StoreRows<OutT, T, false, Q, kPack> em{out, W, ip.x0, ip.y0 * W + ip.x0};
@@ -34,23 +45,23 @@ __device__ __forceinline__ void fwd_boxes(const Src& tab, const int* __restrict_
   }
 }
 
-// Forward, table in LDS: one block per (map, group of bpg boxes).  The block
-// builds the map's table once and evaluates every box of its group.
+// Forward, table in LDS: one block per (map, bpg groups of bpw boxes).  The
+// block builds the map's table once and evaluates every box of its groups.
 // kPitch > 0: the table's row pitch compiled in (as in the LDS backward).  Q:
 // columns per item; kPack: how rows are stored (StoreRows).
 // kHere: the taps are computed from boxes (make_taps_here), else read.
 template <typename T, typename OutT, int SEG, bool kOffset, bool kInt, int kPitch, int Q, int kPack, bool kTail,
-          bool kHere>
+          bool kHere, bool kLanes>
 __global__ __launch_bounds__(kFwdThreads) void k_box_fwd_lds(const T* __restrict__ x, const int* __restrict__ taps,
                                                      const float* __restrict__ boxes,
-                                                     OutT* __restrict__ y, int C, int H, int W, int B, int bpg,
-                                                     int per_box_p) {
+                                                     OutT* __restrict__ y, int C, int H, int W, int B, int bpw,
+                                                     int bpg, int per_grp) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T* S = reinterpret_cast<T*>(smem_raw);
   __shared__ float red[16];
   constexpr int PAD = kPitch > 0 ? kFwdPad : kPad;
   const int pitch = kPitch > 0 ? kPitch + 2 * (PAD - kPad) : lds_pitch_dev(W);
-  const int ngrp = (B + bpg - 1) / bpg;
+  const int groups = (B + bpw - 1) / bpw, ngrp = (groups + bpg - 1) / bpg;
   const int map = blockIdx.x / ngrp, grp = blockIdx.x - map * ngrp;
   const T* src = x + (size_t)map * H * W;
   float mu = 0.f;
@@ -61,9 +72,10 @@ __global__ __launch_bounds__(kFwdThreads) void k_box_fwd_lds(const T* __restrict
   } else {
     build_table_lds<T, true>(src, S, H, W, pitch, mu, kOffset);
   }
-  const int b0 = grp * bpg;
-  fwd_boxes<T, OutT, SEG, kOffset, kInt, Q, kPack, kTail, kHere>(LdsTable<T, PAD>{S, pitch, W, H}, taps, boxes, y, map, map % C, b0,
-                                                          min(bpg, B - b0), H, W, B, per_box_p, mu);
+  const int g0 = grp * bpg;
+  fwd_boxes<T, OutT, SEG, kOffset, kInt, Q, kPack, kTail, kHere, kLanes>(LdsTable<T, PAD>{S, pitch, W, H}, taps, boxes,
+                                                                         y, map, map % C, g0, min(bpg, groups - g0), H,
+                                                                         W, B, bpw, per_grp, mu);
 }
 
 // Strided forward (stride s > 1) on a map's table in LDS, boxes b0 .. b0+nb-1
@@ -256,30 +268,43 @@ static void fwd_lds_t(const void* x, const int* taps, const float* boxes, void* 
       const FwdGeom g = fwd_geom_items(N, C, B, n_chunks(W) * n_segs(H, SEG), 256);
       const size_t shm0 = (size_t)(H + 1) * lds_pitch(W) * sizeof(T);
       with_flag(rounded, [&](auto ki) {
-        hipLaunchKernelGGL((k_box_fwd_lds<T, OutT, SEG, kOffset, decltype(ki)::value, 0, kQ, 0, true, false>),
+        hipLaunchKernelGGL((k_box_fwd_lds<T, OutT, SEG, kOffset, decltype(ki)::value, 0, kQ, 0, true, false, false>),
                            dim3(N * C * g.ngrp), dim3(g.threads), shm0, s, (const T*)x, taps, boxes, (OutT*)y, C, H, W, B,
-                           g.bpg, g.per_box_p);
+                           1, g.bpg, g.per_box_p);
       });
       return;
     }
     constexpr bool kOneSeg = kOffset || std::is_same<T, int>::value;
     const int nch = (W + Q - 1) / Q, seg = pc && !kOneSeg ? fwd_seg(H, nch) : 8;
-    const FwdGeom g = fwd_geom_items(N, C, B, nch * n_segs(H, seg), kFwdThreads);
+    const int per_box = nch * n_segs(H, seg);
+    const bool lanes = pc == 55 && seg == 8 && per_box <= 32 && B > 1;
+    const int bpw = lanes ? std::min(64 / per_box, B) : 1;
+    const FwdGeom g = fwd_geom_items(N, C, (B + bpw - 1) / bpw, bpw * per_box, kFwdThreads);
     const size_t shm = table_lds_bytes(H, W, pc, g.threads) + (pc ? (size_t)(H + 1) * 2 * (kFwdPad - kPad) * 4 : 0);
     auto go = [&](auto ki, auto kseg, auto kp, auto kpack) {
-      auto launch = [&](auto kh) {
+      auto launch = [&](auto kh, auto kl) {
         hipLaunchKernelGGL((k_box_fwd_lds<T, OutT, decltype(kseg)::value, kOffset, decltype(ki)::value,
-                                          decltype(kp)::value, Q, decltype(kpack)::value, false, decltype(kh)::value>),
+                                          decltype(kp)::value, Q, decltype(kpack)::value, false, decltype(kh)::value,
+                                          decltype(kl)::value>),
                            dim3(N * C * g.ngrp), dim3(g.threads), shm, s, (const T*)x, taps, boxes, (OutT*)y, C, H, W,
-                           B, g.bpg, g.per_box_p);
+                           B, bpw, g.bpg, g.per_box_p);
+      };
+      auto with_lanes = [&](auto kh) {
+        if constexpr (decltype(kp)::value == 55 && decltype(kseg)::value == 8) {
+          if (lanes) {
+            launch(kh, std::true_type{});
+            return;
+          }
+        }
+        launch(kh, std::false_type{});
       };
       if constexpr (decltype(kp)::value > 0) {
         if (boxes) {
-          launch(std::true_type{});
+          with_lanes(std::true_type{});
           return;
         }
       }
-      launch(std::false_type{});
+      with_lanes(std::false_type{});
     };
     with_flag(rounded, [&](auto ki) {
       auto packed = [&](auto kseg, auto kp) {

@@ -318,26 +318,29 @@ __device__ __forceinline__ Taps<float> load_taps(const int* __restrict__ rec, in
   return t;
 }
 
-// The same taps computed here from the box itself (wave-uniform; every lane
-// does the same fp64 arithmetic as box_prep, so these are its record's bits):
-// for calls of few boxes, where the arithmetic costs less than the launch of
-// box_prep before them.
+// The same taps computed here from the box itself (the fp64 arithmetic of
+// box_prep, so these are its record's bits): for calls of few boxes, where the
+// arithmetic costs less than the launch of box_prep before them.  kUniform:
+// one box per wave; its taps are then scalars.
+template <bool kUniform = true>
 __device__ __forceinline__ Taps<float> make_taps_here(const float* __restrict__ box, bool adjoint, bool rounded, int W,
                                                       int H) {
   const Taps<float> r = rounded ? make_taps_rounded(box, adjoint, 1 << 20, 1 << 20)
                         : adjoint ? make_taps_adjoint(box, 1 << 20, 1 << 20)
                                   : make_taps_f32(box, false, 1 << 20, 1 << 20);
-  auto first = [](float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); };
+  auto first = [](int v) { return kUniform ? __builtin_amdgcn_readfirstlane(v) : v; };
   Taps<float> t;
 #pragma unroll
   for (int e = 0; e < 2; ++e) {
-    const int fx = __builtin_amdgcn_readfirstlane(clampi(r.ox[2 * e], -(W + 1), W + 1));
-    const int fy = __builtin_amdgcn_readfirstlane(clampi(r.oy[2 * e], -(H + 1), H + 1));
+    const int fx = first(clampi(r.ox[2 * e], -(W + 1), W + 1)), fy = first(clampi(r.oy[2 * e], -(H + 1), H + 1));
     t.ox[2 * e] = fx; t.ox[2 * e + 1] = fx + 1;
     t.oy[2 * e] = fy; t.oy[2 * e + 1] = fy + 1;
   }
 #pragma unroll
-  for (int k = 0; k < 4; ++k) { t.wx[k] = first(r.wx[k]); t.wy[k] = first(r.wy[k]); }
+  for (int k = 0; k < 4; ++k) {
+    t.wx[k] = __int_as_float(first(__float_as_int(r.wx[k])));
+    t.wy[k] = __int_as_float(first(__float_as_int(r.wy[k])));
+  }
   return t;
 }
 
