@@ -30,11 +30,12 @@
 //                   edges (the y-weighted column differences) and v the input;
 //                   dL/dc = -sum_j G(y + fd, j) * T(j), dL/dd =
 //                   sum_j G(y + fc, j) * T(j), with T(j) = sum_k wx[k] *
-//                   V(j + 1 - ox[k]) and V(t) = sum_{x >= t} v(y, x), the
-//                   suffix sums of the input row: the x-interpolated row of the
-//                   table of the single row G(y + f) weighted by v, moved onto
-//                   the input row (sum_x v(x) sum_k wx[k] sum_{j < x+ox[k]} G(j)
-//                   = sum_j G(j) T(j)).
+//                   V(j + 1 - ox[k]) and V(t) = sum_{x >= t} v(y, x): the
+//                   x-interpolated row of the table of the single row G(y + f)
+//                   weighted by v, moved onto the input row (sum_x v(x) sum_k
+//                   wx[k] sum_{j < x+ox[k]} G(j) = sum_j G(j) T(j)).  The
+//                   weights of a box sum to 0, so V may be replaced by minus
+//                   the prefix sums of the input row, one forward scan.
 // Lane layout: a group of LG lanes holds one box's row, CPL consecutive
 // columns per lane (LG * CPL >= W); LG = 16 puts four boxes in a wave (one
 // per DPP row, scans by row shifts), LG = 64 one box per wave.
@@ -133,9 +134,10 @@ template <int CPL>
 __device__ __forceinline__ int slot_at(int j) { return stream_skew<CPL>() ? j + (j >> 5) : j; }
 template <int LG, int CPL> constexpr int slot_words() { return stream_skew<CPL>() ? LG * CPL + LG * CPL / 32 : LG * CPL; }
 
-// Rows of a step are loaded kPrefetch steps ahead (a ring of registers), so
-// that a step's loads are in flight while the steps before it compute.
+// Rows of a step are loaded kPrefetch steps ahead (a ring of registers, the
+// loop unrolled over it, so that no row is copied), so that a step's loads are in flight while the steps before it compute.
 constexpr int kPrefetch = 2;
+constexpr int kFwdPrefetch = 3;  // 256x130 maps, 4 boxes: 63 us two ahead, 59 three
 
 // The lane's CPL columns of a map row: byte offsets within a row (columns
 // outside the map clamped onto its last column, so every load is in bounds)
@@ -182,6 +184,45 @@ struct LaneCols {
   }
 };
 
+// The same for groups of a whole wave: the box, and with it the row, is
+// wave-uniform, so a row is one scalar offset into the map's buffer
+// descriptor (rows outside the map: an offset past its end, which reads 0),
+// and columns outside the map are lane offsets past its end.  Row checks and
+// addresses then cost scalar instructions; they were a third of the vector
+// instructions of these kernels, which wait on those first.
+template <int CPL>
+struct WaveRows {
+  __amdgpu_buffer_rsrc_t rs;
+  unsigned off[CPL];
+  int H, row_bytes;
+  __device__ __forceinline__ WaveRows(const void* map, int x0, int H_, int W) : H(H_), row_bytes(4 * W) {
+    rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(map), (short)0, H_ * W * 4, 0x00020000);
+#pragma unroll
+    for (int k = 0; k < CPL; ++k) off[k] = x0 + k < W ? 4u * (unsigned)(x0 + k) : 0x40000000u;
+  }
+  __device__ __forceinline__ bool inside(int row) const { return row >= 0 && row < H; }
+  template <bool kVec, typename T>
+  __device__ __forceinline__ void load(int row, T* r) const {
+    const unsigned ro = inside(row) ? (unsigned)(row * row_bytes) : 0x40000000u;
+    if constexpr (kVec && CPL == 4) {
+      const auto t = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(off[0] + ro), 0, 0);
+      const unsigned w[4] = {t[0], t[1], t[2], t[3]};
+#pragma unroll
+      for (int k = 0; k < 4; ++k) r[k] = __builtin_bit_cast(T, w[k]);
+    } else {
+#pragma unroll
+      for (int k = 0; k < CPL; ++k)
+        r[k] = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(off[k] + ro), 0, 0));
+    }
+  }
+};
+
+// A value that is the same in every lane of a group: a scalar when the group
+// is the wave.
+template <int LG> __device__ __forceinline__ int group_uniform(int v) {
+  return LG == 64 ? __builtin_amdgcn_readfirstlane(v) : v;
+}
+
 // ---------------------------------------------------------------------------
 // Backward.  One block of NG groups per map (n, c); group g walks box b = g.
 // dx: each group leaves its adjoint sums in LDS slots; every R rows the
@@ -208,7 +249,7 @@ __global__ __launch_bounds__(LG * NG) void k_box_bwd_stream(const float* __restr
   float* SV = SY + NG * RW;               // [NG][RW]: suffix sums of the input row
   float* DX = SV + NG * RW;               // [2][R][NG][SW]: adjoint sums, added over groups
   const int map = blockIdx.x, n = map / C, c = map - n * C;
-  const int g = threadIdx.x / LG, p = threadIdx.x % LG;
+  const int g = group_uniform<LG>(threadIdx.x / LG), p = threadIdx.x % LG;
   const int b = g;
   const bool live = b < B;
   const int x0 = p * CPL;
@@ -217,6 +258,15 @@ __global__ __launch_bounds__(LG * NG) void k_box_bwd_stream(const float* __restr
   const float* gbase = gy + (size_t)map * B * plane;
   const unsigned gmap = live ? 4u * (unsigned)(b * plane) : 0u;
   const LaneCols<CPL> cols(x0, W);
+  const WaveRows<CPL> xrows(xs, x0, H, W), grows(gbase + (size_t)(live ? b : 0) * plane, x0, H, W);
+  auto load_x = [&](int row, float (&r)[CPL]) {
+    if constexpr (LG == 64) xrows.template load<kVec>(row, r);
+    else cols.template load<kVec>(xs, 0u, row, H, W, true, r);
+  };
+  auto load_g = [&](int row, float (&r)[CPL]) {
+    if constexpr (LG == 64) grows.template load<kVec>(live ? row : -1, r);
+    else cols.template load<kVec>(gbase, gmap, row, H, W, live, r);
+  };
   float* sy = SY + g * RW;                // sy[stream_at(v)] = scan Y (v), v in [-PAD, LC + PAD]
   float* sv = SV + g * RW;
   // adjoint record of the box (each group its own; vector loads)
@@ -224,8 +274,8 @@ __global__ __launch_bounds__(LG * NG) void k_box_bwd_stream(const float* __restr
   const int fa = tp.ox[0], fb = tp.ox[2], fc = tp.oy[0], fd = tp.oy[2];
   const float aa = -tp.wx[1], ab = tp.wx[3], bc_ = -tp.wy[1], bd = tp.wy[3];
   // LDS indices of the lane's tap runs (scan Y at the adjoint's x edges, the
-  // suffix sums at the mirrored taps) and of the entries it writes
-  int ia[CPL + 1], ib[CPL + 1], ja[CPL + 1], jb[CPL + 1], iw[CPL], jw[CPL];
+  // input row's sums at the mirrored taps) and of the entries it writes
+  int ia[CPL + 1], ib[CPL + 1], ja[CPL + 1], jb[CPL + 1], iw[CPL];
   {
     const int ra0 = clampi(x0 + fa, -PAD, W), rb0 = clampi(x0 + fb, -PAD, W);
     const int va0 = clampi(x0 - fa, -PAD, W), vb0 = clampi(x0 - fb, -PAD, W);
@@ -237,16 +287,12 @@ __global__ __launch_bounds__(LG * NG) void k_box_bwd_stream(const float* __restr
       jb[k] = stream_at<CPL>(vb0 + k);
     }
 #pragma unroll
-    for (int k = 0; k < CPL; ++k) {
-      iw[k] = stream_at<CPL>(x0 + k + 1);
-      jw[k] = stream_at<CPL>(x0 + k);
-    }
+    for (int k = 0; k < CPL; ++k) iw[k] = stream_at<CPL>(x0 + k + 1);
   }
-  // constant parts of the LDS rows: scan Y is 0 left of column 0, the input
-  // row's suffix sums are 0 right of column W
+  // constant parts of the LDS rows: both are 0 left of column 0
   for (int t = p; t <= PAD; t += LG) {
     sy[stream_at<CPL>(-PAD + t)] = 0.f;
-    sv[stream_at<CPL>(LC + t)] = 0.f;
+    sv[stream_at<CPL>(-PAD + t)] = 0.f;
   }
   // cursors: P(clamp(y + fc)) and P(clamp(y + fd)) at the lane's columns
   float pc[CPL], pd[CPL];
@@ -257,7 +303,7 @@ __global__ __launch_bounds__(LG * NG) void k_box_bwd_stream(const float* __restr
     for (int u0 = 0; u0 < upto; u0 += PF) {
       float r[PF][CPL];
 #pragma unroll
-      for (int i = 0; i < PF; ++i) cols.template load<kVec>(gbase, gmap, u0 + i < upto ? u0 + i : -1, H, W, live, r[i]);
+      for (int i = 0; i < PF; ++i) load_g(u0 + i < upto ? u0 + i : -1, r[i]);
 #pragma unroll
       for (int i = 0; i < PF; ++i) {
         const bool inc = u0 + i < fc;
@@ -270,15 +316,22 @@ __global__ __launch_bounds__(LG * NG) void k_box_bwd_stream(const float* __restr
     }
   }
   float ca = 0.f, cb = 0.f, gcs = 0.f, gds = 0.f;
-  // rows of step y: the input row v, gc_ = G(y + fc), gd_ = G(y + fd); a
-  // queue of PF steps, step y at the front
-  float qv[PF][CPL], qc[PF][CPL], qd[PF][CPL];
+  // rows of step y: the input row v, gc_ = G(y + fc), gd_ = G(y + fd).  kRing:
+  // a ring of PF + 1 steps with the loop unrolled over it; else a queue whose
+  // rows are copied forward (24 moves a step, but one copy of the step: with 4
+  // columns and all gradients the unrolled form takes 187 VGPRs, one block of
+  // 512 per CU; 256x256 maps, 8 boxes: 565 us against 473; 200x150, 6 boxes:
+  // 204 against 215)
+  constexpr bool kRing = CPL < 4 || kInt;
+  constexpr int RS = kRing ? PF + 1 : PF;
+  float qv[RS][CPL], qc[RS][CPL], qd[RS][CPL];
   auto issue = [&](int y, float (&v)[CPL], float (&gc_)[CPL], float (&gd_)[CPL]) {
     const bool in = y < H;
-    if constexpr (!kInt) cols.template load<kVec>(xs, 0u, in ? y : -1, H, W, true, v);
-    cols.template load<kVec>(gbase, gmap, in ? y + fc : -1, H, W, live, gc_);
-    cols.template load<kVec>(gbase, gmap, in ? y + fd : -1, H, W, live, gd_);
+    if constexpr (!kInt) load_x(in ? y : -1, v);
+    load_g(in ? y + fc : -1, gc_);
+    load_g(in ? y + fd : -1, gd_);
   };
+  int bi = 0, ri = 0;   // slot set and row of the current batch
   // one output row
   auto step = [&](int y, const float* v, const float* gc_, const float* gd_) {
     // Y and its scan (inclusive within the lane, then across the group)
@@ -299,18 +352,17 @@ __global__ __launch_bounds__(LG * NG) void k_box_bwd_stream(const float* __restr
 #pragma unroll
       for (int t = 1; t <= PAD; ++t) sy[stream_at<CPL>(LC + t)] = s[CPL - 1] + off;
     }
-    // suffix sums of the input row (the same in every group)
+    // prefix sums of the input row (the same in every group)
     if constexpr (!kInt) {
-      float sfx[CPL];
+      float pfx[CPL];
 #pragma unroll
-      for (int k = CPL - 1; k >= 0; --k) sfx[k] = k < CPL - 1 ? sfx[k + 1] + v[k] : v[k];
-      const float vt = sfx[0];
-      const float voff = group_excl<LG, true>(vt);
+      for (int k = 0; k < CPL; ++k) pfx[k] = k ? pfx[k - 1] + v[k] : v[k];
+      const float voff = group_excl<LG, false>(pfx[CPL - 1]);
 #pragma unroll
-      for (int k = 0; k < CPL; ++k) sv[jw[k]] = sfx[k] + voff;
-      if (p == 0) {
+      for (int k = 0; k < CPL; ++k) sv[iw[k]] = pfx[k] + voff;
+      if (p == LG - 1) {
 #pragma unroll
-        for (int t = 1; t <= PAD; ++t) sv[stream_at<CPL>(-t)] = sfx[0] + voff;
+        for (int t = 1; t <= PAD; ++t) sv[stream_at<CPL>(LC + t)] = pfx[CPL - 1] + voff;
       }
     }
     __builtin_amdgcn_wave_barrier();
@@ -318,8 +370,7 @@ __global__ __launch_bounds__(LG * NG) void k_box_bwd_stream(const float* __restr
     float sa[CPL + 1], sb[CPL + 1];
 #pragma unroll
     for (int k = 0; k <= CPL; ++k) { sa[k] = sy[ia[k]]; sb[k] = sy[ib[k]]; }
-    const int bi = y / R, ri = y - bi * R;
-    float* dxs = DX + (((bi & 1) * R + ri) * NG + g) * SW;
+    float* dxs = DX + ((bi * R + ri) * NG + g) * SW;
 #pragma unroll
     for (int k = 0; k < CPL; ++k) {
       float d;
@@ -339,7 +390,7 @@ __global__ __launch_bounds__(LG * NG) void k_box_bwd_stream(const float* __restr
       for (int k = 0; k <= CPL; ++k) { A[k] = sv[ja[k]]; Bv[k] = sv[jb[k]]; }
 #pragma unroll
       for (int k = 0; k < CPL; ++k) {
-        const float t = fmaf(-ab, Bv[k + 1] - Bv[k], fmaf(aa, A[k + 1] - A[k], Bv[k + 1] - A[k + 1]));
+        const float t = fmaf(ab, Bv[k + 1] - Bv[k], fmaf(-aa, A[k + 1] - A[k], A[k + 1] - Bv[k + 1]));
         gcs = fmaf(gc_[k], t, gcs);
         gds = fmaf(gd_[k], t, gds);
       }
@@ -347,11 +398,11 @@ __global__ __launch_bounds__(LG * NG) void k_box_bwd_stream(const float* __restr
     __builtin_amdgcn_wave_barrier();
     // every R rows (and after the last): the slots of the batch, added over
     // the groups in a fixed order
-    if (ri == R - 1 || y == H - 1) {
+    if (++ri == R || y == H - 1) {
       __syncthreads();
-      const float* slots = DX + (bi & 1) * R * NG * SW;
-      for (int r = 0; r <= ri; ++r) {
-        const int yy = bi * R + r;
+      const float* slots = DX + bi * R * NG * SW;
+      for (int r = 0; r < ri; ++r) {
+        const int yy = y + 1 - ri + r;
         for (int j = threadIdx.x; j < W; j += LG * NG) {
           float acc = 0.f;
 #pragma unroll
@@ -364,20 +415,37 @@ __global__ __launch_bounds__(LG * NG) void k_box_bwd_stream(const float* __restr
           }
         }
       }
+      ri = 0;
+      bi ^= 1;
     }
   };
 #pragma unroll
   for (int i = 0; i < PF; ++i) issue(i, qv[i], qc[i], qd[i]);
-  for (int y = 0; y < H; ++y) {
-    float v[CPL], gc_[CPL], gd_[CPL];
+  if constexpr (kRing) {
+    int y = 0;
+    for (; y + RS <= H; y += RS) {
 #pragma unroll
-    for (int k = 0; k < CPL; ++k) { v[k] = qv[0][k]; gc_[k] = qc[0][k]; gd_[k] = qd[0][k]; }
+      for (int i = 0; i < RS; ++i) {
+        issue(y + i + PF, qv[(i + PF) % RS], qc[(i + PF) % RS], qd[(i + PF) % RS]);
+        step(y + i, qv[i], qc[i], qd[i]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
 #pragma unroll
-    for (int i = 0; i + 1 < PF; ++i)
+    for (int i = 0; i < PF; ++i)
+      if (y + i < H) step(y + i, qv[i], qc[i], qd[i]);
+  } else {
+    for (int y = 0; y < H; ++y) {
+      float v[CPL], gc_[CPL], gd_[CPL];
 #pragma unroll
-      for (int k = 0; k < CPL; ++k) { qv[i][k] = qv[i + 1][k]; qc[i][k] = qc[i + 1][k]; qd[i][k] = qd[i + 1][k]; }
-    issue(y + PF, qv[PF - 1], qc[PF - 1], qd[PF - 1]);
-    step(y, v, gc_, gd_);
+      for (int k = 0; k < CPL; ++k) { v[k] = qv[0][k]; gc_[k] = qc[0][k]; gd_[k] = qd[0][k]; }
+#pragma unroll
+      for (int i = 0; i + 1 < PF; ++i)
+#pragma unroll
+        for (int k = 0; k < CPL; ++k) { qv[i][k] = qv[i + 1][k]; qc[i][k] = qc[i + 1][k]; qd[i][k] = qd[i + 1][k]; }
+      issue(y + PF, qv[PF - 1], qc[PF - 1], qd[PF - 1]);
+      step(y, v, gc_, gd_);
+    }
   }
   if constexpr (!kInt) {
     // (dL/da, dL/db, dL/dc, dL/dd) of the box, one partial per image
@@ -411,19 +479,20 @@ __global__ __launch_bounds__(LG * NG) void k_box_fwd_stream(const T* __restrict_
   constexpr bool kPlain = kInt || std::is_same<T, int>::value;   // corner weights (-1, 0, 1, 0)
   constexpr int PAD = stream_pad<CPL>();
   constexpr int RW = stream_row_words<LG, CPL>();
-  constexpr int PF = kPrefetch;
+  constexpr int PF = kFwdPrefetch;
   constexpr int LC = LG * CPL;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T* SY = reinterpret_cast<T*>(smem_raw);
   __shared__ float red[(LG * NG + 63) / 64];
   const int map = blockIdx.x, c = map % C;
-  const int g = threadIdx.x / LG, p = threadIdx.x % LG;
+  const int g = group_uniform<LG>(threadIdx.x / LG), p = threadIdx.x % LG;
   const int b = g;
   const bool live = b < B;
   const int x0 = p * CPL;
   const size_t plane = (size_t)H * W;
   const T* xs = x + (size_t)map * plane;
   const LaneCols<CPL> cols(x0, W);
+  const WaveRows<CPL> rows(xs, x0, H, W);
   T* sy = SY + g * RW;                    // sy[stream_at(v)] = scan Y (v)
   float mu = 0.f;
   if constexpr (kOffset) {
@@ -456,16 +525,20 @@ __global__ __launch_bounds__(LG * NG) void k_box_fwd_stream(const T* __restrict_
   T pc[CPL], pd[CPL];
 #pragma unroll
   for (int k = 0; k < CPL; ++k) { pc[k] = (T)0; pd[k] = (T)0; }
-  // map row `row` at the lane's columns, minus mu (kOffset), 0 outside
+  // map row `row` at the lane's columns, 0 outside, and (kOffset, where it is
+  // used) minus mu
   auto load_row = [&](int row, T (&r)[CPL]) {
-    cols.template load<kVec>(xs, 0u, row, H, W, live, r);
+    if constexpr (LG == 64) rows.template load<kVec>(live ? row : -1, r);
+    else cols.template load<kVec>(xs, 0u, row, H, W, live, r);
+  };
+  float mul[CPL];   // mu at the lane's columns, 0 outside the map
+#pragma unroll
+  for (int k = 0; k < CPL; ++k) mul[k] = kVec || cols.in[k] ? mu : 0.f;
+  auto minus_mu = [&](int row, T (&r)[CPL]) {
     if constexpr (kOffset) {
       const bool ok = live && row >= 0 && row < H;
 #pragma unroll
-      for (int k = 0; k < CPL; ++k) {
-        const float v = (float)r[k] - mu;
-        r[k] = __builtin_bit_cast(T, __builtin_bit_cast(int, (T)v) & ((ok && cols.in[k]) ? -1 : 0));
-      }
+      for (int k = 0; k < CPL; ++k) r[k] = (T)((float)r[k] - (ok ? (kVec ? mu : mul[k]) : 0.f));
     }
   };
   {
@@ -476,6 +549,7 @@ __global__ __launch_bounds__(LG * NG) void k_box_fwd_stream(const T* __restrict_
       for (int i = 0; i < PF; ++i) load_row(u0 + i < upto ? u0 + i : -1, r[i]);
 #pragma unroll
       for (int i = 0; i < PF; ++i) {
+        minus_mu(u0 + i < upto ? u0 + i : -1, r[i]);
         const bool inc = u0 + i < fc;
 #pragma unroll
         for (int k = 0; k < CPL; ++k) {
@@ -497,7 +571,9 @@ __global__ __launch_bounds__(LG * NG) void k_box_fwd_stream(const T* __restrict_
     }
   }
   OutT* out = y + ((size_t)map * B + (live ? b : 0)) * plane;
-  auto step = [&](int yy, const T* gc_, const T* gd_) {
+  auto step = [&](int yy, T (&gc_)[CPL], T (&gd_)[CPL]) {
+    minus_mu(yy + fc, gc_);
+    minus_mu(yy + fd, gd_);
     T s[CPL];
 #pragma unroll
     for (int k = 0; k < CPL; ++k) {
@@ -524,7 +600,7 @@ __global__ __launch_bounds__(LG * NG) void k_box_fwd_stream(const T* __restrict_
       const int yc = yy + fc, yd = yy + fd;
       const float wc = (float)(clampi(yc + 1, 0, H) - clampi(yc, 0, H));
       const float wd = (float)(clampi(yd + 1, 0, H) - clampi(yd, 0, H));
-      ey = (float)(clampi(yd, 0, H) - clampi(yc, 0, H)) + (kPlain ? 0.f : bd * wd - bc_ * wc);
+      ey = mu * ((float)(clampi(yd, 0, H) - clampi(yc, 0, H)) + (kPlain ? 0.f : bd * wd - bc_ * wc));
     }
     if (live) {
       OutT* row = out + (size_t)yy * W;
@@ -534,7 +610,7 @@ __global__ __launch_bounds__(LG * NG) void k_box_fwd_stream(const T* __restrict_
         T o;
         if constexpr (kPlain) o = sb[k] - sa[k];
         else o = fmaf(ab, sb[k + 1] - sb[k], fmaf(-aa, sa[k + 1] - sa[k], sb[k] - sa[k]));
-        if constexpr (kOffset) o = o + (T)(mu * (ex[k] * ey));
+        if constexpr (kOffset) o = add_offset(o, ex[k], ey);
         if constexpr (std::is_same<OutT, uint16_t>::value) ov[k] = f32_to_bf16_rne((float)o);
         else ov[k] = (OutT)o;
       }
@@ -558,36 +634,38 @@ __global__ __launch_bounds__(LG * NG) void k_box_fwd_stream(const T* __restrict_
     }
     __builtin_amdgcn_wave_barrier();
   };
-  // main loop, the rows of step yy loaded PF steps ahead (a queue, step yy
-  // at the front)
-  T qc[PF][CPL], qd[PF][CPL];
+  // main loop, the rows of step yy loaded PF steps ahead
+  constexpr int RS = PF + 1;
+  T qc[RS][CPL], qd[RS][CPL];
+  auto issue = [&](int yn, T (&gc_)[CPL], T (&gd_)[CPL]) {
+    load_row(yn < H ? yn + fc : -1, gc_);
+    load_row(yn < H ? yn + fd : -1, gd_);
+  };
 #pragma unroll
-  for (int i = 0; i < PF; ++i) {
-    load_row(i < H ? i + fc : -1, qc[i]);
-    load_row(i < H ? i + fd : -1, qd[i]);
+  for (int i = 0; i < PF; ++i) issue(i, qc[i], qd[i]);
+  int yy = 0;
+  for (; yy + RS <= H; yy += RS) {
+#pragma unroll
+    for (int i = 0; i < RS; ++i) {
+      issue(yy + i + PF, qc[(i + PF) % RS], qd[(i + PF) % RS]);
+      step(yy + i, qc[i], qd[i]);
+    }
   }
-  for (int yy = 0; yy < H; ++yy) {
-    T gc_[CPL], gd_[CPL];
 #pragma unroll
-    for (int k = 0; k < CPL; ++k) { gc_[k] = qc[0][k]; gd_[k] = qd[0][k]; }
-#pragma unroll
-    for (int i = 0; i + 1 < PF; ++i)
-#pragma unroll
-      for (int k = 0; k < CPL; ++k) { qc[i][k] = qc[i + 1][k]; qd[i][k] = qd[i + 1][k]; }
-    const int yn = yy + PF;
-    load_row(yn < H ? yn + fc : -1, qc[PF - 1]);
-    load_row(yn < H ? yn + fd : -1, qd[PF - 1]);
-    step(yy, gc_, gd_);
-  }
+  for (int i = 0; i < PF; ++i)
+    if (yy + i < H) step(yy + i, qc[i], qd[i]);
 }
 
 // ---------------------------------------------------------------------------
 // Launchers.  Geometry: LG = 16 for maps up to 64 wide (four boxes per wave),
 // LG = 64 up to 256 wide (a box per wave); CPL = ceil(W / LG); NG = 4 or 8
 // groups (boxes) per block, so B <= 8.  The backward adds the groups' input
-// gradients every R rows (R from an LDS budget of 2 KiB per slot set, which
-// keeps the pose-shaped maps at 32 waves per CU).
+// gradients every R <= 8 rows, as many as kSlotBytes hold.
 // ---------------------------------------------------------------------------
+// LDS for one slot set: the groups' input gradients of R rows, added after a
+// block barrier (256x256 maps, 8 boxes: a barrier every row 492 us, every
+// other row 473, every 4 rows 579, which leave one block per CU).
+constexpr size_t kSlotBytes = 20 << 10;
 struct StreamGeom { int lg, cpl, ng, R; };
 
 static bool stream_geom(int H, int W, int B, StreamGeom& g) {
@@ -605,7 +683,7 @@ static bool stream_geom(int H, int W, int B, StreamGeom& g) {
   // per-lane 32-bit byte offsets into a block's gradient maps
   if ((size_t)g.ng * H * W * 4 >= ((size_t)1 << 31)) return false;
   const size_t slot_set = (size_t)g.ng * (g.lg * g.cpl + g.lg * g.cpl / 32) * 4;
-  g.R = (int)std::max<size_t>(1, std::min<size_t>(8, (2u << 10) / slot_set));
+  g.R = (int)std::max<size_t>(1, std::min<size_t>(8, kSlotBytes / slot_set));
   return true;
 }
 
