@@ -125,7 +125,8 @@ typedef enum {
  *          12..15        zero.
  *         The 16 tap weights of the paper are the products of an x and a y
  *         weight.  box_conv_fwd and box_conv_bwd run this first, into their
- *         workspace, and read their taps from it.
+ *         workspace, and read their taps from it (small calls compute the
+ *         same taps in their kernel instead).
  * ---------------------------------------------------------------------- */
 bc_status box_prep(const float* boxes, int C, int B, unsigned flags, void* table, hipStream_t stream);
 

@@ -95,7 +95,7 @@ def _ptr(t):
         raise BoxConvError("tensors must be on the GPU")
     if not t.is_contiguous():
         raise BoxConvError("tensors must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _need(t, shape, dtypes, what, name):
@@ -106,6 +106,9 @@ def _need(t, shape, dtypes, what, name):
         return
     if not isinstance(t, torch.Tensor):
         raise BoxConvError(f"{what}: {name} must be a tensor")
+    # the common case first: a small call is bound by this marshalling
+    if (t.dtype is dtypes or (type(dtypes) is tuple and t.dtype in dtypes)) and (shape is None or t.shape == shape):
+        return
     if isinstance(dtypes, torch.dtype):
         dtypes = (dtypes,)
     if t.dtype not in dtypes:
@@ -133,13 +136,14 @@ def _maps_and_boxes(x, boxes, what):
     if not isinstance(x, torch.Tensor) or x.dim() != 4:
         raise BoxConvError(f"{what}: x must be a 4-D [N, C, H, W] tensor")
     _need(x, None, _MAPS, what, "x")
-    N, C, H, W = (int(v) for v in x.shape)
-    _need(boxes, (C, None, 4), _F32, what, "boxes")
-    return N, C, H, W, int(boxes.shape[1])
+    N, C, H, W = x.shape
+    B = boxes.shape[1] if isinstance(boxes, torch.Tensor) and boxes.dim() == 3 else None
+    _need(boxes, (C, B, 4), _F32, what, "boxes")
+    return N, C, H, W, B
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch.cuda.current_stream().cuda_stream
 
 
 def dtype_code(t: torch.Tensor) -> int:

@@ -34,6 +34,10 @@ import torch
 from . import boxconv as bc
 
 
+# Pixels (N * P) up to which a bf16 mix reads its fp32 weights directly.
+FEW_PIXELS = 4096
+
+
 @dataclasses.dataclass
 class LayerPlan:
     N: int
@@ -97,9 +101,13 @@ class LayerPlan:
             self.boxes_px = torch.empty((C, B, 4), dtype=torch.float32, device=dev)
         if self.M is not None:
             self.z = torch.empty((N, self.M, Ho, Wo), dtype=torch.int32 if integer else torch.float32, device=dev)
-            # the mix's weights in its compute type, refreshed from w every forward
+            # the mix's weights in its compute type, refreshed from w every
+            # forward; with few pixels the GEMMs round w themselves (to the
+            # same bits) for less than that launch costs (one 64x48 image,
+            # 1024 -> 256, with the binding's shorter checks: forward pass 30
+            # -> 22 us)
             self.w_c = (torch.empty((self.M, K), dtype=torch.bfloat16, device=dev)
-                        if self.compute == bc.BC_BF16 else None)
+                        if self.compute == bc.BC_BF16 and N * P > FEW_PIXELS else None)
         if self.with_backward:
             if self.split is not None:
                 self.ws_bwd = _ws(bc.split_workspace_bytes(1, N, C, H, W, B, self.split), dev)
