@@ -189,7 +189,9 @@ __global__ __launch_bounds__(kMaxT) __attribute__((amdgpu_waves_per_eu(4, 8))) v
   constexpr bool kBands = kPitch > 0 && kUp != 1;
   static_assert(kBands || kUp != 2, "half-row tables are built from bands");
   const int trows = kUp == 2 ? Ho : H;  // rows of the table (below row 0)
-  constexpr int kRows = SEG == 8 && band_cols(kPitch) == 1 ? 32 : 16;
+  // rows per band: what the walk's registers leave (two columns a lane and
+  // 8-row items: 16 rows spill 8 registers, 72x80 maps 57 us against 52)
+  constexpr int kRows = SEG == 8 ? (band_cols(kPitch) == 1 ? 32 : 8) : 16;
   BandTable<float, kRows, band_cols(kPitch)> band;
   float* part = SG + (trows + 1) * pitch;
   const int uwave = __builtin_amdgcn_readfirstlane(wave);
@@ -209,7 +211,7 @@ __global__ __launch_bounds__(kMaxT) __attribute__((amdgpu_waves_per_eu(4, 8))) v
       __syncthreads();
       if (b + 1 < B) band.load(g0 + (b + 1) * plane, H, W, uwave * kRows);
     } else if constexpr (kUp == 2) {
-      build_table_bands<float, 16, band_cols(kPitch), true>(g0 + b * gplane, SG, part, Ho, Wo, pitch, 0.f, false, W);
+      build_table_bands<float, SEG == 8 && band_cols(kPitch) == 2 ? 8 : 16, band_cols(kPitch), true>(g0 + b * gplane, SG, part, Ho, Wo, pitch, 0.f, false, W);
     } else if constexpr (kBands) {
       build_table_bands<float, kRows, band_cols(kPitch)>(g0 + b * plane, SG, part, H, W, pitch, 0.f, false);
     } else {
