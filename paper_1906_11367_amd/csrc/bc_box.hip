@@ -77,7 +77,7 @@ constexpr int kSatRowsPerWave = 4;  // rows of a strip each wave loads before sc
 // kUp: x is [maps][Ho][Wo] and the table is that of its zero-upsampled H x W
 // map (x[i][j] at (s*i, s*j)); mean must then be null.
 // KM: elements per lane in a row scan, K = ceil(W / 64) <= KM (4 for
-// W <= 256, else 16).  kGroups > 1 (W <= 256, few maps): blocks of
+// W <= 256, 8 for W <= 512, else 16).  kGroups > 1 (W <= 256, few maps): blocks of
 // 256 * kGroups threads take strips of kStrip * kGroups rows, and the column
 // pass runs kGroups row groups of kStrip rows in parallel, each starting from
 // the carried sums plus the totals of the groups above it.
@@ -144,7 +144,7 @@ __global__ __launch_bounds__(256 * kGroups) void k_sat_build(const T* __restrict
           v[k] = run;
         }
       }
-      const T excl = wave_excl_scan(run, lane);
+      const T excl = group_excl<64, false>(run);
 #pragma unroll
       for (int k = 0; k < KM; ++k) {
         const int idx = lane * K + k;
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(256 * kGroups) void k_sat_build(const T* __restrict
             v[i][k] = run;
           }
         }
-        const T excl = wave_excl_scan(run, lane);
+        const T excl = group_excl<64, false>(run);
         if (rr < rows) {
 #pragma unroll
           for (int k = 0; k < KM; ++k) {
@@ -437,11 +437,8 @@ hipError_t launch_unit_params(int op, const float* in, int n, float mw, float mh
 // blocks of 1024 threads over 64-row strips; wider ones (fewer than 4 blocks
 // per CU), with scratch for the column sums of each band, are divided over
 // enough blocks for 8 per CU (one block walks the strips of its map one after
-// another, 9 us each: 2 x 32 maps of 288x384 157 us, divided XX us).
-#ifndef SATB
-#define SATB 2048
-#endif
-constexpr int kSatBandMaps = 1024, kSatBandBlocks = SATB;
+// another, 9 us each: 2 x 32 maps of 288x384 157 us, divided 24 us).
+constexpr int kSatBandMaps = 1024, kSatBandBlocks = 2048;
 constexpr int kSatFewMaps = 2048;
 
 template <typename T, bool kUp>
@@ -459,15 +456,20 @@ static void sat_build_t(const T* x, T* sat, float* mean, int maps, int H, int W,
       hipLaunchKernelGGL(k_map_mean, dim3(maps), dim3(1024), 0, s, reinterpret_cast<const float*>(x), mean, H * W);
     hipLaunchKernelGGL((k_sat_bands<T, kUp>), dim3(pad8(total)), dim3(256), 0, s, x, bands, mean, H, W, stride, Ho, Wo,
                        nb, band_rows, total);
-    hipLaunchKernelGGL((k_sat_build<T, kUp, kSatMaxK, 1, true>), dim3(pad8(total)), dim3(256),
-                       (size_t)kStrip * W * 4, s, x, sat, mean, H, W, stride, Ho, Wo, bands, nb, band_rows, total);
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(pad8(total)), dim3(256), (size_t)kStrip * W * 4, s, x, sat, mean, H, W, stride, Ho,
+                         Wo, (const T*)bands, nb, band_rows, total);
+    };
+    if (W <= 512) go(k_sat_build<T, kUp, 8, 1, true>);
+    else go(k_sat_build<T, kUp, kSatMaxK, 1, true>);
     return;
   }
   auto go = [&](auto kernel, int groups) {
     hipLaunchKernelGGL(kernel, dim3(maps), dim3(256 * groups), (size_t)kStrip * groups * W * 4, s, x, sat, mean, H, W,
                        stride, Ho, Wo, (const T*)nullptr, 1, 0, 0);
   };
-  if (W > 256) go(k_sat_build<T, kUp, kSatMaxK, 1>, 1);
+  if (W > 512) go(k_sat_build<T, kUp, kSatMaxK, 1>, 1);
+  else if (W > 256) go(k_sat_build<T, kUp, 8, 1>, 1);
   else if (maps < kSatFewMaps && !kUp) go(k_sat_build<T, kUp, 4, kUp ? 1 : 4>, 4);
   else go(k_sat_build<T, kUp, 4, 1>, 1);
 }
