@@ -20,8 +20,8 @@ OUT = os.path.join(PKG, "libboxconv.so")
 BUILD = os.path.join(PKG, "_build")
 ARCH = "gfx950"
 
-SOURCES = ["bc_api.cpp", "bc_box.hip", "bc_box_lds.hip", "bc_box_split.hip", "bc_mix.hip", "bc_mix_pipe.hip",
-           "bc_noalloc.hip", "bc_stream.hip"]
+SOURCES = ["bc_api.cpp", "bc_box.hip", "bc_box_lds.hip", "bc_box_split.hip", "bc_mix.hip", "bc_mix_direct.hip",
+           "bc_mix_pipe.hip", "bc_noalloc.hip", "bc_stream.hip"]
 
 
 def hipcc() -> str:

@@ -134,6 +134,11 @@ hipError_t launch_mix_fwd_pipe(const void* w, const void* in, float* out, int N,
 bool mix_wgrad_pipe_takes(const void* grad, const void* in, int N, int M, int K, int P);
 hipError_t launch_mix_wgrad_pipe(const void* grad, const void* in, float* part, int N, int M, int K, int P, int sp,
                                  int chunk, hipStream_t s);
+// FWD and BWD_DATA in fp32 without LDS (bc_mix_direct.hip): whether it takes
+// the request, and the launch (relu: of the output, or of aux for BWD_DATA).
+bool mix_f32_direct_takes(bool fwd, int N, int M, int K, int P);
+hipError_t launch_mix_f32_direct(bool fwd, const float* w, const float* b, const float* aux, float* out, int N, int M,
+                                 int K, int P, int relu, hipStream_t s);
 size_t mix_workspace_bytes(int mode, int N, int M, int K, int P, int compute_dt);
 hipError_t launch_cast_bf16(const float* src, void* dst, size_t n, hipStream_t s);
 hipError_t launch_relu_cast_bf16(const float* g, const float* aux, void* dst, size_t n, hipStream_t s);

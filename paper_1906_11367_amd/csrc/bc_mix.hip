@@ -879,13 +879,11 @@ __global__ __launch_bounds__(256) void k_mix_reduce_few(const float4* __restrict
 // Tile side of a GEMM of rows x cols outputs over zt images (or splits): 64
 // where 128-wide tiles would leave CUs without a block or spend a third of
 // their rows on padding.
-#ifndef MIXB
-#define MIXB 512
-#endif
+constexpr long kMixFillBlocks = 512;  // two on each of 256 CUs
 static int mix_tile(int rows, int cols, long zt) {
   const long t128 = (long)((rows + 127) / 128) * ((cols + 127) / 128);
   const long t64 = (long)((rows + 63) / 64) * ((cols + 63) / 64);
-  if (t128 * zt < MIXB) return 64;
+  if (t128 * zt < kMixFillBlocks) return 64;
   return 3 * t64 <= 8 * t128 ? 64 : 128;  // a third or more of the area is padding
 }
 
@@ -965,6 +963,11 @@ static hipError_t launch_mix_t(int mode, const void* a, int a_dt, const void* b,
       if (a_dt == 2 && b_dt == 2 && out_dt == 1 && mix_fwd_pipe_takes(a, b, N, M, K, P))
         return launch_mix_fwd_pipe(a, b, (float*)out, N, M, K, P, relu, s);
     }
+    if constexpr (!BF16) {
+      if (a_dt == 1 && b_dt == 1 && out_dt == 1 && mix_tile(M, P, N) == 64 &&
+          mix_f32_direct_takes(true, N, M, K, P))
+        return launch_mix_f32_direct(true, (const float*)a, (const float*)b, nullptr, (float*)out, N, M, K, P, relu, s);
+    }
     with_dt<BF16>(a_dt, [&](auto ad) {
       with_dt<BF16>(b_dt, [&](auto bd) {
         gemm_launch<BF16, decltype(ad)::value, true, false, decltype(bd)::value, false, false>(
@@ -993,6 +996,10 @@ static hipError_t launch_mix_t(int mode, const void* a, int a_dt, const void* b,
                            shm, s, (const uint4*)ws, b, aux, (float*)out, M, K, P, ms, nstrips);
     });
     return hipGetLastError();
+  }
+  if constexpr (!BF16) {
+    if (mode == 1 && a_dt == 1 && b_dt == 1 && out_dt == 1 && mix_f32_direct_takes(false, N, M, K, P))
+      return launch_mix_f32_direct(false, (const float*)a, (const float*)b, aux, (float*)out, N, M, K, P, relu, s);
   }
   if (mode == 1) {
     // C = out[n] (K x P): A(i=k, l=m) = w[m][k] (k contiguous), B(l=m, j=p) = grad[n][m][p]

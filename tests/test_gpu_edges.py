@@ -181,6 +181,34 @@ def test_mix_edges(dims, compute):
     check(host(dw), refw, RTOL_F32, "dW")
 
 
+# (N, M, K, P) around the fp32 kernel without LDS: one group of 8 reduction
+# indices, less, and tails of 1 to 7; one element more or less than a 32-wide
+# tile; one and two column tiles a wave; the first size past K <= 128, M <= 48.
+DIRECT = [(1, 1, 4, 1), (2, 7, 8, 31), (1, 33, 12, 33), (3, 32, 60, 64), (2, 31, 100, 65), (2, 48, 128, 97),
+          (2, 49, 128, 96), (2, 48, 129, 96), (2, 47, 36, 50), (16, 40, 44, 2100), (1, 3, 50, 40), (5, 64, 20, 4097)]
+
+
+@pytest.mark.parametrize("dims", DIRECT)
+def test_mix_f32_short(dims):
+    N, M, K, P = dims
+    say(f"mix f32 short {dims}")
+    gen = torch.Generator(device="cuda").manual_seed(12)
+    w = torch.randn(M, K, generator=gen, device="cuda") / K ** 0.5
+    o = torch.randn(N, K, P, generator=gen, device="cuda")
+    gz = torch.randn(N, M, P, generator=gen, device="cuda")
+    z, do = torch.empty(N, M, P, device="cuda"), torch.empty(N, K, P, device="cuda")
+    ref = np.matmul(host(w)[None].astype(np.float64), host(o).astype(np.float64))
+    for relu in (1, 0):
+        z.fill_(float("nan"))
+        bc.pointwise_mix(bc.BC_MIX_FWD, w, o, z, N, M, K, P, bc.BC_F32, relu=relu)
+        check(host(z), np.maximum(ref, 0) if relu else ref, RTOL_F32, f"Z relu={relu}")
+    for relu in (0, 1):
+        g = np.where(host(z) > 0, host(gz), 0) if relu else host(gz)
+        do.fill_(float("nan"))
+        bc.pointwise_mix(bc.BC_MIX_BWD_DATA, w, gz, do, N, M, K, P, bc.BC_F32, relu=relu, aux=z if relu else None)
+        check(host(do), np.matmul(host(w).T[None].astype(np.float64), g.astype(np.float64)), RTOL_F32, f"dO relu={relu}")
+
+
 @pytest.mark.parametrize("dims", [(2, 72, 97, 243), (24, 200, 64, 1032), (2, 140, 130, 640)])
 def test_mix_keeps_a_nan_in_its_place(dims):
     """A NaN in one row of an operand, next to a tile's or a row's end, reaches
