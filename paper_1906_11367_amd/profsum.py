@@ -48,7 +48,7 @@ def _csv(dir_, suffix):
 
 
 def short(name):
-    return name.replace("void ", "").split("(")[0]
+    return name.replace("void ", "").replace("(anonymous namespace)::", "").split("(")[0]
 
 
 def counters(dir_):
