@@ -378,6 +378,11 @@ def bc_cast_bf16(src: torch.Tensor, dst: torch.Tensor):
     return dst
 
 
+def need_weights(w: torch.Tensor, n: int):
+    """The checks bc_cast_bf16 makes of n fp32 weights, where no cast is made."""
+    _need_numel(w, n, _F32, "pointwise_mix", "w")
+
+
 def relu_grad_bf16(grad: torch.Tensor, out: torch.Tensor, dst: torch.Tensor):
     """dst (bf16) = bf16(out > 0 ? grad : 0): the ReLU backward in the mix's compute type."""
     if not (grad.numel() == out.numel() == dst.numel()):

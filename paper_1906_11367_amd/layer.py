@@ -34,8 +34,10 @@ import torch
 from . import boxconv as bc
 
 
-# Pixels (N * P) up to which a bf16 mix reads its fp32 weights directly.
+# Pixels (N * P) and weights (M * K) up to which a bf16 mix without a backward
+# reads its fp32 weights directly.
 FEW_PIXELS = 4096
+FEW_WEIGHTS = 1 << 18
 
 
 @dataclasses.dataclass
@@ -102,12 +104,18 @@ class LayerPlan:
         if self.M is not None:
             self.z = torch.empty((N, self.M, Ho, Wo), dtype=torch.int32 if integer else torch.float32, device=dev)
             # the mix's weights in its compute type, refreshed from w every
-            # forward; with few pixels the GEMMs round w themselves (to the
-            # same bits) for less than that launch costs (one 64x48 image,
-            # 1024 -> 256, with the binding's shorter checks: forward pass 30
-            # -> 22 us)
+            # forward; the backward uses this copy, so an update of w between
+            # the two does not reach it.  A plan without a backward and with
+            # few pixels and weights needs no copy: its GEMM rounds w itself
+            # (to the same bits) for less than that launch costs the host (one
+            # 64x48 image, 1024 -> 256, with the binding's shorter checks:
+            # forward pass 30 -> 22 us).  With more weights the rounding in
+            # every tile costs more than the copy (kernel time with and
+            # without it: 1024 -> 256 on 4096 pixels 13.7 and 14.1 us, 2048 ->
+            # 512 on 3072 25 and 28, 2048 -> 2048 on 4096 44 and 54).
             self.w_c = (torch.empty((self.M, K), dtype=torch.bfloat16, device=dev)
-                        if self.compute == bc.BC_BF16 and N * P > FEW_PIXELS else None)
+                        if self.compute == bc.BC_BF16 and not (not self.with_backward and N * P <= FEW_PIXELS
+                                                               and self.M * K <= FEW_WEIGHTS) else None)
         if self.with_backward:
             if self.split is not None:
                 self.ws_bwd = _ws(bc.split_workspace_bytes(1, N, C, H, W, B, self.split), dev)
@@ -157,6 +165,8 @@ class LayerPlan:
         if self.w_c is not None:
             bc.bc_cast_bf16(w, self.w_c)
             w = self.w_c
+        elif self.compute == bc.BC_BF16:
+            bc.need_weights(w, self.M * self.K)   # fp32 weights only, as the copy takes them
         bc.pointwise_mix(bc.BC_MIX_FWD, w, self.o, self.z, self.N, self.M, self.K, self.P, self.compute,
                          relu=int(self.relu))
         tap("mix_fwd")

@@ -13,6 +13,7 @@ import torch
 
 import oracle as O
 from paper_1906_11367_amd import boxconv as bc
+from paper_1906_11367_amd.layer import LayerPlan
 from test_gpu_parity import RTOL_F32, check, dev, host, real_boxes, say
 
 pytestmark = pytest.mark.gpu
@@ -237,3 +238,36 @@ def test_mix_keeps_a_nan_in_its_place(dims):
     bad[0, 1, 0] = float("nan")
     hit = mix(bc.BC_MIX_BWD_WEIGHT, bad, o, dw)
     assert hit[1].all() and int(hit.sum()) == K
+
+
+@pytest.mark.parametrize("H,W", [(16, 24), (72, 64)])
+def test_backward_uses_the_weights_of_the_forward(H, W):
+    """Below and above the pixels up to which a plan may go without its rounded
+    copy of the weights: an update of w between forward and backward does not
+    reach the backward, which needs no w at all with a bf16 mix."""
+    N, C, B, M = 1, 4, 2, 8
+    x, bx, _ = case(H + W, N, C, H, W, B)
+    rng = np.random.default_rng(4)
+    xd, bd = dev(x), dev(bx)
+    w = dev(rng.standard_normal((M, C * B)).astype(np.float32))
+    gz = dev(rng.standard_normal((N, M, H, W)).astype(np.float32))
+    plan = LayerPlan(N, C, H, W, B, M, torch.float32, "bf16", relu=True)
+    plan.forward(xd, bd, w)
+    want = [t.clone() for t in plan.backward(xd, bd, w, gz)]
+    w.mul_(-2.0)
+    for given in (w, None):
+        plan.dx.fill_(float("nan"))
+        assert all(torch.equal(a, b) for a, b in zip(plan.backward(xd, bd, given, gz), want))
+
+
+@pytest.mark.parametrize("H,W", [(16, 24), (72, 64)])
+@pytest.mark.parametrize("backward", [False, True])
+def test_bf16_mix_takes_fp32_weights_only(H, W, backward):
+    N, C, B, M = 1, 4, 2, 8
+    x, bx, _ = case(H + W, N, C, H, W, B)
+    plan = LayerPlan(N, C, H, W, B, M, torch.float32, "bf16", with_backward=backward)
+    w = torch.zeros((M, C * B), device="cuda")
+    plan.forward(dev(x), dev(bx), w)
+    for bad in (w.bfloat16(), w.int(), w[:, 1:].contiguous()):
+        with pytest.raises(bc.BoxConvError):
+            plan.forward(dev(x), dev(bx), bad)
