@@ -45,7 +45,7 @@ __device__ __forceinline__ i32x4_t buf_desc(const void* p, uint32_t bytes) {
 __device__ __forceinline__ void load_to_lds(const i32x4_t& rs, uint32_t voff, uint32_t soff, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 1\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                ::"s"(lds), "v"(voff), "s"(rs), "s"(soff)
-               : "memory");
+               : "memory", "m0");
 }
 
 // Waits until at most kLeft of the wave's memory operations are pending, and
