@@ -34,43 +34,54 @@ __device__ __forceinline__ uint32_t ld_bits(const char* base, size_t idx) {
   else return reinterpret_cast<const uint32_t*>(base)[idx];
 }
 
-// kBytes from memory of the element type's own alignment (2 or 4 bytes): one
+// Loaded data is kept in registers as loaded, in vectors of the load's width:
+// the values of a load in flight then stay one register tuple, where words
+// taken apart are copied out of it, which waits for the load.
+template <int N> using Words = uint32_t __attribute__((ext_vector_type(N)));
+
+// N words from memory of the element type's own alignment (2 or 4 bytes): one
 // wide load, which global memory accesses may be at any alignment here, so
 // that rows of an odd length cost no more instructions than aligned ones.
-template <int kBytes, int kAlign> struct __attribute__((packed, aligned(kAlign))) Bytes { uint32_t w[kBytes / 4]; };
+template <int N, int kAlign> struct __attribute__((packed, aligned(kAlign))) Bytes { uint32_t w[N]; };
 
-// N consecutive elements as stored: N words, or N / 2 packed pairs of bf16.
 template <int DT, int N>
-__device__ __forceinline__ void ld_vec(const char* base, size_t idx, uint32_t* w) {
-  constexpr int kSize = N * StoreBytes<DT>::v;
-  const auto t = *reinterpret_cast<const Bytes<kSize, StoreBytes<DT>::v>*>(base + idx * StoreBytes<DT>::v);
-#pragma unroll
-  for (int k = 0; k < kSize / 4; ++k) w[k] = t.w[k];
+__device__ __forceinline__ Words<N> ld_wide(const char* base, size_t idx) {
+  return __builtin_bit_cast(Words<N>, *reinterpret_cast<const Bytes<N, StoreBytes<DT>::v>*>(base + idx * StoreBytes<DT>::v));
 }
 
-// The same, element by element, those from `avail` on 0: for the last
-// elements of an operand, which a wide load would run past.
+// The same N words element by element, elements from `avail` on 0: for the
+// last elements of an operand, which a wide load would run past.
 template <int DT, int N>
-__device__ __forceinline__ void ld_few(const char* base, size_t idx, int avail, uint32_t* w) {
+__device__ __forceinline__ Words<N> ld_few(const char* base, size_t idx, int avail) {
+  Words<N> w;
 #pragma unroll
   for (int k = 0; k < N; ++k) {
-    const uint32_t b = k < avail ? ld_bits<DT>(base, idx + k) : 0u;
-    if constexpr (DT != 2) w[k] = b;
-    else if (k & 1) w[k / 2] |= b << 16;
-    else w[k / 2] = b;
+    if constexpr (DT == 2) {
+      const uint32_t lo = 2 * k < avail ? ld_bits<DT>(base, idx + 2 * k) : 0u;
+      const uint32_t hi = 2 * k + 1 < avail ? ld_bits<DT>(base, idx + 2 * k + 1) : 0u;
+      w[k] = lo | (hi << 16);
+    } else {
+      w[k] = k < avail ? ld_bits<DT>(base, idx + k) : 0u;
+    }
   }
+  return w;
 }
 
-// N consecutive elements as raw bits (one 32-bit word per element; bf16 in
-// the low half), of which `avail` lie in the operand; `wide`: all N lie in its
-// memory (whatever row they belong to).
+// N words at element idx, of which `avail` elements lie in the operand;
+// `wide`: all of them lie in its memory (whatever row they belong to).
 template <int DT, int N>
-__device__ __forceinline__ void ld_run(const char* base, size_t idx, bool wide, int avail, uint32_t* w) {
-  uint32_t t[DT == 2 ? N / 2 : N];
-  if (wide) ld_vec<DT, N>(base, idx, t);
-  else ld_few<DT, N>(base, idx, avail, t);
-#pragma unroll
-  for (int k = 0; k < N; ++k) w[k] = DT == 2 ? ((k & 1) ? t[k / 2] >> 16 : t[k / 2] & 0xffffu) : t[k];
+__device__ __forceinline__ Words<N> ld_run(const char* base, size_t idx, bool wide, int avail) {
+  Words<N> w;
+  if (wide) w = ld_wide<DT, N>(base, idx);
+  else w = ld_few<DT, N>(base, idx, avail);
+  return w;
+}
+
+// Element k of stored words, as raw bits (bf16 in the low half).
+template <int DT, int N>
+__device__ __forceinline__ uint32_t word_bits(const Words<N>& w, int k) {
+  if constexpr (DT == 2) return (k & 1) ? w[k / 2] >> 16 : w[k / 2] & 0xffffu;
+  else return w[k];
 }
 
 // Buffer-resource loads: a wave-uniform descriptor of one operand (base and
@@ -78,36 +89,11 @@ __device__ __forceinline__ void ld_run(const char* base, size_t idx, bool wide, 
 // byte offset and a wave-uniform byte offset.
 constexpr int kBufWord3 = 0x00020000;  // raw 32-bit data, no format conversion
 
-__device__ __forceinline__ uint4 buf_ld16(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-  const auto q = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0);
-  return make_uint4(q[0], q[1], q[2], q[3]);
-}
-__device__ __forceinline__ uint2 buf_ld8(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-  const auto q = __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, (int)soff, 0);
-  return make_uint2(q[0], q[1]);
-}
-
-// N consecutive elements through a buffer descriptor, as raw bits (one word
-// per element; bf16 in the low half).
-template <int DT, int N>
-__device__ __forceinline__ void buf_run(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, uint32_t* w) {
-  if constexpr (DT == 2) {
-    if constexpr (N == 8) {
-      const uint4 q = buf_ld16(r, voff, soff);
-      const uint32_t p[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-      for (int k = 0; k < 4; ++k) { w[2 * k] = p[k] & 0xffffu; w[2 * k + 1] = p[k] >> 16; }
-    } else {
-      const uint2 q = buf_ld8(r, voff, soff);
-      w[0] = q.x & 0xffffu; w[1] = q.x >> 16; w[2] = q.y & 0xffffu; w[3] = q.y >> 16;
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < N; k += 4) {
-      const uint4 q = buf_ld16(r, voff, soff + k * 4);
-      w[k] = q.x; w[k + 1] = q.y; w[k + 2] = q.z; w[k + 3] = q.w;
-    }
-  }
+template <int N>
+__device__ __forceinline__ Words<N> buf_ld(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+  static_assert(N == 2 || N == 4, "8 or 16 bytes");
+  if constexpr (N == 4) return __builtin_bit_cast(Words<N>, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0));
+  else return __builtin_bit_cast(Words<N>, __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, (int)soff, 0));
 }
 
 // Storage bits -> fp32 value.
@@ -159,7 +145,13 @@ __device__ __forceinline__ int bf16_tile_off(int r, int l) {
 //           of one row.
 // NU units per thread.  bf16 storage without a mask is kept packed and never
 // converted.
-template <bool BF16, int DT, bool KC, bool MASK, int ROWS, int kBK>
+// kVec: the operand's rows are aligned for wide loads (vec_operand), which
+// then serve every tile, those at the operand's edges too.  A kernel takes one
+// kind of load or the other: where both write the registers of a tile in
+// flight, the compiler joins them by copies that wait for the loads as soon as
+// they are issued (fp32, 4 x 128 x 1024 x 65536 in N, M, K, P, both kinds in
+// one kernel: FWD 622 us, BWD_DATA 629; one kind each: 546 and 590).
+template <bool BF16, int DT, bool KC, bool MASK, int ROWS, int kBK, bool kVec>
 struct Stager {
   static constexpr int BK = kBK;
   static constexpr int PITCH = BF16 ? BK + 8 : BK + 1;  // elements; bf16 rows are 16-byte aligned
@@ -167,9 +159,13 @@ struct Stager {
   static constexpr int NU = KC ? (ROWS * BK / UL) / kMixThreads : (ROWS / 4) * (BK / UL) / kMixThreads;
   static_assert(NU >= 1, "every thread has a unit");
   static constexpr bool kRaw = BF16 && DT == 2 && !MASK;
-  // words of one unit: packed bf16 pairs, or one word per element
-  static constexpr int UW = KC ? (kRaw ? UL / 2 : UL) : (kRaw ? UL * 2 : 4 * UL);
-  static constexpr int NW = NU * UW;
+  static constexpr int SB = StoreBytes<DT>::v;
+  // a load: kLW words of kLE elements; kLoads of them per unit (of the mask:
+  // always 4 words, kMaskLoads per unit)
+  static constexpr int kLW = KC ? 4 : SB;
+  static constexpr int kLE = kLW * 4 / SB;
+  static constexpr int kLoads = KC ? UL / kLE : UL;
+  static constexpr int kMaskLoads = KC ? UL / 4 : UL;
   using E = typename std::conditional<BF16, uint16_t, float>::type;
 
   // Byte offset of this thread's first load inside a tile (the same for every
@@ -177,7 +173,6 @@ struct Stager {
   // are kMixThreads / (BK / UL) rows apart, non-KC rows one l apart (and
   // units kUnitL l apart).
   static constexpr int kUnitL = KC ? 0 : kMixThreads / (ROWS / 4) * UL;
-  static constexpr int SB = DT == 2 ? 2 : 4;
 
   const char* p;
   const float* mask;
@@ -185,11 +180,10 @@ struct Stager {
   int rows, depth;
   long extent;  // elements of this image's operand
   int lrem;     // reduction indices left from the loaded tile's first
-  bool vec_ok;
-  uint32_t off0;
+  uint32_t off0, end, mend;
   __amdgpu_buffer_rsrc_t rs, mrs;
-  uint32_t v[NW];
-  uint32_t m[MASK ? NW : 1];
+  Words<kLW> v[NU * kLoads];
+  Words<4> m[MASK ? NU * kMaskLoads : 1];
 
   // Offsets, and buffer descriptors covering this image's operand (and mask).
   __device__ __forceinline__ void init_offsets() {
@@ -197,179 +191,165 @@ struct Stager {
     if constexpr (KC) off0 = (uint32_t)(((long)(tid / (BK / UL)) * ld + (tid % (BK / UL)) * UL) * SB);
     else off0 = (uint32_t)(((long)((tid / (ROWS / 4)) * UL) * ld + (tid % (ROWS / 4)) * 4) * SB);
     extent = KC ? (long)(rows - 1) * ld + depth : (long)(depth - 1) * ld + rows;  // elements
-    rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(p), (short)0, (int)(extent * SB), kBufWord3);
-    if constexpr (MASK)
-      mrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(mask), (short)0, (int)(extent * 4), kBufWord3);
-  }
-  __device__ __forceinline__ long unit_step() const {
-    return KC ? (long)(kMixThreads / (BK / UL)) * ld * SB : ld * SB;
-  }
-  // Whether an image's operand fits the 32-bit byte offsets of the buffer path.
-  __device__ __forceinline__ bool buf_ok() const {
-    return extent * 4 < (1L << 31);
+    end = (uint32_t)(extent * SB);
+    mend = (uint32_t)(extent * 4);
+    rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(p), (short)0, (int)end, kBufWord3);
+    if constexpr (MASK) mrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(mask), (short)0, (int)mend, kBufWord3);
   }
 
-  // Whole tile in range and aligned: the block takes the unguarded path
-  // (the condition is uniform, so no lane diverges and the wide loads stay in
-  // flight until store() consumes them).  The unguarded path reads through
-  // the buffer descriptor: the thread's one offset plus a wave-uniform offset
-  // per K-step and unit, so no address is computed in the loop.
   __device__ __forceinline__ void load(int r0, int l0) {
     lrem = depth - l0;
-    if (vec_ok && r0 + ROWS <= rows && lrem >= BK) load_full(r0, l0);
-    else load_edge(r0, l0);
+    if constexpr (kVec) load_vec(r0, l0);
+    else load_any(r0, l0);
   }
 
-  __device__ __forceinline__ void load_full(int r0, int l0) {
+  // Through the buffer descriptor: the thread's one offset plus a wave-uniform
+  // offset per K-step and unit, so no address is computed in the loop, and no
+  // branch surrounds a load.  At the operand's edges, what lies past its end
+  // reads as 0 (the wave-uniform offset is held to its size, from which the
+  // range check subtracts it); rows past the last read the next l's values
+  // (row-contiguous) and are not stored; l past the range is zeroed when the
+  // tile is stored to LDS.  No load straddles the operand's end: its rows are
+  // whole units.
+  __device__ __forceinline__ void load_vec(int r0, int l0) {
     const uint32_t origin = (uint32_t)(KC ? (long)r0 * ld + l0 : (long)l0 * ld + r0);
-    const uint32_t step = (uint32_t)unit_step();
+    const uint32_t step = (uint32_t)(KC ? (long)(kMixThreads / (BK / UL)) * ld : ld);  // elements
     const uint32_t moff = off0 / SB * 4;
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
-      if constexpr (KC) {
-        const uint32_t so = origin * SB + u * step;
-        if constexpr (kRaw) {
-          const uint4 q = buf_ld16(rs, off0, so);
-          uint32_t* w = v + u * UW;
-          w[0] = q.x; w[1] = q.y; w[2] = q.z; w[3] = q.w;
-        } else {
-          buf_run<DT, UL>(rs, off0, so, v + u * UW);
-          if constexpr (MASK) buf_run<1, UL>(mrs, moff, origin * 4 + u * (step / SB * 4), m + u * UW);
-        }
-      } else {
 #pragma unroll
-        for (int e = 0; e < UL; ++e) {
-          const uint32_t so = origin * SB + (u * kUnitL + e) * step;
-          if constexpr (kRaw) {
-            const uint2 q = buf_ld8(rs, off0, so);
-            v[u * UW + e * 2] = q.x; v[u * UW + e * 2 + 1] = q.y;
-          } else {
-            buf_run<DT, 4>(rs, off0, so, v + u * UW + e * 4);
-            if constexpr (MASK) buf_run<1, 4>(mrs, moff, origin * 4 + (u * kUnitL + e) * (step / SB * 4), m + u * UW + e * 4);
-          }
+      for (int e = 0; e < kLoads; ++e) {
+        const uint32_t at = KC ? origin + u * step + e * kLE : origin + (u * kUnitL + e) * step;
+        v[u * kLoads + e] = buf_ld<kLW>(rs, off0, min(at * SB, end));
+      }
+      if constexpr (MASK) {
+#pragma unroll
+        for (int e = 0; e < kMaskLoads; ++e) {
+          const uint32_t at = KC ? origin + u * step + e * 4 : origin + (u * kUnitL + e) * step;
+          m[u * kMaskLoads + e] = buf_ld<4>(mrs, moff, min(at * 4, mend));
         }
       }
     }
   }
 
-  // Tiles at the operand's edges and operands of any alignment: the same wide
-  // loads from clamped addresses, unaligned.  What lies outside needs no
-  // guard where it only reaches outputs that are not stored (rows past the
-  // last: the last row again, or, row-contiguous, the next l's values); l past
-  // the range is zeroed when the tile is stored to LDS.  Only the operand's
-  // last few elements, which a wide load would run past, are read one by one.
-  __device__ __forceinline__ void load_edge(int r0, int l0) {
+  // Operands of any alignment: the same wide loads from clamped addresses.
+  // What lies outside needs no guard where it only reaches outputs that are
+  // not stored (rows past the last: the last row again, or, row-contiguous,
+  // the next l's values); l past the range is zeroed when the tile is stored
+  // to LDS.  Only the operand's last few elements, which a wide load would run
+  // past, are read one by one.
+  __device__ __forceinline__ void load_any(int r0, int l0) {
     const int tid = threadIdx.x;
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
+      const int unit = tid + u * kMixThreads;
       if constexpr (KC) {
-        const int unit = tid + u * kMixThreads;
         const int r = min(r0 + unit / (BK / UL), rows - 1), l = l0 + (unit % (BK / UL)) * UL;
-        const long idx = (long)r * ld + min(l, depth - 1);
-        load_unit<UL>(idx, min(UL, depth - l), v + u * UW, m + (MASK ? u * UW : 0));
+        const long row = (long)r * ld;
+#pragma unroll
+        for (int e = 0; e < kLoads; ++e) {
+          const long idx = row + min(l + e * kLE, depth - 1);
+          v[u * kLoads + e] = ld_run<DT, kLW>(p, idx, idx + kLE <= extent, depth - l - e * kLE);
+        }
+        if constexpr (MASK) {
+#pragma unroll
+          for (int e = 0; e < kMaskLoads; ++e) {
+            const long idx = row + min(l + e * 4, depth - 1);
+            m[u * kMaskLoads + e] = ld_run<1, 4>(reinterpret_cast<const char*>(mask), idx, idx + 4 <= extent, depth - l - e * 4);
+          }
+        }
       } else {
-        const int unit = tid + u * kMixThreads;
         const int r = r0 + (unit % (ROWS / 4)) * 4, lb = l0 + (unit / (ROWS / 4)) * UL;
 #pragma unroll
         for (int e = 0; e < UL; ++e) {
           const long idx = (long)min(lb + e, depth - 1) * ld + min(r, rows - 1);
-          load_unit<4>(idx, rows - r, v + u * UW + e * (UW / UL), m + (MASK ? u * UW + e * 4 : 0));
+          v[u * UL + e] = ld_run<DT, kLW>(p, idx, idx + 4 <= extent, rows - r);
+          if constexpr (MASK) m[u * UL + e] = ld_run<1, 4>(reinterpret_cast<const char*>(mask), idx, idx + 4 <= extent, rows - r);
         }
       }
     }
   }
 
-  template <int N>
-  __device__ __forceinline__ void load_unit(long idx, int avail, uint32_t* w, uint32_t* mw) const {
-    const bool wide = idx + N <= extent;
-    if constexpr (kRaw) {
-      if (wide) ld_vec<DT, N>(p, idx, w);
-      else ld_few<DT, N>(p, idx, avail, w);
-    } else {
-      ld_run<DT, N>(p, idx, wide, avail, w);
-      if constexpr (MASK) ld_run<1, N>(reinterpret_cast<const char*>(mask), idx, wide, avail, mw);
-    }
+  // Element k of unit u (KC: l of the unit; else element i of its l = e).
+  __device__ __forceinline__ float f_kc(int u, int k) const {
+    return operand_f32<DT, MASK>(word_bits<DT, kLW>(v[u * kLoads + k / kLE], k % kLE), MASK ? m[u * kMaskLoads + k / 4][k % 4] : 0u);
+  }
+  __device__ __forceinline__ float f_rc(int u, int e, int i) const {
+    return operand_f32<DT, MASK>(word_bits<DT, kLW>(v[u * kLoads + e], i), MASK ? m[u * kMaskLoads + e][i] : 0u);
   }
 
-  // Zeroes the loaded values of reduction indices past the range.
-  __device__ __forceinline__ void zero_past() {
+  // kTail: the tile reaches past the reduction's end; what lies there is
+  // stored as 0.
+  template <bool kTail>
+  __device__ __forceinline__ void store(E* T) const {
     const int tid = threadIdx.x;
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
+      const int unit = tid + u * kMixThreads;
       if constexpr (KC) {
-        const int left = lrem - (tid % (BK / UL)) * UL;
-#pragma unroll
-        for (int k = 0; k < UW; ++k) {
-          if constexpr (kRaw) v[u * UW + k] &= left >= 2 * k + 2 ? 0xffffffffu : left == 2 * k + 1 ? 0xffffu : 0u;
-          else v[u * UW + k] = left > k ? v[u * UW + k] : 0u;
-        }
-      } else {
-        const int left = lrem - (tid / (ROWS / 4)) * UL - u * kUnitL;
-#pragma unroll
-        for (int e = 0; e < UL; ++e)
-#pragma unroll
-          for (int k = 0; k < UW / UL; ++k) v[u * UW + e * (UW / UL) + k] = left > e ? v[u * UW + e * (UW / UL) + k] : 0u;
-      }
-    }
-  }
-
-  __device__ __forceinline__ uint32_t mk(int i) const { return MASK ? m[i] : 0u; }
-  __device__ __forceinline__ float f(int i) const { return operand_f32<DT, MASK>(v[i], mk(i)); }
-
-  __device__ __forceinline__ void store(E* T) {
-    const int tid = threadIdx.x;
-    if (lrem < BK) zero_past();
-#pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      const int unit = tid + u * kMixThreads, b = u * UW;
-      if constexpr (KC) {
-        const int r = unit / (BK / UL), l = (unit % (BK / UL)) * UL;
+        const int r = unit / (BK / UL), l = (unit % (BK / UL)) * UL, left = lrem - l;
+        auto at = [&](int k) { return !kTail || left > k ? f_kc(u, k) : 0.f; };
         if constexpr (BF16) {
-          uint4 q;
+          Words<4> q;
           if constexpr (kRaw) {
-            q.x = v[b + 0]; q.y = v[b + 1]; q.z = v[b + 2]; q.w = v[b + 3];
+            q = v[u];
+            if constexpr (kTail) {
+#pragma unroll
+              for (int k = 0; k < 4; ++k) q[k] &= left >= 2 * k + 2 ? 0xffffffffu : left == 2 * k + 1 ? 0xffffu : 0u;
+            }
           } else {
-            q.x = pack2_bf16(f(b + 0), f(b + 1)); q.y = pack2_bf16(f(b + 2), f(b + 3));
-            q.z = pack2_bf16(f(b + 4), f(b + 5)); q.w = pack2_bf16(f(b + 6), f(b + 7));
+#pragma unroll
+            for (int k = 0; k < 4; ++k) q[k] = pack2_bf16(at(2 * k), at(2 * k + 1));
           }
-          *reinterpret_cast<uint4*>(T + bf16_tile_off<PITCH>(r, l)) = q;
+          *reinterpret_cast<Words<4>*>(T + bf16_tile_off<PITCH>(r, l)) = q;
         } else {
           E* dst = T + r * PITCH + l;
 #pragma unroll
-          for (int k = 0; k < UL; ++k) dst[k] = f(b + k);
+          for (int k = 0; k < UL; ++k) dst[k] = at(k);
         }
       } else {
-        const int r = (unit % (ROWS / 4)) * 4, lb = (unit / (ROWS / 4)) * UL;
+        const int r = (unit % (ROWS / 4)) * 4, lb = (unit / (ROWS / 4)) * UL, left = lrem - lb;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
+          auto at = [&](int e) { return !kTail || left > e ? f_rc(u, e, i) : 0.f; };
           if constexpr (BF16) {
-            uint4 q;
+            Words<4> q;
             if constexpr (kRaw) {
               // element i of rows (l, l+1) -> one packed word: bytes of the
               // low (i even) or high (i odd) halves of the two source words
               const uint32_t sel = (i & 1) ? 0x07060302u : 0x05040100u;
-              const int h = b + (i >> 1);
-              q.x = __builtin_amdgcn_perm(v[1 * 2 + h], v[0 * 2 + h], sel);
-              q.y = __builtin_amdgcn_perm(v[3 * 2 + h], v[2 * 2 + h], sel);
-              q.z = __builtin_amdgcn_perm(v[5 * 2 + h], v[4 * 2 + h], sel);
-              q.w = __builtin_amdgcn_perm(v[7 * 2 + h], v[6 * 2 + h], sel);
+#pragma unroll
+              for (int k = 0; k < 4; ++k) {
+                q[k] = __builtin_amdgcn_perm(v[u * UL + 2 * k + 1][i >> 1], v[u * UL + 2 * k][i >> 1], sel);
+                if constexpr (kTail) q[k] &= left >= 2 * k + 2 ? 0xffffffffu : left == 2 * k + 1 ? 0xffffu : 0u;
+              }
             } else {
-              q.x = pack2_bf16(f(b + 0 * 4 + i), f(b + 1 * 4 + i));
-              q.y = pack2_bf16(f(b + 2 * 4 + i), f(b + 3 * 4 + i));
-              q.z = pack2_bf16(f(b + 4 * 4 + i), f(b + 5 * 4 + i));
-              q.w = pack2_bf16(f(b + 6 * 4 + i), f(b + 7 * 4 + i));
+#pragma unroll
+              for (int k = 0; k < 4; ++k) q[k] = pack2_bf16(at(2 * k), at(2 * k + 1));
             }
-            *reinterpret_cast<uint4*>(T + bf16_tile_off<PITCH>(r + i, lb)) = q;
+            *reinterpret_cast<Words<4>*>(T + bf16_tile_off<PITCH>(r + i, lb)) = q;
           } else {
             E* dst = T + (r + i) * PITCH + lb;
 #pragma unroll
-            for (int e = 0; e < UL; ++e) dst[e] = f(b + e * 4 + i);
+            for (int e = 0; e < UL; ++e) dst[e] = at(e);
           }
         }
       }
     }
   }
 };
+
+// Stages the loaded tiles of both operands (the same reduction indices).
+template <typename SA, typename SB>
+__device__ __forceinline__ void store_tiles(const SA& sa, const SB& sb, typename SA::E* As, typename SB::E* Bs) {
+  if (sa.lrem < SA::BK) {
+    sa.template store<true>(As);
+    sb.template store<true>(Bs);
+  } else {
+    sa.template store<false>(As);
+    sb.template store<false>(Bs);
+  }
+}
 
 // Stores the TT x TT accumulator tiles of one wave.  OK: 0 = fp32, 1 = int32
 // (exact integer values), 3 = fp32 accumulate, 4 = fp32 with ReLU.  `full`
@@ -433,15 +413,15 @@ constexpr int mix_depth() {
   return BF16 ? 64 : 32;
 }
 
-template <bool BF16, int ADT, bool AKC, bool AMASK, int BDT, bool BKC, bool BMASK, int kTile>
+template <bool BF16, int ADT, bool AKC, bool AMASK, int BDT, bool BKC, bool BMASK, int kTile, bool kVecA, bool kVecB>
 __global__ __launch_bounds__(kMixThreads)
 __attribute__((amdgpu_waves_per_eu(kTile == 64 ? 3 : mix_waves<BF16, ADT, AKC, AMASK, BDT, BKC, BMASK>(), 8))) void k_mix_gemm(
     const void* __restrict__ a, const void* __restrict__ b, const float* __restrict__ aux, void* __restrict__ out,
     int rows, int cols, int depth, long lda, long ldb, long ldc, long a_bs, long b_bs, long c_bs,
     int mt, int nt, int zt, int nsplit_p, int pchunk, int out_kind, int relu) {
   constexpr int kDepth = mix_depth<BF16, ADT, AKC, AMASK, BDT, BKC, BMASK, kTile>();
-  using SA = Stager<BF16, ADT, AKC, AMASK, kTile, kDepth>;
-  using SB = Stager<BF16, BDT, BKC, BMASK, kTile, kDepth>;
+  using SA = Stager<BF16, ADT, AKC, AMASK, kTile, kDepth, kVecA>;
+  using SB = Stager<BF16, BDT, BKC, BMASK, kTile, kDepth, kVecB>;
   constexpr int BK = SA::BK, PITCH = SA::PITCH;
   constexpr int TT = kTile / 64, kSub = kTile / 2;  // 32 x 32 tiles and rows per wave, each way
   using E = typename SA::E;
@@ -468,16 +448,12 @@ __attribute__((amdgpu_waves_per_eu(kTile == 64 ? 3 : mix_waves<BF16, ADT, AKC, A
   sa.p = reinterpret_cast<const char*>(a) + (size_t)n * a_bs * StoreBytes<ADT>::v;
   sa.mask = AMASK ? aux + (size_t)n * a_bs : nullptr;
   sa.ld = lda; sa.rows = rows; sa.depth = depth;
-  sa.vec_ok = (lda & 7) == 0 && ((uintptr_t)sa.p & 15) == 0 && (!AMASK || ((uintptr_t)sa.mask & 15) == 0);
   SB sb;
   sb.p = reinterpret_cast<const char*>(b) + (size_t)n * b_bs * StoreBytes<BDT>::v;
   sb.mask = BMASK ? aux + (size_t)n * b_bs : nullptr;
   sb.ld = ldb; sb.rows = cols; sb.depth = depth;
-  sb.vec_ok = (ldb & 7) == 0 && ((uintptr_t)sb.p & 15) == 0 && (!BMASK || ((uintptr_t)sb.mask & 15) == 0);
   sa.init_offsets();
   sb.init_offsets();
-  sa.vec_ok = sa.vec_ok && sa.buf_ok();
-  sb.vec_ok = sb.vec_ok && sb.buf_ok();
   // loads stop at this block's reduction range (a split chunk need not be a
   // whole number of K-steps; the descriptors keep the operand's extent)
   sa.depth = l_end;
@@ -497,8 +473,7 @@ __attribute__((amdgpu_waves_per_eu(kTile == 64 ? 3 : mix_waves<BF16, ADT, AKC, A
   if (l_begin < l_end) {
     sa.load(i0, l_begin);
     sb.load(j0, l_begin);
-    sa.store(As);
-    sb.store(Bs);
+    store_tiles(sa, sb, As, Bs);
     __syncthreads();
   }
   for (int l0 = l_begin; l0 < l_end; l0 += BK) {
@@ -540,8 +515,7 @@ __attribute__((amdgpu_waves_per_eu(kTile == 64 ? 3 : mix_waves<BF16, ADT, AKC, A
     }
     __syncthreads();
     if (more) {
-      sa.store(As);
-      sb.store(Bs);
+      store_tiles(sa, sb, As, Bs);
       __syncthreads();
     }
   }
@@ -642,16 +616,17 @@ __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(3, 
         const int m = m0 + e;
         const int avail = m < M ? max(0, min(4, P - pp)) : 0;
         const size_t idx = avail > 0 ? (size_t)m * P + pp : 0;
-        uint32_t raw[4], mk[4] = {0u, 0u, 0u, 0u};
         // columns past P are not stored, so only the image's last elements
         // need the narrow loads (any P: the wide ones may be unaligned)
         const bool wide = avail > 0 && idx + 4 <= plane;
-        ld_run<BDT, 4>(gb, idx, wide, avail, raw);
-        if constexpr (BMASK) ld_run<1, 4>(reinterpret_cast<const char*>(mb), idx, wide, avail, mk);
+        const Words<StoreBytes<BDT>::v> raw = ld_run<BDT, StoreBytes<BDT>::v>(gb, idx, wide, avail);
+        Words<4> mk = {0u, 0u, 0u, 0u};
+        if constexpr (BMASK) mk = ld_run<1, 4>(reinterpret_cast<const char*>(mb), idx, wide, avail);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          if constexpr (BDT == 2 && !BMASK) v[e][i] = raw[i] & 0xffffu;
-          else v[e][i] = i < avail ? (pack2_bf16(operand_f32<BDT, BMASK>(raw[i], mk[i]), 0.f) & 0xffffu) : 0u;
+          const uint32_t bits = word_bits<BDT, StoreBytes<BDT>::v>(raw, i);
+          if constexpr (BDT == 2 && !BMASK) v[e][i] = bits;
+          else v[e][i] = i < avail ? (pack2_bf16(operand_f32<BDT, BMASK>(bits, mk[i]), 0.f) & 0xffffu) : 0u;
         }
       }
 #pragma unroll
@@ -677,13 +652,13 @@ __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(3, 
                                                                       (int)((size_t)wt_ksteps(K) * msteps * 1024), kBufWord3);
   const __amdgpu_buffer_rsrc_t orr = __builtin_amdgcn_make_buffer_rsrc(out + (size_t)n * K * P, (short)0,
                                                                        (int)((size_t)K * P * 4), kBufWord3);
-  auto load_group = [&](int t, uint4 (&a)[kWtGroup][2]) {
+  auto load_group = [&](int t, Words<4> (&a)[kWtGroup][2]) {
     const int kb = 2 * (wave + 4 * (t / ngroups));
     const int ms0 = (t % ngroups) * kWtGroup;
 #pragma unroll
     for (int s = 0; s < kWtGroup; ++s)
 #pragma unroll
-      for (int x = 0; x < 2; ++x) a[s][x] = buf_ld16(fr, (uint32_t)lane * 16, (uint32_t)(((kb + x) * msteps + ms0 + s) * 1024));
+      for (int x = 0; x < 2; ++x) a[s][x] = buf_ld<4>(fr, (uint32_t)lane * 16, (uint32_t)(((kb + x) * msteps + ms0 + s) * 1024));
   };
   f32x16_t acc[2][2];
 #pragma unroll
@@ -696,7 +671,7 @@ __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(3, 
   float* obase = out + (size_t)n * K * P;
   // the MFMAs of group t (m-steps of one tile), then the tile's store when
   // it is the tile's last group
-  auto step = [&](int t, const uint4 (&a)[kWtGroup][2]) {
+  auto step = [&](int t, const Words<4> (&a)[kWtGroup][2]) {
     const int ms0 = (t % ngroups) * kWtGroup;
 #pragma unroll
     for (int s = 0; s < kWtGroup; ++s) {
@@ -743,7 +718,7 @@ __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(3, 
         for (int r = 0; r < 16; ++r) acc[x][y][r] = 0.f;
   };
   // groups alternate between two register sets, each loaded one group ahead
-  uint4 a0[kWtGroup][2], a1[kWtGroup][2];
+  Words<4> a0[kWtGroup][2], a1[kWtGroup][2];
   if (total > 0) load_group(0, a0);
   for (int t = 0; t < total; t += 2) {
     if (t + 1 < total) load_group(t + 1, a1);
@@ -876,15 +851,23 @@ __global__ __launch_bounds__(256) void k_mix_reduce_few(const float4* __restrict
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
-// Tile side of a GEMM of rows x cols outputs over zt images (or splits): 64
-// where 128-wide tiles would leave CUs without a block or spend a third of
-// their rows on padding.
+// Whether a GEMM of rows x cols outputs over zt images is small: 128-wide tiles
+// would leave CUs without a block or spend a third of their rows on padding.
 constexpr long kMixFillBlocks = 512;  // two on each of 256 CUs
-static int mix_tile(int rows, int cols, long zt) {
+static bool mix_small(int rows, int cols, long zt, long fill = kMixFillBlocks) {
   const long t128 = (long)((rows + 127) / 128) * ((cols + 127) / 128);
   const long t64 = (long)((rows + 63) / 64) * ((cols + 63) / 64);
-  if (t128 * zt < kMixFillBlocks) return 64;
-  return 3 * t64 <= 8 * t128 ? 64 : 128;  // a third or more of the area is padding
+  return t128 * zt < fill || 3 * t64 <= 8 * t128;
+}
+
+// Tile side of such a GEMM: 64 where it is small.  A reduction of one 128-wide
+// K-step at most fills half of the twice as deep step of the 64-wide tiles, so
+// there one block per CU is enough for the others (int32, 21 x 120 x 8 x 3072 in
+// N, M, K, P, 504 128-wide tiles: 13.0 us with those, 17.9 with 64-wide ones; 126
+// of them or fewer: 0.7 of the time with 64-wide tiles).
+template <bool BF16>
+static int mix_tile(int rows, int cols, long zt, int depth) {
+  return mix_small(rows, cols, zt, depth <= (BF16 ? 64 : 32) ? kMixFillBlocks / 2 : kMixFillBlocks) ? 64 : 128;
 }
 
 struct WeightSplit { int tile, sp, chunk, S; };
@@ -911,6 +894,16 @@ size_t mix_workspace_bytes(int mode, int N, int M, int K, int P, int compute_dt)
   return ws.S > 1 ? (size_t)ws.S * M * K * sizeof(float) : 0;
 }
 
+// Whether an operand (see Stager) of rows x depth takes the aligned loads: rows
+// of whole 16-byte units, and offsets, up to a tile past the end, that fit the
+// descriptor's 32 bits.  Images then start aligned too: their stride is whole
+// rows.
+static bool vec_operand(const void* p, const void* mask, bool kc, long ld, int rows, int depth) {
+  if ((ld & 7) || ((uintptr_t)p & 15) || (mask && ((uintptr_t)mask & 15))) return false;
+  const long n = kc ? rows : depth;
+  return n * ld * 4 < (1L << 31) && (n + 128) * ld * 4 < (1L << 32);
+}
+
 template <bool BF16, int ADT, bool AKC, bool AMASK, int BDT, bool BKC, bool BMASK>
 static void gemm_launch(int tile, const void* a, const void* b, const float* aux, void* out, int rows, int cols,
                         int depth, long lda, long ldb, long ldc, long a_bs, long b_bs, long c_bs, int zt,
@@ -918,25 +911,50 @@ static void gemm_launch(int tile, const void* a, const void* b, const float* aux
   const int mt = (rows + tile - 1) / tile, nt = (cols + tile - 1) / tile;
   const int total = mt * nt * zt;
   const int grid = (total + 7) & ~7;
-  auto go = [&](auto kt) {
-    hipLaunchKernelGGL((k_mix_gemm<BF16, ADT, AKC, AMASK, BDT, BKC, BMASK, decltype(kt)::value>), dim3(grid),
-                       dim3(kMixThreads), 0, s, a, b, aux, out, rows, cols, depth, lda, ldb, ldc, a_bs, b_bs, c_bs, mt,
-                       nt, zt, nsplit_p, pchunk, out_kind, relu);
+  const bool va = vec_operand(a, AMASK ? aux : nullptr, AKC, lda, rows, depth);
+  const bool vb = vec_operand(b, BMASK ? aux : nullptr, BKC, ldb, cols, depth);
+  auto go = [&](auto kt, auto ka, auto kb) {
+    hipLaunchKernelGGL((k_mix_gemm<BF16, ADT, AKC, AMASK, BDT, BKC, BMASK, decltype(kt)::value, decltype(ka)::value,
+                                   decltype(kb)::value>),
+                       dim3(grid), dim3(kMixThreads), 0, s, a, b, aux, out, rows, cols, depth, lda, ldb, ldc, a_bs, b_bs,
+                       c_bs, mt, nt, zt, nsplit_p, pchunk, out_kind, relu);
   };
-  if (tile == 64) go(std::integral_constant<int, 64>{});
-  else go(std::integral_constant<int, 128>{});
+  auto vec = [&](auto kt) {
+    if constexpr (AKC && BKC) {  // both rows have the reduction's length
+      if (va && vb) go(kt, std::true_type{}, std::true_type{});
+      else go(kt, std::false_type{}, std::false_type{});
+    } else {
+      if (va && vb) go(kt, std::true_type{}, std::true_type{});
+      else if (va) go(kt, std::true_type{}, std::false_type{});
+      else if (vb) go(kt, std::false_type{}, std::true_type{});
+      else go(kt, std::false_type{}, std::false_type{});
+    }
+  };
+  if (tile == 64) vec(std::integral_constant<int, 64>{});
+  else vec(std::integral_constant<int, 128>{});
 }
 
-// Stored operand dtypes instantiated per compute type: bf16 compute reads
-// fp32 or bf16 storage; fp32 compute reads int32 or fp32 storage.
-template <bool BF16, typename F>
+// f(integral_constant dtype) for the stored type of a bf16 operand: fp32 or bf16.
+template <typename F>
 static void with_dt(int dt, F&& f) {
+  if (dt == 2) f(std::integral_constant<int, 2>{});
+  else f(std::integral_constant<int, 1>{});
+}
+
+// f(a's, b's) for the stored types a GEMM is compiled for: bf16 compute reads
+// fp32 or bf16 storage, fp32 compute reads fp32, or (FWD) int32, on both sides.
+template <bool BF16, bool kInts, typename F>
+static void with_dts(int a_dt, int b_dt, F&& f) {
   if constexpr (BF16) {
-    if (dt == 2) f(std::integral_constant<int, 2>{});
-    else f(std::integral_constant<int, 1>{});
+    with_dt(a_dt, [&](auto ad) { with_dt(b_dt, [&](auto bd) { f(ad, bd); }); });
   } else {
-    if (dt == 0) f(std::integral_constant<int, 0>{});
-    else f(std::integral_constant<int, 1>{});
+    if constexpr (kInts) {
+      if (a_dt == 0) {
+        f(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
+        return;
+      }
+    }
+    f(std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{});
   }
 }
 
@@ -964,15 +982,13 @@ static hipError_t launch_mix_t(int mode, const void* a, int a_dt, const void* b,
         return launch_mix_fwd_pipe(a, b, (float*)out, N, M, K, P, relu, s);
     }
     if constexpr (!BF16) {
-      if (a_dt == 1 && b_dt == 1 && out_dt == 1 && mix_tile(M, P, N) == 64 &&
+      if (a_dt == 1 && b_dt == 1 && out_dt == 1 && mix_small(M, P, N) &&
           mix_f32_direct_takes(true, N, M, K, P))
         return launch_mix_f32_direct(true, (const float*)a, (const float*)b, nullptr, (float*)out, N, M, K, P, relu, s);
     }
-    with_dt<BF16>(a_dt, [&](auto ad) {
-      with_dt<BF16>(b_dt, [&](auto bd) {
-        gemm_launch<BF16, decltype(ad)::value, true, false, decltype(bd)::value, false, false>(
-            mix_tile(M, P, N), a, b, nullptr, out, M, P, K, K, P, P, 0, (long)K * P, (long)M * P, N, 0, 0, ok_fwd, relu, s);
-      });
+    with_dts<BF16, true>(a_dt, b_dt, [&](auto ad, auto bd) {
+      gemm_launch<BF16, decltype(ad)::value, true, false, decltype(bd)::value, false, false>(
+          mix_tile<BF16>(M, P, N, K), a, b, nullptr, out, M, P, K, K, P, P, 0, (long)K * P, (long)M * P, N, 0, 0, ok_fwd, relu, s);
     });
     return hipGetLastError();
   }
@@ -981,13 +997,13 @@ static hipError_t launch_mix_t(int mode, const void* a, int a_dt, const void* b,
     // per (image, kStripP columns)
     const int ms = wt_msteps(M);
     const size_t nfr = (size_t)wt_ksteps(K) * ms * 64;
-    with_dt<true>(a_dt, [&](auto ad) {
+    with_dt(a_dt, [&](auto ad) {
       hipLaunchKernelGGL(k_wt_frags<decltype(ad)::value>, dim3((unsigned)((nfr + 255) / 256)), dim3(256), 0, s, a, M,
                          K, ms, nfr, (uint4*)ws);
     });
     const int nstrips = (P + kStripP - 1) / kStripP;
     const size_t shm = strip_lds_bytes(M);
-    with_dt<true>(b_dt, [&](auto bd) {
+    with_dt(b_dt, [&](auto bd) {
       if (relu)
         hipLaunchKernelGGL((k_mix_bwd_data_strip<decltype(bd)::value, true>), dim3(N * nstrips), dim3(kMixThreads),
                            shm, s, (const uint4*)ws, b, aux, (float*)out, M, K, P, ms, nstrips);
@@ -1003,15 +1019,13 @@ static hipError_t launch_mix_t(int mode, const void* a, int a_dt, const void* b,
   }
   if (mode == 1) {
     // C = out[n] (K x P): A(i=k, l=m) = w[m][k] (k contiguous), B(l=m, j=p) = grad[n][m][p]
-    with_dt<BF16>(a_dt, [&](auto ad) {
-      with_dt<BF16>(b_dt, [&](auto bd) {
-        if (relu)
-          gemm_launch<BF16, decltype(ad)::value, false, false, decltype(bd)::value, false, true>(
-              mix_tile(K, P, N), a, b, aux, out, K, P, M, K, P, P, 0, (long)M * P, (long)K * P, N, 0, 0, ok_bwd_data, 0, s);
-        else
-          gemm_launch<BF16, decltype(ad)::value, false, false, decltype(bd)::value, false, false>(
-              mix_tile(K, P, N), a, b, nullptr, out, K, P, M, K, P, P, 0, (long)M * P, (long)K * P, N, 0, 0, ok_bwd_data, 0, s);
-      });
+    with_dts<BF16, false>(a_dt, b_dt, [&](auto ad, auto bd) {
+      if (relu)
+        gemm_launch<BF16, decltype(ad)::value, false, false, decltype(bd)::value, false, true>(
+            mix_tile<BF16>(K, P, N, M), a, b, aux, out, K, P, M, K, P, P, 0, (long)M * P, (long)K * P, N, 0, 0, ok_bwd_data, 0, s);
+      else
+        gemm_launch<BF16, decltype(ad)::value, false, false, decltype(bd)::value, false, false>(
+            mix_tile<BF16>(K, P, N, M), a, b, nullptr, out, K, P, M, K, P, P, 0, (long)M * P, (long)K * P, N, 0, 0, ok_bwd_data, 0, s);
     });
     return hipGetLastError();
   }
@@ -1030,17 +1044,15 @@ static hipError_t launch_mix_t(int mode, const void* a, int a_dt, const void* b,
       piped = true;
     }
   }
-  if (!piped) with_dt<BF16>(a_dt, [&](auto ad) {
-    with_dt<BF16>(b_dt, [&](auto bd) {
-      if (relu)
-        gemm_launch<BF16, decltype(ad)::value, true, true, decltype(bd)::value, true, false>(
-            sp.tile, a, b, aux, dst, M, K, P, P, P, K, (long)M * P, (long)K * P, direct ? 0 : (long)M * K, sp.S, sp.sp,
-            sp.chunk, ok, 0, s);
-      else
-        gemm_launch<BF16, decltype(ad)::value, true, false, decltype(bd)::value, true, false>(
-            sp.tile, a, b, nullptr, dst, M, K, P, P, P, K, (long)M * P, (long)K * P, direct ? 0 : (long)M * K, sp.S, sp.sp,
-            sp.chunk, ok, 0, s);
-    });
+  if (!piped) with_dts<BF16, false>(a_dt, b_dt, [&](auto ad, auto bd) {
+    if (relu)
+      gemm_launch<BF16, decltype(ad)::value, true, true, decltype(bd)::value, true, false>(
+          sp.tile, a, b, aux, dst, M, K, P, P, P, K, (long)M * P, (long)K * P, direct ? 0 : (long)M * K, sp.S, sp.sp,
+          sp.chunk, ok, 0, s);
+    else
+      gemm_launch<BF16, decltype(ad)::value, true, false, decltype(bd)::value, true, false>(
+          sp.tile, a, b, nullptr, dst, M, K, P, P, P, K, (long)M * P, (long)K * P, direct ? 0 : (long)M * K, sp.S, sp.sp,
+          sp.chunk, ok, 0, s);
   });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || direct) return e;

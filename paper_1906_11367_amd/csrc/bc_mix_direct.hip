@@ -165,7 +165,7 @@ long tiles32(int rows, int P, int N, int ct) {
 
 // FWD: K a multiple of 4 (16-byte runs of w's rows); the caller asks only where
 // the tiled kernel would take 64-wide tiles (elsewhere its 128-wide ones reuse
-// more: 4 x 128 x 1024 x 65536 in N, M, K, P 612 us tiled, 697 here).
+// more: 4 x 128 x 1024 x 65536 in N, M, K, P 546 us tiled, 697 here).
 // BWD_DATA: where M and K are short, so that the tiled kernel's padding and its
 // one or two K-steps cost most (2 x 48 x 128 x 110592 61 us tiled, 47 here; 4 x
 // 17 x 96 x 2451 7.9 and 4.2); with more of either the re-reading of the

@@ -210,7 +210,48 @@ def test_mix_f32_short(dims):
         check(host(do), np.matmul(host(w).T[None].astype(np.float64), g.astype(np.float64)), RTOL_F32, f"dO relu={relu}")
 
 
-@pytest.mark.parametrize("dims", [(2, 72, 97, 243), (24, 200, 64, 1032), (2, 140, 130, 640)])
+# (N, M, K, P): rows of whole 16-byte units, whose loads run past the operand
+# (the ends of tiles of 64 and 128, reductions inside and just past a K-step);
+# rows of none (K = 37); and short reductions on 128-wide tiles.
+ALIGNED = [(1, 8, 8, 8), (2, 72, 40, 136), (1, 129, 200, 264), (3, 130, 520, 1096), (2, 64, 37, 200), (9, 8, 256, 3072),
+           (21, 120, 8, 1024)]
+
+
+@pytest.mark.parametrize("dims", ALIGNED)
+@pytest.mark.parametrize("stored", ["f32", "bf16", "bf16/f32", "f32/bf16", "i32"])
+def test_mix_of_aligned_rows(dims, stored):
+    """Every stored type, with and without the ReLU's mask in the backward."""
+    N, M, K, P = dims
+    say(f"mix aligned {dims} {stored}")
+    gen = torch.Generator(device="cuda").manual_seed(13)
+    if stored == "i32":
+        w, o = (torch.randint(-3, 4, s, generator=gen, device="cuda", dtype=torch.int32) for s in [(M, K), (N, K, P)])
+        z = torch.empty(N, M, P, dtype=torch.int32, device="cuda")
+        bc.pointwise_mix(bc.BC_MIX_FWD, w, o, z, N, M, K, P, bc.BC_F32)
+        assert torch.equal(z.double(), torch.matmul(w.double(), o.double()))
+        return
+    ct = bc.BC_BF16 if "bf16" in stored else bc.BC_F32
+    a, b = [torch.bfloat16 if t == "bf16" else torch.float32 for t in (stored.split("/") * 2)[:2]]
+    rounded = lambda t: t.bfloat16().double() if ct == bc.BC_BF16 else t.double()  # noqa: E731
+    rand = lambda dt, *s: torch.randn(*s, generator=gen, device="cuda").to(dt)  # noqa: E731
+    w, o, gw, gd, aux = rand(a, M, K), rand(b, N, K, P), rand(a, N, M, P), rand(b, N, M, P), rand(torch.float32, N, M, P)
+    z, do, dw = torch.empty(N, M, P, device="cuda"), torch.empty(N, K, P, device="cuda"), torch.empty(M, K, device="cuda")
+    for relu in (0, 1):
+        for t in (z, do, dw):
+            t.fill_(float("nan"))
+        bc.pointwise_mix(bc.BC_MIX_FWD, w, o, z, N, M, K, P, ct, relu=relu)
+        ref = torch.matmul(rounded(w), rounded(o))
+        check(host(z), host(ref.clamp(min=0) if relu else ref), RTOL_F32, f"Z relu={relu}")
+        keep = (aux > 0).double() if relu else 1.0
+        mask = aux if relu else None
+        bc.pointwise_mix(bc.BC_MIX_BWD_DATA, w, gd, do, N, M, K, P, ct, relu=relu, aux=mask)
+        check(host(do), host(torch.matmul(rounded(w).t().contiguous(), rounded(gd) * keep)), RTOL_F32, f"dO relu={relu}")
+        bc.pointwise_mix(bc.BC_MIX_BWD_WEIGHT, gw, o, dw, N, M, K, P, ct, relu=relu, aux=mask)
+        ref = sum(torch.matmul((rounded(gw) * keep)[n], rounded(o)[n].t().contiguous()) for n in range(N))
+        check(host(dw), host(ref), RTOL_F32, f"dW relu={relu}")
+
+
+@pytest.mark.parametrize("dims", [(2, 72, 97, 243), (24, 200, 64, 1032), (2, 140, 130, 640), (2, 72, 136, 264)])
 def test_mix_keeps_a_nan_in_its_place(dims):
     """A NaN in one row of an operand, next to a tile's or a row's end, reaches
     the outputs that row has part in and no other."""
