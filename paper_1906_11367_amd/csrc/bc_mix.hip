@@ -586,7 +586,22 @@ __global__ void k_wt_frags(const void* __restrict__ w, int M, int K, int msteps,
   frags[i] = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
 }
 
-template <int BDT, bool BMASK>
+// Elements `by` (0 .. 3) and after of a run moved to its front, zeros after them.
+__device__ __forceinline__ void shift_run(uint32_t (&w)[4], int by) {
+  const bool one = by & 1, two = by & 2;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) w[i] = one ? (i < 3 ? w[i + 1] : 0u) : w[i];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) w[i] = two ? (i < 2 ? w[i + 2] : 0u) : w[i];
+}
+
+// The gradient is staged by loads that no branch surrounds, all 8 of a unit in
+// flight: a branch for the operand's end makes the compiler wait for each load
+// before the next (12 x 136 x 8 x 65536 in N, M, K, P, fp32 gradient: 197 us,
+// 117 without).  kVec (rows of whole runs of 4): through a descriptor, whose
+// range check gives zeros past the operand's end.  Else from addresses held
+// back to the last whole run, whose elements are moved to their places.
+template <int BDT, bool BMASK, bool kVec>
 __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_mix_bwd_data_strip(const uint4* __restrict__ frags,
                                                                     const void* __restrict__ g,
                                                                     const float* __restrict__ aux,
@@ -602,31 +617,63 @@ __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(3, 
   const size_t plane = (size_t)M * P;
 
   // grad[n][m][p0 + j] -> Bs[j * pitch + m]: units of 8 m x 4 p, transposed
-  // in registers so each LDS write is 16 contiguous bytes of one row.
+  // in registers so each LDS write is 16 contiguous bytes of one row.  Columns
+  // past P hold any values and are not stored; m past M are zeros.
   {
-    const char* gb = reinterpret_cast<const char*>(g) + (size_t)n * plane * StoreBytes<BDT>::v;
-    const float* mb = BMASK ? aux + (size_t)n * plane : nullptr;
+    constexpr int SB = StoreBytes<BDT>::v;  // and the words of a run of 4
+    const char* gb = reinterpret_cast<const char*>(g) + (size_t)n * plane * SB;
+    const char* mb = BMASK ? reinterpret_cast<const char*>(aux + (size_t)n * plane) : nullptr;
+    const uint32_t end = (uint32_t)(plane * SB), mend = (uint32_t)(plane * 4);
+    __amdgpu_buffer_rsrc_t gr, mr;
+    if constexpr (kVec) gr = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(gb), (short)0, (int)end, kBufWord3);
+    if constexpr (kVec && BMASK) mr = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(mb), (short)0, (int)mend, kBufWord3);
     const int units = (msteps * 16 / 8) * (kStripP / 4);
     for (int u = tid; u < units; u += kMixThreads) {
       const int pg = u % (kStripP / 4), mg = u / (kStripP / 4);
       const int pp = p0 + pg * 4, m0 = mg * 8;
-      uint32_t v[8][4];
+      Words<SB> raw[8];
+      Words<4> mk[BMASK ? 8 : 1];
+      int back[8];  // elements the run was held back by
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const int m = m0 + e;
-        const int avail = m < M ? max(0, min(4, P - pp)) : 0;
-        const size_t idx = avail > 0 ? (size_t)m * P + pp : 0;
-        // columns past P are not stored, so only the image's last elements
-        // need the narrow loads (any P: the wide ones may be unaligned)
-        const bool wide = avail > 0 && idx + 4 <= plane;
-        const Words<StoreBytes<BDT>::v> raw = ld_run<BDT, StoreBytes<BDT>::v>(gb, idx, wide, avail);
-        Words<4> mk = {0u, 0u, 0u, 0u};
-        if constexpr (BMASK) mk = ld_run<1, 4>(reinterpret_cast<const char*>(mb), idx, wide, avail);
+        if constexpr (kVec) {
+          const uint32_t at = (uint32_t)m0 * (uint32_t)P + (uint32_t)pp;
+          raw[e] = buf_ld<SB>(gr, at * SB, min((uint32_t)(e * P) * SB, end));
+          if constexpr (BMASK) mk[e] = buf_ld<4>(mr, at * 4, min((uint32_t)(e * P) * 4, mend));
+        } else {
+          const size_t idx = (size_t)min(m0 + e, M - 1) * P + min(pp, P - 1), held = min(idx, plane - 4);
+          back[e] = (int)(idx - held);
+          raw[e] = ld_wide<BDT, SB>(gb, held);
+          if constexpr (BMASK) mk[e] = ld_wide<1, 4>(mb, held);
+        }
+      }
+      uint32_t v[8][4], a[8][4];
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const uint32_t bits = word_bits<BDT, StoreBytes<BDT>::v>(raw, i);
-          if constexpr (BDT == 2 && !BMASK) v[e][i] = bits;
-          else v[e][i] = i < avail ? (pack2_bf16(operand_f32<BDT, BMASK>(bits, mk[i]), 0.f) & 0xffffu) : 0u;
+          v[e][i] = word_bits<BDT, SB>(raw[e], i);
+          a[e][i] = BMASK ? mk[BMASK ? e : 0][i] : 0u;
+        }
+      if constexpr (!kVec) {
+        int any = 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) any |= back[e];
+        if (__builtin_amdgcn_ballot_w64(any != 0) != 0) {  // the wave holding the image's last elements
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            shift_run(v[e], back[e]);
+            if constexpr (BMASK) shift_run(a[e], back[e]);
+          }
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const bool in = kVec || m0 + e < M;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if constexpr (BDT != 2 || BMASK) v[e][i] = pack2_bf16(operand_f32<BDT, BMASK>(v[e][i], a[e][i]), 0.f) & 0xffffu;
+          if (!in) v[e][i] = 0u;
         }
       }
 #pragma unroll
@@ -992,7 +1039,9 @@ static hipError_t launch_mix_t(int mode, const void* a, int a_dt, const void* b,
     });
     return hipGetLastError();
   }
-  if (mode == 1 && BF16 && strip_lds_bytes(M) > 0 && out_dt == 1 && (size_t)K * P * 4 < ((size_t)1 << 31)) {
+  // (an image of fewer than 4 gradient values holds no whole run: below)
+  if (mode == 1 && BF16 && strip_lds_bytes(M) > 0 && out_dt == 1 && (size_t)K * P * 4 < ((size_t)1 << 31) &&
+      (size_t)M * P >= 4) {
     // strip kernel: w^T in fragment order in the workspace, then one block
     // per (image, kStripP columns)
     const int ms = wt_msteps(M);
@@ -1003,13 +1052,20 @@ static hipError_t launch_mix_t(int mode, const void* a, int a_dt, const void* b,
     });
     const int nstrips = (P + kStripP - 1) / kStripP;
     const size_t shm = strip_lds_bytes(M);
+    // rows of whole runs, and byte offsets, up to the last m-step, in 32 bits
+    const bool vec = (P & 3) == 0 && (size_t)M * P * 4 < ((size_t)1 << 31) && (size_t)ms * 16 * P * 4 < ((size_t)1 << 32);
+    auto go = [&](auto bd, auto masked, auto kv) {
+      hipLaunchKernelGGL((k_mix_bwd_data_strip<decltype(bd)::value, decltype(masked)::value, decltype(kv)::value>),
+                         dim3(N * nstrips), dim3(kMixThreads), shm, s, (const uint4*)ws, b, aux, (float*)out, M, K, P,
+                         ms, nstrips);
+    };
     with_dt(b_dt, [&](auto bd) {
-      if (relu)
-        hipLaunchKernelGGL((k_mix_bwd_data_strip<decltype(bd)::value, true>), dim3(N * nstrips), dim3(kMixThreads),
-                           shm, s, (const uint4*)ws, b, aux, (float*)out, M, K, P, ms, nstrips);
-      else
-        hipLaunchKernelGGL((k_mix_bwd_data_strip<decltype(bd)::value, false>), dim3(N * nstrips), dim3(kMixThreads),
-                           shm, s, (const uint4*)ws, b, aux, (float*)out, M, K, P, ms, nstrips);
+      auto with_vec = [&](auto masked) {
+        if (vec) go(bd, masked, std::true_type{});
+        else go(bd, masked, std::false_type{});
+      };
+      if (relu) with_vec(std::true_type{});
+      else with_vec(std::false_type{});
     });
     return hipGetLastError();
   }

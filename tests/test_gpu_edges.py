@@ -251,6 +251,37 @@ def test_mix_of_aligned_rows(dims, stored):
         check(host(dw), host(ref), RTOL_F32, f"dW relu={relu}")
 
 
+# (N, M, K, P) of the bf16 data gradient: images of fewer than a run of 4
+# gradient values, of one, with 1 to 3 values past the last whole run, and with
+# rows of whole runs that end inside a strip of 64 columns.
+STRIP = [(1, 1, 5, 1), (2, 1, 3, 3), (1, 4, 9, 1), (2, 1, 6, 5), (1, 17, 40, 66), (2, 50, 20, 131), (1, 65, 9, 4),
+         (3, 9, 8, 68), (1, 100, 65, 61)]
+
+
+@pytest.mark.parametrize("dims", STRIP)
+@pytest.mark.parametrize("relu", [0, 1])
+@pytest.mark.parametrize("stored", [torch.float32, torch.bfloat16])
+def test_mix_data_gradient_ends(dims, relu, stored):
+    """The last gradient values of an image reach their column alone, a NaN
+    among them too."""
+    N, M, K, P = dims
+    gen = torch.Generator(device="cuda").manual_seed(14)
+    w = torch.randn(M, K, generator=gen, device="cuda").bfloat16()
+    g = torch.randn(N, M, P, generator=gen, device="cuda").to(stored)
+    aux = torch.randn(N, M, P, generator=gen, device="cuda")
+    do = torch.full((N, K, P), float("nan"), device="cuda")
+    run = lambda: bc.pointwise_mix(bc.BC_MIX_BWD_DATA, w, g, do, N, M, K, P, bc.BC_BF16, relu=relu,  # noqa: E731
+                                   aux=aux if relu else None)
+    run()
+    masked = g.bfloat16().double() * ((aux > 0).double() if relu else 1.0)
+    check(host(do), host(torch.matmul(w.double().t().contiguous(), masked)), RTOL_F32, "dO")
+    aux[0, M - 1, P - 1] = 1.0
+    g[0, M - 1, P - 1] = float("nan")
+    run()
+    hit = torch.isnan(do)
+    assert hit[0, :, P - 1].all() and int(hit.sum()) == K
+
+
 @pytest.mark.parametrize("dims", [(2, 72, 97, 243), (24, 200, 64, 1032), (2, 140, 130, 640), (2, 72, 136, 264)])
 def test_mix_keeps_a_nan_in_its_place(dims):
     """A NaN in one row of an operand, next to a tile's or a row's end, reaches
