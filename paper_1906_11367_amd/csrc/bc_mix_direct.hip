@@ -184,10 +184,12 @@ hipError_t launch_mix_f32_direct(bool fwd, const float* w, const float* b, const
     return relu ? go<false, true, 1>(w, b, aux, out, N, M, K, P, 0, s)
                 : go<false, false, 1>(w, b, aux, out, N, M, K, P, 0, s);
   // two column tiles a wave reuse w's operand, one spreads over more SIMDs
-  // (1024): the fewer rounds of column tiles win, ties go to two (8 x 64 x 512
-  // x 3072: 21 us with two, 27 with one; 1 x 256 x 1024 x 3072: 35 and 22)
+  // (1024): two, unless that takes a quarter more rounds of column tiles (us with
+  // two and with one: 8 x 64 x 512 x 3072, as many rounds, 21 and 27; 51 x 128 x
+  // 896 x 1024, 8 rounds and 7, 114 and 142; 1 x 256 x 1024 x 3072, 2 and 1, 35
+  // and 22)
   const long two = 2 * ((tiles32(M, P, N, 2) + 1023) / 1024), one = (tiles32(M, P, N, 1) + 1023) / 1024;
-  return two <= one ? go<true, false, 2>(w, b, nullptr, out, N, M, K, P, relu, s)
+  return 4 * two <= 5 * one ? go<true, false, 2>(w, b, nullptr, out, N, M, K, P, relu, s)
                     : go<true, false, 1>(w, b, nullptr, out, N, M, K, P, relu, s);
 }
 
