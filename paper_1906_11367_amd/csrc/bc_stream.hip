@@ -84,10 +84,14 @@ template <int CPL>
 __device__ __forceinline__ int slot_at(int j) { return stream_skew<CPL>() ? j + (j >> 5) : j; }
 template <int LG, int CPL> constexpr int slot_words() { return stream_skew<CPL>() ? LG * CPL + LG * CPL / 32 : LG * CPL; }
 
-// Rows of a step are loaded kPrefetch steps ahead (a ring of registers, the
-// loop unrolled over it, so that no row is copied), so that a step's loads are in flight while the steps before it compute.
+// Rows of a step are loaded this many steps ahead, so that its loads are in
+// flight while the steps before it compute: in a ring of registers with the
+// loop unrolled over it, or (kRing, below) in a queue copied forward.
 constexpr int kPrefetch = 2;
-constexpr int kFwdPrefetch = 3;  // 256x130 maps, 4 boxes: 63 us two ahead, 59 three
+// Forward: three (us two and three ahead: 2 x 64 maps of 300x130, 4 boxes 123 and
+// 119; 1 x 32 of 256x256, 8 boxes 112 and 108; 4 x 128 of those 322 and 322), but
+// two where three leave one block per CU that does not fill it (kAhead).
+constexpr int kFwdPrefetch = 3;
 
 // The lane's CPL columns of a map row: byte offsets within a row (columns
 // outside the map clamped onto its last column, so every load is in bounds)
@@ -196,7 +200,7 @@ __global__ __launch_bounds__(LG * NG) void k_box_bwd_stream(const float* __restr
   constexpr int SW = slot_words<LG, CPL>();
   extern __shared__ __align__(16) float smem[];
   float* SY = smem;                       // [NG][RW]: scan Y of each group's box
-  float* SV = SY + NG * RW;               // [NG][RW]: suffix sums of the input row
+  float* SV = SY + NG * RW;               // [NG][RW]: prefix sums of the input row
   float* DX = SV + NG * RW;               // [2][R][NG][SW]: adjoint sums, added over groups
   const int map = blockIdx.x, n = map / C, c = map - n * C;
   const int g = group_uniform<LG>(threadIdx.x / LG), p = threadIdx.x % LG;
@@ -268,11 +272,13 @@ __global__ __launch_bounds__(LG * NG) void k_box_bwd_stream(const float* __restr
   float ca = 0.f, cb = 0.f, gcs = 0.f, gds = 0.f;
   // rows of step y: the input row v, gc_ = G(y + fc), gd_ = G(y + fd).  kRing:
   // a ring of PF + 1 steps with the loop unrolled over it; else a queue whose
-  // rows are copied forward (24 moves a step, but one copy of the step: with 4
-  // columns and all gradients the unrolled form takes 187 VGPRs, one block of
-  // 512 per CU; 256x256 maps, 8 boxes: 565 us against 473; 200x150, 6 boxes:
-  // 204 against 215)
-  constexpr bool kRing = CPL < 4 || kInt;
+  // rows are copied forward (up to 24 moves a step, but one copy of the step).
+  // With all gradients the unrolled form takes 187 VGPRs for 4 columns and 148
+  // for 3: one block of 512 threads per CU.  4 x 128 maps, ring and queue: 256
+  // x 256, 8 boxes 565 and 473 us; 256 x 160, 8 boxes 519 and 465; 256 x 130, 4
+  // boxes (blocks of 256) 227 and 253.  16 x 128 maps of 400 x 46, 6 boxes 722
+  // and 630.
+  constexpr bool kRing = CPL < 3 || (CPL == 3 && NG == 4) || kInt;
   constexpr int RS = kRing ? PF + 1 : PF;
   float qv[RS][CPL], qc[RS][CPL], qd[RS][CPL];
   auto issue = [&](int y, float (&v)[CPL], float (&gc_)[CPL], float (&gd_)[CPL]) {
@@ -422,14 +428,20 @@ __global__ __launch_bounds__(LG * NG) void k_box_bwd_stream(const float* __restr
 // before the cursors add its rows and mu times the clipped box area is added
 // back (the same combination applied to the clamped coordinates).  kNT:
 // non-temporal output stores (outputs larger than the last-level cache).
+// kAhead: steps a row is loaded ahead.  kRing: the rows in a ring, else in a
+// queue (see the backward): non-temporal stores word by word write their lines
+// to memory in parts, the more the further the waves run apart, and the queue
+// holds them closer together (4 x 128 maps of 256 x 128, 8 boxes: 269 us in a
+// ring, 235 in a queue).
 // ---------------------------------------------------------------------------
-template <typename T, typename OutT, int LG, int CPL, int NG, bool kOffset, bool kInt, bool kNT, bool kVec>
+template <typename T, typename OutT, int LG, int CPL, int NG, bool kOffset, bool kInt, bool kNT, bool kVec, int kAhead>
 __global__ __launch_bounds__(LG * NG) void k_box_fwd_stream(const T* __restrict__ x, const int* __restrict__ taps,
                                                             OutT* __restrict__ y, int C, int H, int W, int B) {
+  constexpr bool kRing = !kNT || kVec;
   constexpr bool kPlain = kInt || std::is_same<T, int>::value;   // corner weights (-1, 0, 1, 0)
   constexpr int PAD = stream_pad<CPL>();
   constexpr int RW = stream_row_words<LG, CPL>();
-  constexpr int PF = kFwdPrefetch;
+  constexpr int PF = kAhead;
   constexpr int LC = LG * CPL;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T* SY = reinterpret_cast<T*>(smem_raw);
@@ -585,7 +597,7 @@ __global__ __launch_bounds__(LG * NG) void k_box_fwd_stream(const T* __restrict_
     __builtin_amdgcn_wave_barrier();
   };
   // main loop, the rows of step yy loaded PF steps ahead
-  constexpr int RS = PF + 1;
+  constexpr int RS = kRing ? PF + 1 : PF;
   T qc[RS][CPL], qd[RS][CPL];
   auto issue = [&](int yn, T (&gc_)[CPL], T (&gd_)[CPL]) {
     load_row(yn < H ? yn + fc : -1, gc_);
@@ -593,17 +605,31 @@ __global__ __launch_bounds__(LG * NG) void k_box_fwd_stream(const T* __restrict_
   };
 #pragma unroll
   for (int i = 0; i < PF; ++i) issue(i, qc[i], qd[i]);
-  int yy = 0;
-  for (; yy + RS <= H; yy += RS) {
+  if constexpr (kRing) {
+    int yy = 0;
+    for (; yy + RS <= H; yy += RS) {
 #pragma unroll
-    for (int i = 0; i < RS; ++i) {
-      issue(yy + i + PF, qc[(i + PF) % RS], qd[(i + PF) % RS]);
-      step(yy + i, qc[i], qd[i]);
+      for (int i = 0; i < RS; ++i) {
+        issue(yy + i + PF, qc[(i + PF) % RS], qd[(i + PF) % RS]);
+        step(yy + i, qc[i], qd[i]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < PF; ++i)
+      if (yy + i < H) step(yy + i, qc[i], qd[i]);
+  } else {
+    for (int yy = 0; yy < H; ++yy) {
+      T gc_[CPL], gd_[CPL];
+#pragma unroll
+      for (int k = 0; k < CPL; ++k) { gc_[k] = qc[0][k]; gd_[k] = qd[0][k]; }
+#pragma unroll
+      for (int i = 0; i + 1 < PF; ++i)
+#pragma unroll
+        for (int k = 0; k < CPL; ++k) { qc[i][k] = qc[i + 1][k]; qd[i][k] = qd[i + 1][k]; }
+      issue(yy + PF, qc[PF - 1], qd[PF - 1]);
+      step(yy, gc_, gd_);
     }
   }
-#pragma unroll
-  for (int i = 0; i < PF; ++i)
-    if (yy + i < H) step(yy + i, qc[i], qd[i]);
 }
 
 // ---------------------------------------------------------------------------
@@ -633,7 +659,10 @@ static bool stream_geom(int H, int W, int B, StreamGeom& g) {
   // per-lane 32-bit byte offsets into a block's gradient maps
   if ((size_t)g.ng * H * W * 4 >= ((size_t)1 << 31)) return false;
   const size_t slot_set = (size_t)g.ng * (g.lg * g.cpl + g.lg * g.cpl / 32) * 4;
-  g.R = (int)std::max<size_t>(1, std::min<size_t>(8, kSlotBytes / slot_set));
+  // small blocks of many boxes: every row, for more blocks per CU (16 x 128 maps
+  // of 420 x 64, 8 boxes: 753 us, every 8 rows 938)
+  if (g.lg == 16 && g.ng == 8 && g.cpl >= 3) g.R = 1;
+  else g.R = (int)std::max<size_t>(1, std::min<size_t>(8, kSlotBytes / slot_set));
   return true;
 }
 
@@ -646,6 +675,12 @@ bool box_stream_supported(int H, int W, int B) {
 // aligned rows (W == LG * CPL, CPL = 4, base pointers 16-byte aligned).
 static bool stream_vec(int W, int lg, int cpl) { return cpl == 4 && W == lg * cpl; }
 
+// Layouts that store such outputs non-temporally word by word (those that store
+// whole rows always do): 65 to 128 columns.  The others' partial lines cost more
+// than the cache they leave free (4 x 128 maps of 256 x 160, 8 boxes: 514 us,
+// with ordinary stores 364; 16 x 128 of 800 x 30, 4 boxes: 790, 504).
+constexpr bool stream_nt_words(int lg, int cpl) { return lg == 64 && cpl == 2; }
+
 template <int LG, int CPL, int NG>
 static void bwd_stream_t(const float* x, const int* taps, const float* gy, void* gx, float* partials, int N, int C,
                          int H, int W, int B, bool rounded, bool relu_bf16, int R, hipStream_t s) {
@@ -657,8 +692,13 @@ static void bwd_stream_t(const float* x, const int* taps, const float* gy, void*
                        grid, block, shm, s, x, taps, gy, gx, partials, C, H, W, B, R);
   };
   auto with_vec = [&](auto ki, auto kr) {
-    if (CPL == 4 && stream_vec(W, LG, CPL)) go(ki, kr, std::true_type{});
-    else go(ki, kr, std::false_type{});
+    if constexpr (CPL == 4) {
+      if (stream_vec(W, LG, CPL)) {
+        go(ki, kr, std::true_type{});
+        return;
+      }
+    }
+    go(ki, kr, std::false_type{});
   };
   if (rounded) with_vec(std::true_type{}, std::false_type{});
   else if (relu_bf16) with_vec(std::false_type{}, std::true_type{});
@@ -686,23 +726,51 @@ template <typename T, typename OutT, int LG, int CPL, int NG, bool kOffset>
 static void fwd_stream_t(const void* x, const int* taps, void* y, int N, int C, int H, int W, int B, bool rounded,
                          bool nt, hipStream_t s) {
   const size_t shm = (size_t)NG * stream_row_words<LG, CPL>() * sizeof(T);
-  const bool vec = stream_vec(W, LG, CPL);
-  auto go = [&](auto ki, auto kn) {
-    if (CPL == 4 && vec)
-      hipLaunchKernelGGL((k_box_fwd_stream<T, OutT, LG, CPL, NG, kOffset, decltype(ki)::value, decltype(kn)::value,
-                                           true>),
-                         dim3(N * C), dim3(LG * NG), shm, s, (const T*)x, taps, (OutT*)y, C, H, W, B);
-    else
-      hipLaunchKernelGGL((k_box_fwd_stream<T, OutT, LG, CPL, NG, kOffset, decltype(ki)::value, decltype(kn)::value,
-                                           false>),
-                         dim3(N * C), dim3(LG * NG), shm, s, (const T*)x, taps, (OutT*)y, C, H, W, B);
+  auto launch = [&](auto ki, auto kn, auto kv, auto ka) {
+    hipLaunchKernelGGL((k_box_fwd_stream<T, OutT, LG, CPL, NG, kOffset, decltype(ki)::value, decltype(kn)::value,
+                                         decltype(kv)::value, decltype(ka)::value>),
+                       dim3(N * C), dim3(LG * NG), shm, s, (const T*)x, taps, (OutT*)y, C, H, W, B);
   };
-  auto with_nt = [&](auto ki) {
-    if (nt) go(ki, std::true_type{});
-    else go(ki, std::false_type{});
+  using Two = std::integral_constant<int, 2>;
+  auto go = [&](auto ki, auto kn, auto kv) {
+    // mean removed, 4 columns: 140 VGPRs, one block of 512 threads per CU; with 5
+    // of its 8 boxes at work that does not fill it (4 x 128 maps of 256x256: 304
+    // us three ahead, 267 two; 8 boxes 354 and 368)
+    if constexpr (kOffset && LG == 64 && CPL == 4 && NG == 8 && decltype(kv)::value) {
+      if (B == 5) {
+        launch(ki, kn, kv, Two{});
+        return;
+      }
+    }
+    if constexpr (decltype(kn)::value && !decltype(kv)::value) launch(ki, kn, kv, Two{});
+    else launch(ki, kn, kv, std::integral_constant<int, kFwdPrefetch>{});
   };
-  if (rounded) with_nt(std::true_type{});
-  else with_nt(std::false_type{});
+  auto with_vec = [&](auto ki) {
+    const std::true_type yes;
+    const std::false_type no;
+    constexpr bool kF32 = std::is_same<OutT, float>::value;
+    if constexpr (CPL == 4) {
+      if (stream_vec(W, LG, CPL)) {
+        if constexpr (kF32) {
+          if (nt) {
+            go(ki, yes, yes);
+            return;
+          }
+        }
+        go(ki, no, yes);
+        return;
+      }
+    }
+    if constexpr (kF32 && stream_nt_words(LG, CPL)) {
+      if (nt) {
+        go(ki, yes, no);
+        return;
+      }
+    }
+    go(ki, no, no);
+  };
+  if (rounded) with_vec(std::true_type{});
+  else with_vec(std::false_type{});
 }
 
 template <int LG, int CPL, int NG>
@@ -722,7 +790,7 @@ hipError_t launch_box_fwd_stream(const void* x, bool is_int, const int* taps, vo
                                  int H, int W, int B, bool offset, bool rounded, hipStream_t s) {
   StreamGeom g;
   if (!stream_geom(H, W, B, g)) return hipErrorInvalidValue;
-  // fp32 outputs larger than the last-level cache are stored non-temporally
+  // fp32 outputs larger than the last-level cache
   const bool nt = out_kind == 1 && (size_t)N * C * B * H * W * 4 > ((size_t)256 << 20);
 #define BC_FWD_STREAM(LG, CPL, NG)                                                                                \
   if (g.lg == LG && g.cpl == CPL && g.ng == NG) {                                                               \

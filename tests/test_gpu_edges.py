@@ -147,6 +147,48 @@ def test_wide_maps_in_bands(H, W, stride):
         np.testing.assert_array_equal(yi.cpu().numpy(), O.box_forward(xi.cpu().numpy(), bi))
 
 
+# Maps the streaming kernels take, by how they hold their rows: columns per lane
+# 1 to 4 of groups of 16 lanes (narrow, tall maps) and of a wave, blocks of up to
+# 4 and 8 boxes, heights that end inside the unrolled loop, whole-row accesses.
+STREAM = [(330, 14, 3), (331, 15, 8), (340, 30, 6), (372, 46, 6), (373, 47, 3), (290, 64, 8), (291, 64, 4), (160, 128, 7),
+          (161, 127, 2), (122, 160, 8), (123, 161, 4), (90, 256, 5), (91, 256, 3), (89, 250, 8)]
+
+
+@pytest.mark.parametrize("H,W,B", STREAM)
+def test_stream_edges(H, W, B):
+    N, C = 1, 2
+    say(f"stream {H}x{W} B={B}")
+    x, bx, g = case(H * 5 + W, N, C, H, W, B)
+    xd, bd, gd = dev(x), dev(bx), dev(g)
+    ref = O.box_forward(x, bx)
+    y = torch.empty(tuple(g.shape), device="cuda")
+    for flags in (0, bc.BC_FLAG_MEAN_OFFSET):
+        y.fill_(float("nan"))
+        check(host(bc.box_conv_fwd(xd, bd, y, flags)), ref, RTOL_F32, f"y flags={flags}")
+    dx, db = torch.empty_like(xd), torch.empty((C, B, 4), device="cuda")
+    bc.box_conv_bwd(xd, bd, gd, dx, db)
+    check(host(dx), O.box_backward_input(g, bx, H, W), RTOL_F32, "dx")
+    check(host(db), O.box_backward_params(x, g, bx), RTOL_F32, "dboxes")
+    bc.box_conv_bwd(xd, bd, gd, dx, None, bc.BC_FLAG_INTEGER_CORNERS)
+    check(host(dx), O.box_backward_input(g, bx, H, W, integer_corners=True), RTOL_F32, "dx, integer corners")
+
+
+@pytest.mark.parametrize("W,B,flags", [(128, 5, 0), (127, 8, bc.BC_FLAG_MEAN_OFFSET), (160, 5, 0), (256, 5, bc.BC_FLAG_MEAN_OFFSET)])
+def test_stream_large_output_same_bits(W, B, flags):
+    """Outputs beyond the last-level cache may be stored, and their rows held,
+    another way: every half batch, whose output is smaller, has the same bits."""
+    H, C = 160, 64
+    N = 2 * (((256 << 20) // (C * B * H * W * 4)) // 2 + 1)
+    assert N * C * B * H * W * 4 > 256 << 20 >= (N // 2) * C * B * H * W * 4
+    gen = torch.Generator(device="cuda").manual_seed(15)
+    x = torch.randn(N, C, H, W, generator=gen, device="cuda")
+    bd = dev(real_boxes(np.random.default_rng(3), C, B, 20, 0.3, 60))
+    y = bc.box_conv_fwd(x, bd, torch.full((N, C * B, H, W), float("nan"), device="cuda"), flags)
+    for lo in (0, N // 2):
+        half = bc.box_conv_fwd(x[lo:lo + N // 2].contiguous(), bd, torch.empty(N // 2, C * B, H, W, device="cuda"), flags)
+        assert torch.equal(y[lo:lo + N // 2], half)
+
+
 # (N, M, K, P): 64-wide tiles with ragged rows, columns and reductions; odd
 # rows (2-byte aligned bf16); the pipelined forward (M > 64, K % 64 == 0, P % 8
 # == 0, 192 tiles or more) with one and several row tiles, ragged in both
