@@ -434,18 +434,24 @@ hipError_t launch_unit_params(int op, const float* in, int n, float mw, float mh
 }
 
 // Maps too few to fill the chip with one block each: up to 256 wide they take
-// blocks of 1024 threads over 64-row strips; wider ones (fewer than 4 blocks
-// per CU), with scratch for the column sums of each band, are divided over
-// enough blocks for 8 per CU (one block walks the strips of its map one after
-// another, 9 us each: 2 x 32 maps of 288x384 157 us, divided 24 us).
-constexpr int kSatBandMaps = 1024, kSatBandBlocks = 2048;
+// blocks of 1024 threads over 64-row strips; wider ones, with scratch for the
+// column sums of each band, are divided over enough blocks for 8 per CU (one
+// block walks the strips of its map one after another, 9 us each: 2 x 32 maps of
+// 288x384 157 us, divided 24 us).  Dividing reads the map twice, which costs more
+// than it fills from little more than a block per CU on, or, where the mean is
+// read first and so costs as much anyway, from about three (us of a call with
+// whole and with divided tables; backward, 1 box: 256 maps of 162x680 273, 256;
+// 400 384, 431; 600 567, 660; 256 of 288x384 257, 214; 400 359, 367; 600 488, 569;
+// forward with the mean, 4 boxes: 400 of 288x384 660, 499; 700 963, 963).
+constexpr int kSatBandMaps = 320, kSatBandMapsMean = 640, kSatBandBlocks = 2048;
 constexpr int kSatFewMaps = 2048;
 
 template <typename T, bool kUp>
 static void sat_build_t(const T* x, T* sat, float* mean, int maps, int H, int W, int stride, SatScratch scratch,
                         hipStream_t s) {
   const int Ho = (H + stride - 1) / stride, Wo = (W + stride - 1) / stride, cols = kUp ? Wo : W;
-  int nb = W > 256 && maps < kSatBandMaps ? std::min((kSatBandBlocks + maps - 1) / maps, (H + kStrip - 1) / kStrip) : 1;
+  const bool divide = W > 256 && maps < (mean ? kSatBandMapsMean : kSatBandMaps);
+  int nb = divide ? std::min((kSatBandBlocks + maps - 1) / maps, (H + kStrip - 1) / kStrip) : 1;
   nb = (int)std::min<size_t>(nb, scratch.bytes / ((size_t)maps * cols * 4));
   if (nb > 1) {
     const int band_rows = ((H + nb * kStrip - 1) / (nb * kStrip)) * kStrip;

@@ -147,6 +147,21 @@ def test_wide_maps_in_bands(H, W, stride):
         np.testing.assert_array_equal(yi.cpu().numpy(), O.box_forward(xi.cpu().numpy(), bi))
 
 
+@pytest.mark.parametrize("C", [319, 320])
+def test_wide_maps_divided_or_not(C):
+    """Both sides of the number of maps up to which tables are divided."""
+    N, B, H, W = 1, 1, 21, 259
+    x, bx, g = case(C, N, C, H, W, B)
+    xd, bd, gd = dev(x), dev(bx), dev(g)
+    for flags in (0, bc.BC_FLAG_MEAN_OFFSET):
+        y = torch.full(tuple(g.shape), float("nan"), device="cuda")
+        check(host(bc.box_conv_fwd(xd, bd, y, flags)), O.box_forward(x, bx), RTOL_F32, f"y flags={flags}")
+    dx, db = torch.empty_like(xd), torch.empty((C, B, 4), device="cuda")
+    bc.box_conv_bwd(xd, bd, gd, dx, db)
+    check(host(dx), O.box_backward_input(g, bx, H, W), RTOL_F32, "dx")
+    check(host(db), O.box_backward_params(x, g, bx), RTOL_F32, "dboxes")
+
+
 # Maps the streaming kernels take, by how they hold their rows: columns per lane
 # 1 to 4 of groups of 16 lanes (narrow, tall maps) and of a wave, blocks of up to
 # 4 and 8 boxes, heights that end inside the unrolled loop, whole-row accesses.
