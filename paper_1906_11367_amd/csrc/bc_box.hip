@@ -326,9 +326,11 @@ __global__ __launch_bounds__(256) void k_box_fwd_gather_strided(const T* __restr
 // Backward, tables in HBM (one table per gradient map, built beforehand).
 // One 256-thread block per (map, block of 256 items); loops over boxes.
 // partials: [((n * nblk + blk) * 4 + wave) * C*B + c*B + b][4]; kInt as in
-// k_box_bwd_lds.
+// k_box_bwd_lds.  Four waves per SIMD: without the ReLU that takes exactly the 128
+// VGPRs allowed, with it 129, so there the bound is set (3 x 63 maps of 106x583,
+// 4 boxes: 414 us without, 400 with).
 template <int SEG, bool kInt, bool kRelu>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_box_bwd_gather(const float* __restrict__ x, const float* __restrict__ sat_g,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kRelu ? 4 : 3, 8))) void k_box_bwd_gather(const float* __restrict__ x, const float* __restrict__ sat_g,
                                                         const int* __restrict__ taps, void* __restrict__ gx,
                                                         float* __restrict__ partials, int C, int H, int W, int B,
                                                         int nblk, int total) {

@@ -75,18 +75,21 @@ def test_mix_loads_stay_in_flight(device_code, a, b, tile):
     assert loads and not waits, waits
 
 
-def test_stream_gradient_blocks_share_a_cu(device_code):
-    """Blocks of 512 threads of the streaming backward: at most 128 registers,
-    so that a CU takes two of them, and none in memory."""
+# (kernels, registers that leave the waves they are built for, bytes in memory):
+# blocks of 512 threads of the streaming backward, two per CU; the backward from
+# tables in memory, four waves per SIMD, two registers of the masked one spilled
+@pytest.mark.parametrize("pattern,registers,spilled", [(r"k_box_bwd_streamILi64ELi\dELi8E", 128, 0),
+                                                       (r"k_box_bwd_gatherI", 128, 8)])
+def test_waves_per_simd(device_code, pattern, registers, spilled):
     readelf = _tool("llvm-readelf")
     seen = 0
     for obj in device_code:
         notes = subprocess.run([readelf, "--notes", obj], check=True, capture_output=True, text=True).stdout
         for kernel in notes.split("- .agpr_count:")[1:]:
             name = re.search(r"\.name:\s+(\S+)", kernel).group(1)
-            if not re.search(r"k_box_bwd_streamILi64ELi\dELi8E", name):
+            if not re.search(pattern, name):
                 continue
             seen += 1
-            assert int(re.search(r"\.vgpr_count:\s+(\d+)", kernel).group(1)) <= 128, name
-            assert int(re.search(r"\.private_segment_fixed_size:\s+(\d+)", kernel).group(1)) == 0, name
+            assert int(re.search(r"\.vgpr_count:\s+(\d+)", kernel).group(1)) <= registers, name
+            assert int(re.search(r"\.private_segment_fixed_size:\s+(\d+)", kernel).group(1)) <= spilled, name
     assert seen
