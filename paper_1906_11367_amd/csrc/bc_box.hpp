@@ -216,7 +216,7 @@ __device__ void build_table_lds(const T* __restrict__ src, T* S, int H, int W, i
     int j = tid % W;
     int o = (tid / W + 1) * pitch + j + 1;
     const int step = di * pitch + dj, wrap = pitch - W;
-    constexpr int kBatch1 = kSkip ? 8 : 4;
+    constexpr int kBatch1 = kSkip ? 2 : 4;  // more take 82 VGPRs in the forward instead of 53
     for (int base = 0; base < n; base += nt * kBatch1) {
       T q[kBatch1];
 #pragma unroll
