@@ -32,7 +32,7 @@ def case(seed, N, C, H, W, B, stride=1):
 # 96 columns; lanes end at 64), heights around the segments (4, 8, 10, 13 rows)
 # and the bands (16 and 32 rows per wave, several strips for narrow tall maps).
 SHAPES = [(5, 7), (7, 6), (8, 2), (8, 3), (9, 47), (10, 48), (13, 49), (16, 61), (17, 62), (33, 63), (64, 64), (31, 65),
-          (40, 95), (65, 96), (12, 97), (100, 17), (130, 31), (128, 48)]
+          (40, 95), (65, 96), (12, 97), (100, 17), (130, 31), (128, 48), (8, 58), (15, 64), (11, 75), (16, 96), (17, 90)]
 
 
 @pytest.mark.parametrize("H,W", SHAPES)
