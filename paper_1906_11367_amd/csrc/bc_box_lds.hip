@@ -260,6 +260,22 @@ static int fwd_seg(int H, int nch) {
   return best;
 }
 
+// Whether the forward's items are 3 columns of 16 rows instead of 6 columns of
+// seg.  Six columns halve the table reads but leave fp32 and int32 rows as a
+// 16- and an 8-byte store per lane, each of which writes parts of its lines;
+// three go out as 12 bytes a lane, whole lines together.  Calls of many maps
+// are bound by those stores (32 x 256 maps of 64x48, 4 boxes: 127 us with six
+// columns, 104 with three) unless the narrow items cost clearly more waves x
+// rows x columns (72x80 maps: 171 against 132, and 161 us become 238 with the
+// mean); calls of few maps run on latency and keep the wide items.
+constexpr int kTallSeg = 16;
+static bool fwd_tall_items(long boxes, int H, int W, int seg) {
+  if (boxes <= kTapsHereBoxes || H < kTallSeg) return false;
+  const long wide = (long)(((W + 5) / 6 * n_segs(H, seg) + 63) / 64) * (seg + 3) * 6;
+  const long tall = (long)((n_chunks(W) * n_segs(H, kTallSeg) + 63) / 64) * (kTallSeg + 3) * kQ;
+  return 5 * tall <= 6 * wide;
+}
+
 template <typename T, typename OutT, bool kOffset>
 static void fwd_lds_t(const void* x, const int* taps, const float* boxes, void* y, int N, int C, int H, int W, int B, bool rounded,
                       int stride, hipStream_t s) {
@@ -279,8 +295,9 @@ static void fwd_lds_t(const void* x, const int* taps, const float* boxes, void* 
     }
     constexpr bool kOneSeg = kOffset || std::is_same<T, int>::value;
     const int nch = (W + Q - 1) / Q, seg = pc && !kOneSeg ? fwd_seg(H, nch) : 8;
-    const int per_box = nch * n_segs(H, seg);
-    const bool lanes = pc > 0 && seg == 8 && per_box <= 32 && B > 1;
+    const bool lanes = pc > 0 && seg == 8 && nch * n_segs(H, seg) <= 32 && B > 1;
+    const bool tall = sizeof(OutT) == 4 && !lanes && fwd_tall_items((long)N * C * B, H, W, seg);
+    const int per_box = tall ? n_chunks(W) * n_segs(H, kTallSeg) : nch * n_segs(H, seg);
     const int bpw = lanes ? std::min(64 / per_box, B) : 1;
     const FwdGeom g = fwd_geom_items(N, C, (B + bpw - 1) / bpw, bpw * per_box, kFwdThreads);
     const size_t shm = table_lds_bytes(H, W, pc, g.threads) + (pc ? (size_t)(H + 1) * 2 * (kFwdPad - kPad) * 4 : 0);
@@ -309,6 +326,19 @@ static void fwd_lds_t(const void* x, const int* taps, const float* boxes, void* 
       }
       with_lanes(std::false_type{});
     };
+    if constexpr (sizeof(OutT) == 4) {
+      if (tall) {
+        with_flag(rounded, [&](auto ki) {
+          with_pitch(pc, [&](auto kp) {
+            hipLaunchKernelGGL((k_box_fwd_lds<T, OutT, kTallSeg, kOffset, decltype(ki)::value, decltype(kp)::value, kQ, 0,
+                                              false, false, false>),
+                               dim3(N * C * g.ngrp), dim3(g.threads), shm, s, (const T*)x, taps, boxes, (OutT*)y, C, H,
+                               W, B, 1, g.bpg, g.per_box_p);
+          });
+        });
+        return;
+      }
+    }
     with_flag(rounded, [&](auto ki) {
       auto packed = [&](auto kseg, auto kp) {
         // bf16 rows of an even width go out as aligned packed words

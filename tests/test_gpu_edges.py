@@ -73,6 +73,31 @@ def test_lds_box_edges_many_maps(H, W):
     check(host(db), O.box_backward_params(x, g, bx), RTOL_F32, "dboxes")
 
 
+@pytest.mark.parametrize("H,W", [(15, 48), (16, 6), (16, 48), (17, 7), (32, 97), (33, 63), (64, 48), (100, 17), (47, 64)])
+def test_lds_forward_many_maps(H, W):
+    """More than 4096 filtered maps: their taps come from memory, and 4-byte
+    outputs may take the items of 16 rows; int32 is exact on every path."""
+    N, C, B = 2, 700, 3
+    x, bx, _ = case(H + 2 * W, N, C, H, W, B)
+    xd, bd = dev(x), dev(bx)
+    say(f"forward of many maps {H}x{W}")
+    y = torch.empty((N, C * B, H, W), device="cuda")
+    check(host(bc.box_conv_fwd(xd, bd, y)), O.box_forward(x, bx), RTOL_F32, "y")
+    yb = torch.empty_like(y, dtype=torch.bfloat16)
+    # the bf16 output of the other items: the fp32 sums agree to RTOL_F32 of the largest
+    bc.box_conv_fwd(xd, bd, yb)
+    assert (yb.float() - y).abs().max() <= (2.0 ** -8 + RTOL_F32) * y.abs().max()
+    ym = torch.empty_like(y)
+    check(host(bc.box_conv_fwd(xd, bd, ym, bc.BC_FLAG_MEAN_OFFSET)), host(y), RTOL_F32, "y, mean offset")
+    bc.box_conv_fwd(xd, bd, y, bc.BC_FLAG_INTEGER_CORNERS)
+    check(host(y), O.box_forward(x, bx, integer_corners=True), RTOL_F32, "y, integer corners")
+    xi = (8 * xd).round().int()
+    yi, yh = (torch.empty((N, C * B, H, W), device="cuda", dtype=torch.int32) for _ in range(2))
+    bc.box_conv_fwd(xi, bd, yi, bc.BC_FLAG_INTEGER_CORNERS)
+    bc.box_conv_fwd(xi, bd, yh, bc.BC_FLAG_INTEGER_CORNERS | bc.BC_FLAG_FORCE_HBM)
+    assert torch.equal(yi, yh)
+
+
 @pytest.mark.parametrize("stride", [2, 3])
 @pytest.mark.parametrize("H,W", [(8, 3), (9, 47), (13, 48), (33, 63), (64, 64), (31, 65), (41, 95), (70, 17)])
 def test_strided_edges(H, W, stride):
