@@ -267,7 +267,8 @@ static int fwd_seg(int H, int nch) {
 // are bound by those stores (32 x 256 maps of 64x48, 4 boxes: 127 us with six
 // columns, 104 with three) unless the narrow items cost clearly more waves x
 // rows x columns (72x80 maps: 171 against 132, and 161 us become 238 with the
-// mean); calls of few maps run on latency and keep the wide items.
+// mean); calls of few maps run on latency and keep the wide items, and tables
+// of run-time pitch gain nothing (21 x 133 maps of 109x96: 64 us either way).
 constexpr int kTallSeg = 16;
 static bool fwd_tall_items(long boxes, int H, int W, int seg) {
   if (boxes <= kTapsHereBoxes || H < kTallSeg) return false;
@@ -296,7 +297,7 @@ static void fwd_lds_t(const void* x, const int* taps, const float* boxes, void* 
     constexpr bool kOneSeg = kOffset || std::is_same<T, int>::value;
     const int nch = (W + Q - 1) / Q, seg = pc && !kOneSeg ? fwd_seg(H, nch) : 8;
     const bool lanes = pc > 0 && seg == 8 && nch * n_segs(H, seg) <= 32 && B > 1;
-    const bool tall = sizeof(OutT) == 4 && !lanes && fwd_tall_items((long)N * C * B, H, W, seg);
+    const bool tall = sizeof(OutT) == 4 && pc > 0 && !lanes && fwd_tall_items((long)N * C * B, H, W, seg);
     const int per_box = tall ? n_chunks(W) * n_segs(H, kTallSeg) : nch * n_segs(H, seg);
     const int bpw = lanes ? std::min(64 / per_box, B) : 1;
     const FwdGeom g = fwd_geom_items(N, C, (B + bpw - 1) / bpw, bpw * per_box, kFwdThreads);
@@ -330,10 +331,11 @@ static void fwd_lds_t(const void* x, const int* taps, const float* boxes, void* 
       if (tall) {
         with_flag(rounded, [&](auto ki) {
           with_pitch(pc, [&](auto kp) {
-            hipLaunchKernelGGL((k_box_fwd_lds<T, OutT, kTallSeg, kOffset, decltype(ki)::value, decltype(kp)::value, kQ, 0,
-                                              false, false, false>),
-                               dim3(N * C * g.ngrp), dim3(g.threads), shm, s, (const T*)x, taps, boxes, (OutT*)y, C, H,
-                               W, B, 1, g.bpg, g.per_box_p);
+            if constexpr (decltype(kp)::value > 0)
+              hipLaunchKernelGGL((k_box_fwd_lds<T, OutT, kTallSeg, kOffset, decltype(ki)::value, decltype(kp)::value, kQ,
+                                                0, false, false, false>),
+                                 dim3(N * C * g.ngrp), dim3(g.threads), shm, s, (const T*)x, taps, boxes, (OutT*)y, C, H,
+                                 W, B, 1, g.bpg, g.per_box_p);
           });
         });
         return;
