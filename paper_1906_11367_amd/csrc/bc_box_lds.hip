@@ -399,6 +399,14 @@ static void bwd_lds_t(const float* x, const int* taps, const float* boxes, const
   const int Ho = (H + stride - 1) / stride, Wo = (W + stride - 1) / stride;
   const bool tail = W < kQ || H < SEG;
   int pc = tail ? 0 : lds_pitch_class(H, W);
+  // Tables from registers load a row per wave: narrow maps of more rows than
+  // their waves' bands leave most lanes idle strip after strip, and are staged
+  // instead (at run-time pitch).  2046 maps of 98x12, 4 boxes: 54 us from
+  // registers, 37 staged; 3114 of 50x24, 8 boxes 89 and 71; 4096 of 100x30, 4
+  // boxes 121 and 147, of 32x12 (one strip) 31 and 36.  Calls of few
+  // maps (4-row items, more waves a map) keep the registers: 128 maps of 64x16,
+  // 8 boxes 28 and 35.
+  if (SEG == 8 && stride == 1 && W <= 24 && H > threads / 64 * 32) pc = 0;
   if (stride > 2) pc = 0;  // the whole upsampled map is tabulated at run-time pitch
   const bool half = stride == 2 && pc > 0;
   const size_t shm = table_lds_bytes(half ? Ho : H, W, pc, threads);

@@ -61,9 +61,11 @@ def test_lds_box_edges(H, W, B):
     check(host(dx), O.box_backward_input(g, bx, H, W, integer_corners=True), RTOL_F32, "dx, integer corners")
 
 
-@pytest.mark.parametrize("H,W", [(9, 47), (16, 61), (17, 62), (33, 63), (64, 64), (31, 65), (40, 95)])
+@pytest.mark.parametrize("H,W", [(9, 47), (16, 61), (17, 62), (33, 63), (64, 64), (31, 65), (40, 95), (98, 12), (65, 5),
+                                 (33, 24), (32, 24), (33, 25)])
 def test_lds_box_edges_many_maps(H, W):
-    """Enough maps for the 8-row items (2048 waves of them)."""
+    """Enough maps for the 8-row items (2048 waves of them); narrow maps taller
+    than their waves' bands are tabulated at run-time pitch."""
     N, C, B = 16, 128, 2
     x, bx, g = case(H + W, N, C, H, W, B)
     dx, db = torch.empty((N, C, H, W), device="cuda"), torch.empty((C, B, 4), device="cuda")
