@@ -241,7 +241,8 @@ static bc_status box_bwd_impl(const float* x, const float* boxes, const float* g
   if (path == BoxPath::Stream) {
     e = bc::launch_box_bwd_stream(x, taps, grad_y, grad_x, partials, N, C, H, W, B, rounded, relu_bf16, stream);
   } else if (!hbm) {
-    e = bc::launch_box_bwd_lds(x, taps, here ? boxes : nullptr, grad_y, grad_x, partials, N, C, H, W, B, rounded, relu_bf16, stride, stream);
+    e = bc::launch_box_bwd_lds(x, taps, here ? boxes : nullptr, grad_y, grad_x, partials, N, C, H, W, B, rounded, relu_bf16,
+                                stride, stream);
   } else {
     float* sat_g = reinterpret_cast<float*>(base + L.sat_g);
     const size_t gy_n = (size_t)N * C * B * ((H + stride - 1) / stride) * ((W + stride - 1) / stride);

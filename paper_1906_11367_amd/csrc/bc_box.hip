@@ -144,7 +144,7 @@ __global__ __launch_bounds__(256 * kGroups) void k_sat_build(const T* __restrict
           v[k] = run;
         }
       }
-      const T excl = group_excl<64, false>(run);
+      const T excl = group_excl<64>(run);
 #pragma unroll
       for (int k = 0; k < KM; ++k) {
         const int idx = lane * K + k;
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(256 * kGroups) void k_sat_build(const T* __restrict
             v[i][k] = run;
           }
         }
-        const T excl = group_excl<64, false>(run);
+        const T excl = group_excl<64>(run);
         if (rr < rows) {
 #pragma unroll
           for (int k = 0; k < KM; ++k) {
@@ -330,10 +330,9 @@ __global__ __launch_bounds__(256) void k_box_fwd_gather_strided(const T* __restr
 // VGPRs allowed, with it 129, so there the bound is set (3 x 63 maps of 106x583,
 // 4 boxes: 414 us without, 400 with).
 template <int SEG, bool kInt, bool kRelu>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kRelu ? 4 : 3, 8))) void k_box_bwd_gather(const float* __restrict__ x, const float* __restrict__ sat_g,
-                                                        const int* __restrict__ taps, void* __restrict__ gx,
-                                                        float* __restrict__ partials, int C, int H, int W, int B,
-                                                        int nblk, int total) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kRelu ? 4 : 3, 8))) void k_box_bwd_gather(
+    const float* __restrict__ x, const float* __restrict__ sat_g, const int* __restrict__ taps, void* __restrict__ gx,
+    float* __restrict__ partials, int C, int H, int W, int B, int nblk, int total) {
   const int L = xcd_remap(blockIdx.x, gridDim.x);
   if (L >= total) return;
   const int blk = L % nblk, map = L / nblk;

@@ -212,7 +212,8 @@ __global__ __launch_bounds__(kMaxT) __attribute__((amdgpu_waves_per_eu(4, 8))) v
       __syncthreads();
       if (b + 1 < B) band.load(g0 + (b + 1) * plane, H, W, uwave * kRows);
     } else if constexpr (kUp == 2) {
-      build_table_bands<float, SEG == 8 && band_cols(kPitch) == 2 ? 8 : 16, band_cols(kPitch), true>(g0 + b * gplane, SG, part, Ho, Wo, pitch, 0.f, false, W);
+      build_table_bands<float, SEG == 8 && band_cols(kPitch) == 2 ? 8 : 16, band_cols(kPitch), true>(
+          g0 + b * gplane, SG, part, Ho, Wo, pitch, 0.f, false, W);
     } else if constexpr (kBands) {
       build_table_bands<float, kRows, band_cols(kPitch)>(g0 + b * plane, SG, part, H, W, pitch, 0.f, false);
     } else {

@@ -3,10 +3,6 @@
 #include "bc_box.hpp"
 
 namespace bc {
-#ifndef SPR
-#define SPR 32
-#endif
-
 // ---------------------------------------------------------------------------
 // Kernel splitting (Section 3.1, Fig. 2): a box cut at its centre line(s)
 // m = (a + b) / 2, n = (c + d) / 2 into nx * ny pieces with their own
@@ -341,10 +337,13 @@ __global__ __launch_bounds__(kMaxT) void k_box_bwd_lds_split(const float* __rest
 #pragma unroll
     for (int q = 0; q < kQ; ++q) acc[s][q] = 0.f;
   const LdsTable<float> tg{SG, pitch, W, H};
+  // rows per band: 8-row items have fewer waves to a map, and with one column a
+  // lane the registers for 32 rows in flight
+  constexpr int kRows = SEG == 8 && band_cols(kPitch) == 1 ? 32 : 16;
   if constexpr (kPitch > 0) table_zero_edges(SG, H, pitch);
   for (int b = 0; b < B; ++b) {
     if constexpr (kPitch > 0) {
-      build_table_bands<float, SEG == 8 && band_cols(kPitch) == 1 ? SPR : 16, band_cols(kPitch)>(
+      build_table_bands<float, kRows, band_cols(kPitch)>(
           g0 + b * plane, SG, SG + (H + 1) * pitch, H, W, pitch, 0.f, false);
     } else {
       __syncthreads();

@@ -157,9 +157,9 @@ __device__ __forceinline__ int med3_i32(int v, int hi) {
 
 // Table accessors.  A walk addresses a table row by an unclamped row
 // coordinate in the table's own units (row_coord(v) for table row v; one row
-// further is + row_step()), row_at(c, j) the row j after c, and the two runs of columns it reads by
-// cols(ba, bb) with ba = x0 + fa, bb = x0 + fb unclamped.  runs<N>(coord, c,
-// sa, sb) returns S(clamp(v, 0, H), clamp(ba + k, 0, W)) and the same at bb,
+// further is + row_step(), the row j after c is row_at(c, j)), and the two runs
+// of columns it reads by cols(ba, bb) with ba = x0 + fa, bb = x0 + fb
+// unclamped.  runs<N>(coord, c, sa, sb) returns S(clamp(v, 0, H), clamp(ba + k, 0, W)) and the same at bb,
 // k in [0, N); N = kQ + 1 for interpolated edges, kQ for integer ones.
 //
 // LDS table, padded: S(u, v) at p[u * pitch + PAD + v], v in [-PAD, W + PAD];
@@ -210,7 +210,9 @@ struct HalfRowTable : LdsTable<float> {
   __device__ __forceinline__ Coord row_coord(int v) const {
     return {((v + 1) >> 1) * row_step(), ((v + 2) >> 1) * row_step()};
   }
-  __device__ __forceinline__ int row_at(const Coord& c, int j) const { return (j & 1 ? c.b : c.a) + (j >> 1) * row_step(); }
+  __device__ __forceinline__ int row_at(const Coord& c, int j) const {
+    return (j & 1 ? c.b : c.a) + (j >> 1) * row_step();
+  }
 };
 
 // Table in HBM, (H+1) x (W+1), unpadded: row coordinates are row indices and
@@ -375,50 +377,32 @@ __device__ __forceinline__ float wave_sum(float v) {
 template <typename T> __device__ __forceinline__ int bits_of(T v) { return __builtin_bit_cast(int, v); }
 template <typename T> __device__ __forceinline__ T of_bits(int v) { return __builtin_bit_cast(T, v); }
 
-// Inclusive prefix (kRev: suffix) sum over the lanes of each group of LG
-// lanes, for every lane.  LG = 16: row shifts within each DPP row; LG = 64:
-// then the row broadcasts carry each row's total into the rows after it.
-template <int LG, bool kRev, typename T>
+// Inclusive prefix sum over the lanes of each group of LG lanes, for every
+// lane.  LG = 16: row shifts within each DPP row; LG = 64: then the row
+// broadcasts carry each row's total into the rows after it.
+template <int LG, typename T>
 __device__ __forceinline__ T group_scan(T v) {
   static_assert(LG == 16 || LG == 64, "groups are DPP rows or whole waves");
-  if constexpr (!kRev) {
-    v += of_bits<T>(__builtin_amdgcn_update_dpp(0, bits_of(v), 0x111, 0xF, 0xF, true));  // row_shr:1
-    v += of_bits<T>(__builtin_amdgcn_update_dpp(0, bits_of(v), 0x112, 0xF, 0xF, true));  // row_shr:2
-    v += of_bits<T>(__builtin_amdgcn_update_dpp(0, bits_of(v), 0x114, 0xF, 0xF, true));  // row_shr:4
-    v += of_bits<T>(__builtin_amdgcn_update_dpp(0, bits_of(v), 0x118, 0xF, 0xF, true));  // row_shr:8
-    if constexpr (LG == 64) {
-      v += of_bits<T>(__builtin_amdgcn_update_dpp(0, bits_of(v), 0x142, 0xA, 0xF, false));  // row_bcast:15
-      v += of_bits<T>(__builtin_amdgcn_update_dpp(0, bits_of(v), 0x143, 0xC, 0xF, false));  // row_bcast:31
-    }
-  } else {
-    v += of_bits<T>(__builtin_amdgcn_update_dpp(0, bits_of(v), 0x101, 0xF, 0xF, true));  // row_shl:1
-    v += of_bits<T>(__builtin_amdgcn_update_dpp(0, bits_of(v), 0x102, 0xF, 0xF, true));  // row_shl:2
-    v += of_bits<T>(__builtin_amdgcn_update_dpp(0, bits_of(v), 0x104, 0xF, 0xF, true));  // row_shl:4
-    v += of_bits<T>(__builtin_amdgcn_update_dpp(0, bits_of(v), 0x108, 0xF, 0xF, true));  // row_shl:8
-    if constexpr (LG == 64) {
-      // rows after this one: lane 0 of the next row holds that row's total,
-      // then the rows beyond it (a reversed scan of the four row totals)
-      const int lane = threadIdx.x & 63, row = lane >> 4;
-      const T t1 = __shfl(v, ((row + 1) & 3) << 4, 64);
-      const T t2 = __shfl(v, ((row + 2) & 3) << 4, 64);
-      const T t3 = __shfl(v, ((row + 3) & 3) << 4, 64);
-      v += (row < 3 ? t1 : (T)0) + (row < 2 ? t2 : (T)0) + (row < 1 ? t3 : (T)0);
-    }
+  v += of_bits<T>(__builtin_amdgcn_update_dpp(0, bits_of(v), 0x111, 0xF, 0xF, true));  // row_shr:1
+  v += of_bits<T>(__builtin_amdgcn_update_dpp(0, bits_of(v), 0x112, 0xF, 0xF, true));  // row_shr:2
+  v += of_bits<T>(__builtin_amdgcn_update_dpp(0, bits_of(v), 0x114, 0xF, 0xF, true));  // row_shr:4
+  v += of_bits<T>(__builtin_amdgcn_update_dpp(0, bits_of(v), 0x118, 0xF, 0xF, true));  // row_shr:8
+  if constexpr (LG == 64) {
+    v += of_bits<T>(__builtin_amdgcn_update_dpp(0, bits_of(v), 0x142, 0xA, 0xF, false));  // row_bcast:15
+    v += of_bits<T>(__builtin_amdgcn_update_dpp(0, bits_of(v), 0x143, 0xC, 0xF, false));  // row_bcast:31
   }
   return v;
 }
 
-// Exclusive form of group_scan: the inclusive scan moved one lane along the
-// scan direction (lane 0 of the group, or its last lane when reversed, gets 0
-// from bound_ctrl).  Taking the neighbour's inclusive value, rather than
-// subtracting the lane's own value from its inclusive scan, keeps a lane's
-// earlier columns exact when a later column holds a NaN or an infinity, and
-// costs the same one instruction.
-template <int LG, bool kRev, typename T>
+// Exclusive form of group_scan: the inclusive scan moved one lane along (lane
+// 0 of the group gets 0 from bound_ctrl).  Taking the neighbour's inclusive
+// value, rather than subtracting the lane's own value from its inclusive scan,
+// keeps a lane's earlier columns exact when a later column holds a NaN or an
+// infinity, and costs the same one instruction.
+template <int LG, typename T>
 __device__ __forceinline__ T group_excl(T v) {
-  const T incl = group_scan<LG, kRev>(v);
-  constexpr int ctrl = kRev ? (LG == 16 ? 0x101 : 0x130)    // row_shl:1 / wave_shl:1
-                            : (LG == 16 ? 0x111 : 0x138);   // row_shr:1 / wave_shr:1
+  const T incl = group_scan<LG>(v);
+  constexpr int ctrl = LG == 16 ? 0x111 : 0x138;  // row_shr:1 / wave_shr:1
   return of_bits<T>(__builtin_amdgcn_update_dpp(0, bits_of(incl), ctrl, 0xF, 0xF, true));
 }
 

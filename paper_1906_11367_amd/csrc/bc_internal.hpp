@@ -14,8 +14,10 @@ inline int lds_pitch(int W) { return (W + 7) | 1; }
 
 // Row pitches compiled into the LDS kernels (0: none applies): the smallest of
 // three, for maps up to 48, 64 and 96 wide, whose rows then have constant
-// offsets; narrower maps waste the difference, so the table must still leave
-// room for four blocks per CU (40 KiB), which all maps up to 96x96 do.
+// offsets; narrower maps waste the difference, so the table alone may take at
+// most a quarter of a CU's LDS (40 KiB), which all maps up to 96x96 keep to.
+// The band totals and the forward's wider padding come on top: a 96x96 forward
+// in blocks of 512 threads asks for about 50 KiB, three blocks per CU.
 constexpr size_t kLdsClassBytes = 40 * 1024;
 inline int lds_pitch_class(int H, int W) {
   const int p = W <= 48 ? 55 : W <= 64 ? 71 : W <= 96 ? 103 : 0;

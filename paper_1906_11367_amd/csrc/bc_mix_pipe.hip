@@ -351,7 +351,7 @@ hipError_t launch_mix_fwd_pipe(const void* w, const void* in, float* out, int N,
   return M > 128 ? fwd_pipe<4, 2>(w, in, out, N, M, K, P, relu, s) : fwd_pipe<2, 4>(w, in, out, N, M, K, P, relu, s);
 }
 
-// Splits of the weight gradient's reduction: one block per CU.
+// Tiles of the weight gradient.
 static int wgrad_tiles(int M, int K) { return ((M + 255) / 256) * ((K + 127) / 128); }
 
 bool mix_wgrad_pipe_takes(const void* grad, const void* in, int N, int M, int K, int P) {

@@ -301,7 +301,7 @@ __global__ __launch_bounds__(LG * NG) void k_box_bwd_stream(const float* __restr
       pd[k] += gd_[k];
     }
     const float tot = s[CPL - 1];
-    const float off = group_excl<LG, false>(tot);
+    const float off = group_excl<LG>(tot);
 #pragma unroll
     for (int k = 0; k < CPL; ++k) sy[iw[k]] = s[k] + off;
     if (p == LG - 1) {
@@ -313,7 +313,7 @@ __global__ __launch_bounds__(LG * NG) void k_box_bwd_stream(const float* __restr
       float pfx[CPL];
 #pragma unroll
       for (int k = 0; k < CPL; ++k) pfx[k] = k ? pfx[k - 1] + v[k] : v[k];
-      const float voff = group_excl<LG, false>(pfx[CPL - 1]);
+      const float voff = group_excl<LG>(pfx[CPL - 1]);
 #pragma unroll
       for (int k = 0; k < CPL; ++k) sv[iw[k]] = pfx[k] + voff;
       if (p == LG - 1) {
@@ -546,7 +546,7 @@ __global__ __launch_bounds__(LG * NG) void k_box_fwd_stream(const T* __restrict_
       pd[k] += gd_[k];
     }
     const T tot = s[CPL - 1];
-    const T off = group_excl<LG, false>(tot);
+    const T off = group_excl<LG>(tot);
 #pragma unroll
     for (int k = 0; k < CPL; ++k) sy[iw[k]] = s[k] + off;
     if (p == LG - 1) {

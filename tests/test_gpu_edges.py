@@ -366,6 +366,26 @@ def test_mix_data_gradient_ends(dims, relu, stored):
     assert hit[0, :, P - 1].all() and int(hit.sum()) == K
 
 
+@pytest.mark.parametrize("dims", [(72, 256, 64, 1032), (72, 256, 128, 1024), (90, 128, 64, 2056), (40, 136, 192, 2056)])
+@pytest.mark.parametrize("relu", [0, 1])
+def test_mix_blocks_of_several_whole_tiles(dims, relu):
+    """The pipelined forward on reductions of one to three K-steps, more tiles
+    than blocks: a whole tile's stores are in flight while the next one's loads
+    are waited for, a ragged tile follows a whole one on the same block."""
+    N, M, K, P = dims
+    say(f"mix several tiles {dims} relu={relu}")
+    gen = torch.Generator(device="cuda").manual_seed(15)
+    w = (torch.randn(M, K, generator=gen, device="cuda") / K ** 0.5).bfloat16()
+    o = torch.randn(N, K, P, generator=gen, device="cuda").bfloat16()
+    z = torch.full((N, M, P), float("nan"), device="cuda")
+    bc.pointwise_mix(bc.BC_MIX_FWD, w, o, z, N, M, K, P, bc.BC_BF16, relu=relu)
+    ref = torch.matmul(w.double(), o.double())
+    ref = ref.clamp(min=0) if relu else ref
+    # products of bf16 pairs are exact; each of the K additions rounds by 2^-24 of a partial sum
+    bound = (K + 1) * 2.0 ** -24 * torch.matmul(w.double().abs(), o.double().abs())
+    assert ((z.double() - ref).abs() <= bound).all()
+
+
 @pytest.mark.parametrize("dims", [(2, 72, 97, 243), (24, 200, 64, 1032), (2, 140, 130, 640), (2, 72, 136, 264)])
 def test_mix_keeps_a_nan_in_its_place(dims):
     """A NaN in one row of an operand, next to a tile's or a row's end, reaches
