@@ -911,10 +911,14 @@ static bool mix_small(int rows, int cols, long zt, long fill = kMixFillBlocks) {
 // K-step at most fills half of the twice as deep step of the 64-wide tiles, so
 // there one block per CU is enough for the others (int32, 21 x 120 x 8 x 3072 in
 // N, M, K, P, 504 128-wide tiles: 13.0 us with those, 17.9 with 64-wide ones; 126
-// of them or fewer: 0.7 of the time with 64-wide tiles).
+// of them or fewer: 0.7 of the time with 64-wide tiles).  In fp32 two whole
+// steps of 32 are as good on the wide tiles (50 x 100 x 64 x 1024, 400 of them:
+// 13.7 and 17.2), a second one of 31 is not (30 x 256 x 63 x 1000: 21.3 and 17.7).
+static bool mix_shallow_f32(int depth) { return depth <= 32 || depth == 64; }
 template <bool BF16>
 static int mix_tile(int rows, int cols, long zt, int depth) {
-  return mix_small(rows, cols, zt, depth <= (BF16 ? 64 : 32) ? kMixFillBlocks / 2 : kMixFillBlocks) ? 64 : 128;
+  const bool shallow = BF16 ? depth <= 64 : mix_shallow_f32(depth);
+  return mix_small(rows, cols, zt, shallow ? kMixFillBlocks / 2 : kMixFillBlocks) ? 64 : 128;
 }
 
 struct WeightSplit { int tile, sp, chunk, S; };
@@ -1029,7 +1033,8 @@ static hipError_t launch_mix_t(int mode, const void* a, int a_dt, const void* b,
         return launch_mix_fwd_pipe(a, b, (float*)out, N, M, K, P, relu, s);
     }
     if constexpr (!BF16) {
-      if (a_dt == 1 && b_dt == 1 && out_dt == 1 && mix_small(M, P, N) &&
+      if (a_dt == 1 && b_dt == 1 && out_dt == 1 &&
+          mix_small(M, P, N, K == 64 ? kMixFillBlocks / 2 : kMixFillBlocks) &&
           mix_f32_direct_takes(true, N, M, K, P))
         return launch_mix_f32_direct(true, (const float*)a, (const float*)b, nullptr, (float*)out, N, M, K, P, relu, s);
     }

@@ -165,7 +165,10 @@ long tiles32(int rows, int P, int N, int ct) {
 
 // FWD: K a multiple of 4 (16-byte runs of w's rows); the caller asks only where
 // the tiled kernel would take 64-wide tiles (elsewhere its 128-wide ones reuse
-// more: 4 x 128 x 1024 x 65536 in N, M, K, P 546 us tiled, 697 here).
+// more: 4 x 128 x 1024 x 65536 in N, M, K, P 546 us tiled, 697 here), and at two
+// whole K-steps of those (K = 64) only where one block per CU would not be full
+// either (14 x 256 x 64 x 2048, 448 of them: 14.7 us tiled, 22.8 here; 12 x 256 x
+// 32 x 2048 11 and 8.6).
 // BWD_DATA: where M and K are short, so that the tiled kernel's padding and its
 // one or two K-steps cost most (2 x 48 x 128 x 110592 61 us tiled, 47 here; 4 x
 // 17 x 96 x 2451 7.9 and 4.2); with more of either the re-reading of the
@@ -187,9 +190,11 @@ hipError_t launch_mix_f32_direct(bool fwd, const float* w, const float* b, const
   // (1024): two, unless that takes a quarter more rounds of column tiles (us with
   // two and with one: 8 x 64 x 512 x 3072, as many rounds, 21 and 27; 51 x 128 x
   // 896 x 1024, 8 rounds and 7, 114 and 142; 1 x 256 x 1024 x 3072, 2 and 1, 35
-  // and 22)
+  // and 22); any more rounds at reductions of 36 to 128, which have less of w to
+  // reuse (10 x 256 x 128 x 2048, 6 rounds and 5, 24.4 and 20.8; 20 x 256 x 56 x
+  // 1024, 14.7 and 12.5; at 32 the stores decide: 28 x 208 x 32 x 1024 10.8 and 13)
   const long two = 2 * ((tiles32(M, P, N, 2) + 1023) / 1024), one = (tiles32(M, P, N, 1) + 1023) / 1024;
-  return 4 * two <= 5 * one ? go<true, false, 2>(w, b, nullptr, out, N, M, K, P, relu, s)
+  return 4 * two <= (K > 32 && K <= 128 ? 4 : 5) * one ? go<true, false, 2>(w, b, nullptr, out, N, M, K, P, relu, s)
                     : go<true, false, 1>(w, b, nullptr, out, N, M, K, P, relu, s);
 }
 

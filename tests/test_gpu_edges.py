@@ -298,7 +298,7 @@ def test_mix_f32_short(dims):
 # (the ends of tiles of 64 and 128, reductions inside and just past a K-step);
 # rows of none (K = 37); and short reductions on 128-wide tiles.
 ALIGNED = [(1, 8, 8, 8), (2, 72, 40, 136), (1, 129, 200, 264), (3, 130, 520, 1096), (2, 64, 37, 200), (9, 8, 256, 3072),
-           (21, 120, 8, 1024)]
+           (21, 120, 8, 1024), (16, 130, 64, 1100), (5, 64, 130, 4100)]
 
 
 @pytest.mark.parametrize("dims", ALIGNED)
