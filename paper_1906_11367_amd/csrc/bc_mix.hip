@@ -387,13 +387,20 @@ __device__ __forceinline__ void epilogue(const f32x16_t (&acc)[TT][TT], char* cb
 // block), so a third resident block per CU pays whenever the variant still
 // fits in 168 registers without spilling -- the accumulators then move from
 // AGPRs to VGPRs.  Variants that would spill (l-contiguous masked or fp32
-// operands in bf16 compute, the bf16 weight-gradient GEMM) keep two.
-template <bool BF16, int ADT, bool AKC, bool AMASK, int BDT, bool BKC, bool BMASK>
+// operands in bf16 compute, the bf16 weight-gradient GEMM) keep two.  Loads from
+// clamped addresses (kVec false) take more: where one in flight was spilled, and
+// so waited for, 2 x 940 x 763 x 2451 in N, M, K, P, masked, took 145 us instead
+// of 56, the weight gradient of 11 x 808 x 8 x 572 18.6 instead of 14.6.
+template <bool BF16, int ADT, bool AKC, bool AMASK, int BDT, bool BKC, bool BMASK, int kTile, bool kVec>
 constexpr int mix_waves() {
+  if (kTile == 64) {
+    if (!BF16 || kVec || !(AMASK || BMASK)) return 3;
+    return (AKC ? ADT == 1 && BDT == 2 : BDT == 1) ? 3 : 2;
+  }
   if (!BF16) return (AKC && AMASK) ? 2 : 3;
   if (AMASK || BMASK) return 2;
   if (AKC && !BKC) return (ADT == 2 && BDT == 2) ? 3 : 2;
-  if (!AKC && !BKC) return (ADT == 1 && BDT == 1) ? 2 : 3;
+  if (!AKC && !BKC) return (ADT == 1 && BDT == 1) || !kVec ? 2 : 3;
   return 2;
 }
 
@@ -415,7 +422,8 @@ constexpr int mix_depth() {
 
 template <bool BF16, int ADT, bool AKC, bool AMASK, int BDT, bool BKC, bool BMASK, int kTile, bool kVecA, bool kVecB>
 __global__ __launch_bounds__(kMixThreads)
-__attribute__((amdgpu_waves_per_eu(kTile == 64 ? 3 : mix_waves<BF16, ADT, AKC, AMASK, BDT, BKC, BMASK>(), 8))) void k_mix_gemm(
+__attribute__((amdgpu_waves_per_eu(mix_waves<BF16, ADT, AKC, AMASK, BDT, BKC, BMASK, kTile, kVecA && kVecB>(), 8))) void
+k_mix_gemm(
     const void* __restrict__ a, const void* __restrict__ b, const float* __restrict__ aux, void* __restrict__ out,
     int rows, int cols, int depth, long lda, long ldb, long ldc, long a_bs, long b_bs, long c_bs,
     int mt, int nt, int zt, int nsplit_p, int pchunk, int out_kind, int relu) {
@@ -915,9 +923,10 @@ static bool mix_small(int rows, int cols, long zt, long fill = kMixFillBlocks) {
 // steps of 32 are as good on the wide tiles (50 x 100 x 64 x 1024, 400 of them:
 // 13.7 and 17.2), a second one of 31 is not (30 x 256 x 63 x 1000: 21.3 and 17.7).
 static bool mix_shallow_f32(int depth) { return depth <= 32 || depth == 64; }
+// Not so for int32, converted on its way (16 x 136 x 64 x 1903: 17.4 and 14.1).
 template <bool BF16>
-static int mix_tile(int rows, int cols, long zt, int depth) {
-  const bool shallow = BF16 ? depth <= 64 : mix_shallow_f32(depth);
+static int mix_tile(int rows, int cols, long zt, int depth, bool i32 = false) {
+  const bool shallow = BF16 ? depth <= 64 : i32 ? depth <= 32 : mix_shallow_f32(depth);
   return mix_small(rows, cols, zt, shallow ? kMixFillBlocks / 2 : kMixFillBlocks) ? 64 : 128;
 }
 
@@ -1040,7 +1049,7 @@ static hipError_t launch_mix_t(int mode, const void* a, int a_dt, const void* b,
     }
     with_dts<BF16, true>(a_dt, b_dt, [&](auto ad, auto bd) {
       gemm_launch<BF16, decltype(ad)::value, true, false, decltype(bd)::value, false, false>(
-          mix_tile<BF16>(M, P, N, K), a, b, nullptr, out, M, P, K, K, P, P, 0, (long)K * P, (long)M * P, N, 0, 0, ok_fwd, relu, s);
+          mix_tile<BF16>(M, P, N, K, a_dt == 0), a, b, nullptr, out, M, P, K, K, P, P, 0, (long)K * P, (long)M * P, N, 0, 0, ok_fwd, relu, s);
     });
     return hipGetLastError();
   }
