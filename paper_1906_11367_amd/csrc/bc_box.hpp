@@ -172,7 +172,7 @@ __device__ __forceinline__ typename Vec4<T>::type load_stream4(const typename Ve
 // not stored, so no lane branches around a load).  Then a column pass (lanes
 // own columns) and the row pass, each reading kScan elements ahead before it
 // writes.  With `sub`, mu is subtracted from the tabulated values.
-template <typename T, bool kSkip = false>
+template <typename T, int kSkip = 0>
 __device__ void build_table_lds(const T* __restrict__ src, T* S, int H, int W, int pitch, float mu, bool sub) {
   using V = typename Vec4<T>::type;
   constexpr int kBatch = 8;
@@ -216,7 +216,7 @@ __device__ void build_table_lds(const T* __restrict__ src, T* S, int H, int W, i
     int j = tid % W;
     int o = (tid / W + 1) * pitch + j + 1;
     const int step = di * pitch + dj, wrap = pitch - W;
-    constexpr int kBatch1 = kSkip ? 2 : 4;  // more take 82 VGPRs in the forward instead of 53
+    constexpr int kBatch1 = kSkip ? kSkip : 4;
     for (int base = 0; base < n; base += nt * kBatch1) {
       T q[kBatch1];
 #pragma unroll

@@ -71,7 +71,11 @@ __global__ __launch_bounds__(kFwdThreads) void k_box_fwd_lds(const T* __restrict
     table_zero_edges<PAD>(S, H, pitch);
     build_table_bands<T, 16, band_cols(kPitch), false, PAD>(src, S, S + (H + 1) * pitch, H, W, pitch, mu, kOffset);
   } else {
-    build_table_lds<T, true>(src, S, H, W, pitch, mu, kOffset);
+    // Words ahead where rows have no alignment.  Eight take 82 VGPRs instead of
+    // 53, which the small tables (kTail) pay for in waves (12 x 212 maps of 14x2, 5
+    // boxes 38 us with eight, 29 with two); the others have at most three blocks
+    // on a CU by their LDS (2 x 314 of 171x82, 3 boxes 87 with eight, 107 with two).
+    build_table_lds<T, kTail ? 2 : 8>(src, S, H, W, pitch, mu, kOffset);
   }
   const int g0 = grp * bpg;
   fwd_boxes<T, OutT, SEG, kOffset, kInt, Q, kPack, kTail, kHere, kLanes>(LdsTable<T, PAD>{S, pitch, W, H}, taps, boxes,
@@ -266,16 +270,16 @@ static int fwd_seg(int H, int nch) {
 // 16- and an 8-byte store per lane, each of which writes parts of its lines;
 // three go out as 12 bytes a lane, whole lines together.  Calls of many maps
 // are bound by those stores (32 x 256 maps of 64x48, 4 boxes: 127 us with six
-// columns, 104 with three) unless the narrow items cost clearly more waves x
-// rows x columns (72x80 maps: 171 against 132, and 161 us become 238 with the
-// mean); calls of few maps run on latency and keep the wide items, and tables
+// columns, 104 with three) unless the narrow items cost more waves x rows x
+// columns, a tenth or above (15 x 84 maps of 54x64: 114 against 96, 25 us become
+// 30; 72x80: 171 and 132, 161 us become 238 with the mean); calls of few maps run on latency and keep the wide items, and tables
 // of run-time pitch gain nothing (21 x 133 maps of 109x96: 64 us either way).
 constexpr int kTallSeg = 16;
 static bool fwd_tall_items(long boxes, int H, int W, int seg) {
   if (boxes <= kTapsHereBoxes || H < kTallSeg) return false;
   const long wide = (long)(((W + 5) / 6 * n_segs(H, seg) + 63) / 64) * (seg + 3) * 6;
   const long tall = (long)((n_chunks(W) * n_segs(H, kTallSeg) + 63) / 64) * (kTallSeg + 3) * kQ;
-  return 5 * tall <= 6 * wide;
+  return 10 * tall <= 11 * wide;
 }
 
 template <typename T, typename OutT, bool kOffset>

@@ -79,11 +79,11 @@ def test_mix_loads_stay_in_flight(device_code, a, b, tile):
 # blocks of 512 threads of the streaming backward, two per CU; the backward from
 # tables in memory, four waves per SIMD, two registers of the masked one spilled;
 # the mix, two waves or three and nothing in memory, where a load in flight would
-# be waited for; the forward on tables of run-time pitch, eight waves
+# be waited for; the forward of maps smaller than an item, eight waves
 @pytest.mark.parametrize("pattern,registers,spilled", [(r"k_box_bwd_streamILi64ELi\dELi8E", 128, 0),
                                                        (r"k_box_bwd_gatherI", 128, 8),
                                                        (r"k_mix_gemmI", 256, 0),
-                                                       (r"k_box_fwd_ldsI\w+?Li\d+ELb\dELb\dELi0E", 64, 0)])
+                                                       (r"k_box_fwd_ldsI\w+?Li\d+ELb\dELb\dELi0ELi3ELi0ELb1E", 64, 0)])
 def test_waves_per_simd(device_code, pattern, registers, spilled):
     readelf = _tool("llvm-readelf")
     seen = 0
