@@ -187,7 +187,7 @@ template <int LG> __device__ __forceinline__ int group_uniform(int v) {
 // written as bf16(x > 0 ? dx : 0).  partials: [n][C*B][4] edge gradients
 // (one row per image).
 // ---------------------------------------------------------------------------
-template <int LG, int CPL, int NG, bool kInt, bool kRelu, bool kVec>
+template <int LG, int CPL, int NG, bool kInt, bool kRelu, bool kVec, bool kRing>
 __global__ __launch_bounds__(LG * NG) void k_box_bwd_stream(const float* __restrict__ x, const int* __restrict__ taps,
                                                             const float* __restrict__ gy, void* __restrict__ gx,
                                                             float* __restrict__ partials, int C, int H, int W, int B,
@@ -273,12 +273,6 @@ __global__ __launch_bounds__(LG * NG) void k_box_bwd_stream(const float* __restr
   // rows of step y: the input row v, gc_ = G(y + fc), gd_ = G(y + fd).  kRing:
   // a ring of PF + 1 steps with the loop unrolled over it; else a queue whose
   // rows are copied forward (up to 24 moves a step, but one copy of the step).
-  // With all gradients the unrolled form takes 187 VGPRs for 4 columns and 148
-  // for 3: one block of 512 threads per CU.  4 x 128 maps, ring and queue: 256
-  // x 256, 8 boxes 565 and 473 us; 256 x 160, 8 boxes 519 and 465; 256 x 130, 4
-  // boxes (blocks of 256) 227 and 253.  16 x 128 maps of 400 x 46, 6 boxes 722
-  // and 630.
-  constexpr bool kRing = CPL < 3 || (CPL == 3 && NG == 4) || kInt;
   constexpr int RS = kRing ? PF + 1 : PF;
   float qv[RS][CPL], qc[RS][CPL], qd[RS][CPL];
   auto issue = [&](int y, float (&v)[CPL], float (&gc_)[CPL], float (&gd_)[CPL]) {
@@ -687,9 +681,26 @@ static void bwd_stream_t(const float* x, const int* taps, const float* gy, void*
   constexpr int RW = stream_row_words<LG, CPL>();
   const size_t shm = ((size_t)2 * NG * RW + (size_t)2 * R * NG * slot_words<LG, CPL>()) * sizeof(float);
   const dim3 grid(N * C), block(LG * NG);
+  // Rows in a ring or a queue.  With all gradients the ring's unrolled loop takes
+  // 187 VGPRs for 4 columns and 148 for 3: one block of 512 threads per CU.  4 x
+  // 128 maps, ring and queue: 256 x 256, 8 boxes 565 and 473 us; 256 x 160, 8
+  // boxes 519 and 465; 256 x 130, 4 boxes (blocks of 256) 227 and 253.  16 x 128
+  // maps of 400 x 46, 6 boxes 722 and 630.  Calls whose blocks are all resident
+  // with the ring as well keep it: 3 x 44 maps of 132 x 136, 8 boxes, masked, 131
+  // and 163; 5 x 80 of 400 x 46 (blocks of 128, six a CU) 305 and 361.
   auto go = [&](auto ki, auto kr, auto kv) {
-    hipLaunchKernelGGL((k_box_bwd_stream<LG, CPL, NG, decltype(ki)::value, decltype(kr)::value, decltype(kv)::value>),
-                       grid, block, shm, s, x, taps, gy, gx, partials, C, H, W, B, R);
+    auto launch = [&](auto kring) {
+      hipLaunchKernelGGL((k_box_bwd_stream<LG, CPL, NG, decltype(ki)::value, decltype(kr)::value, decltype(kv)::value,
+                                           decltype(kring)::value>),
+                         grid, block, shm, s, x, taps, gy, gx, partials, C, H, W, B, R);
+    };
+    constexpr bool kInt = decltype(ki)::value;
+    if constexpr (CPL == 3 && NG == 8 && !kInt) {
+      if ((long)N * C <= (LG == 16 ? 6 * 256 : 256)) launch(std::true_type{});
+      else launch(std::false_type{});
+    } else {
+      launch(std::integral_constant<bool, CPL <= 3 || kInt>{});
+    }
   };
   auto with_vec = [&](auto ki, auto kr) {
     if constexpr (CPL == 4) {
