@@ -487,12 +487,21 @@ hipError_t launch_box_prep_corners(const float* boxes, const float* piece_w, int
   return last_error();
 }
 
+// Narrow maps of several strips of bands are staged, as for whole boxes, in calls
+// of four waves per CU and more: two strips where one wave walks them alone, three
+// elsewhere (backward of 2 x 3141 maps of 86x8, 8 boxes 324 us from registers, 227
+// staged; 6 x 519 of 50x24, 8 boxes 149 and 122; two waves and two strips, 8 x 512
+// of 100x22, 4 boxes 147 and 164; forward of 10 x 598 of 80x12 57 and 44).
+static bool split_staged(int W, int H, int waves, long blocks) {
+  return W <= 24 && H > waves * (waves == 1 ? 32 : 64) && blocks * waves >= 1024;
+}
+
 template <typename OutT, int NXC, int NYC>
 static void fwd_split_t(const float* x, const int* rec, void* y, int N, int C, int H, int W, int B, hipStream_t s) {
   constexpr int SEG = 16;
   const FwdGeom g = fwd_geom_items(N, C, B, n_chunks(W) * n_segs(H, SEG), 256);
   const bool tail = W < kQ || H < SEG;
-  const int pc = tail ? 0 : lds_pitch_class(H, W);
+  const int pc = tail || split_staged(W, H, g.threads / 64, (long)N * C * g.ngrp) ? 0 : lds_pitch_class(H, W);
   const size_t shm = table_lds_bytes(H, W, pc, g.threads);
   auto go = [&](auto kp, auto kt) {
     hipLaunchKernelGGL((k_box_fwd_lds_split<OutT, SEG, NXC, NYC, decltype(kp)::value, decltype(kt)::value>),
@@ -529,7 +538,7 @@ template <int SEG, int NXC, int NYC, int kMaxT>
 static void bwd_split_t(const float* x, const int* rec, const float* gy, float* gx, float* partials, int N, int C,
                         int H, int W, int B, hipStream_t s) {
   const int threads = ((n_chunks(W) * n_segs(H, SEG) + 63) / 64) * 64;
-  const int pc = lds_pitch_class(H, W);
+  const int pc = SEG == 8 && split_staged(W, H, threads / 64, (long)N * C) ? 0 : lds_pitch_class(H, W);
   const size_t shm = table_lds_bytes(H, W, pc, threads);
   with_pitch(pc, [&](auto kp) {
     hipLaunchKernelGGL((k_box_bwd_lds_split<SEG, NXC, NYC, kMaxT, decltype(kp)::value>), dim3(N * C), dim3(threads),

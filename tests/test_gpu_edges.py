@@ -140,6 +140,31 @@ def test_split_edges(H, W, mode):
     check(host(dw), rw, RTOL_F32, "dpieces")
 
 
+@pytest.mark.parametrize("H,W", [(33, 24), (32, 24), (70, 5), (65, 12), (33, 25)])
+def test_split_narrow_many_maps(H, W):
+    """Calls that fill the chip stage the tables of narrow maps taller than
+    their waves' bands; the same calls of few maps load them row by row."""
+    N, C, B = 2, 1040, 2
+    say(f"split narrow {H}x{W}")
+    x, bx, g = case(H * 5 + W, N, C, H, W, B)
+    pw = np.random.default_rng(6).uniform(-1, 1, (C, B, 4)).astype(np.float32)
+    outs = []
+    for c0, c1 in [(0, C), (0, 8), (C - 8, C)]:
+        xd, bd, wd = dev(x[:, c0:c1]).contiguous(), dev(bx[c0:c1]), dev(pw[c0:c1])
+        gd = dev(g.reshape(N, C, B, H, W)[:, c0:c1]).reshape(N, -1, H, W).contiguous()
+        y, dx = torch.empty_like(gd), torch.empty_like(xd)
+        db, dw = torch.empty((c1 - c0, B, 4), device="cuda"), torch.empty_like(wd)
+        bc.box_conv_split_fwd(xd, bd, wd, "4", y)
+        bc.box_conv_split_bwd(xd, bd, wd, "4", gd, dx, db, dw)
+        outs.append([host(t) for t in (y, dx, db, dw)])
+    for c0, part in ((0, outs[1]), (C - 8, outs[2])):
+        check(outs[0][0][:, c0 * B:(c0 + 8) * B], part[0], RTOL_F32, "y")
+        check(outs[0][1][:, c0:c0 + 8], part[1], RTOL_F32, "dx")
+        check(outs[0][2][c0:c0 + 8], part[2], RTOL_F32, "dboxes")
+        check(outs[0][3][c0:c0 + 8], part[3], RTOL_F32, "dpieces")
+    check(outs[0][1][:, :8], O.box_backward_split_input(g[:, :8 * B], bx[:8], pw[:8], "4", H, W), RTOL_F32, "dx")
+
+
 @pytest.mark.parametrize("H,W,stride", [(40, 257, 1), (100, 300, 1), (16, 300, 1), (50, 300, 2)])
 def test_wide_maps_in_bands(H, W, stride):
     """Few maps wider than 256: tables divided into row bands; and in place
